@@ -226,50 +226,46 @@ void launch_hx_generic(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, c
 // Rows outside the sphere are stored as zero; on input they must hold zero
 // (the layout contract), so they enter the stencil as the zero boundary.
 // ---------------------------------------------------------------------------
-template <class T>
-struct Quad;
-template <>
-struct Quad<float> {
-    using V = float4;
-    static constexpr int N = 4;
-};
-template <>
-struct Quad<double> {
-    using V = double2;
-    static constexpr int N = 2;
-};
-
-template <class V>
-__device__ inline V vzero();
-template <>
-__device__ inline float4 vzero<float4>() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-template <>
-__device__ inline double2 vzero<double2>() { return make_double2(0.0, 0.0); }
-
-__device__ inline float4 vfma(float s, float4 a, float4 c) {
-    return make_float4(fmaf(s, a.x, c.x), fmaf(s, a.y, c.y), fmaf(s, a.z, c.z), fmaf(s, a.w, c.w));
-}
-__device__ inline double2 vfma(double s, double2 a, double2 c) { return make_double2(fma(s, a.x, c.x), fma(s, a.y, c.y)); }
-__device__ inline float4 vadd(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
-__device__ inline double2 vadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-__device__ inline float4 vscale(float s, float4 a) { return make_float4(s * a.x, s * a.y, s * a.z, s * a.w); }
-__device__ inline double2 vscale(double s, double2 a) { return make_double2(s * a.x, s * a.y); }
-
 // ---------------------------------------------------------------------------
 // KB gather: C[a][lm][v] = sum_j (h^3 beta_alm(row_j)) X[row_j][v]
-// One workgroup per (projector atom, 64-quad vector chunk): 4 waves split the
-// support list (row j goes to wave j % 4), each lane owns one 16-byte quad of
-// vectors, and every lane keeps four independent row loads in flight.  The
-// four wave partials are summed in fixed order (deterministic).
+//
+// One workgroup per (projector atom, chunk of QL pieces of QN vectors).  The
+// support's rows are dealt to kSlots row slots (row j to slot j mod kSlots);
+// each slot sums its rows in order and the slots are added as a binary tree,
+// lowest slot bit first: over the RL = 64 / QL row lanes of a wave, then over
+// the WV = kSlots / RL waves.  So the sums do not depend on how a width is
+// spread over lanes: a vector's coefficients are the same bits in a block of
+// any width, and on every run.
+//
+// What bounds it: the re-reads of the support rows (~1,350 per atom, each row
+// in ~2.9 supports).  Chunks of 256 bytes keep the rows that the atoms in
+// flight on an XCD share in its 4 MB L2; the chunks run one after the other.
+// Against one workgroup of 4 waves per 1024-byte chunk, which also left a wave
+// 338 rows in series (us per launch, before -> now): 5 nm, 256 FP32 vectors
+// 690 -> 582 (7.6 TB/s of rows); 2.5 nm 219 -> 84; 5 nm, 128 FP64 870 -> 704;
+// 1.1 nm, 128 FP64 191 -> 24; 3 nm, 2 FP64 161 -> 20.  Chunks of 512 bytes
+// took 817 us at 5 nm FP32, of 128 bytes 614.
 // ---------------------------------------------------------------------------
-template <class T>
-__global__ void __launch_bounds__(256) kb_gather_kernel(const int64_t* __restrict__ sup_off,
-                                                        const int32_t* __restrict__ sup_row,
-                                                        const T* __restrict__ sup_beta, const T* __restrict__ X,
-                                                        int64_t ldx, int nvec, T* __restrict__ C, int n_proj) {
-    using V = typename Quad<T>::V;
-    constexpr int QN = Quad<T>::N;
-    __shared__ V part[4][4][64];
+constexpr int kSlots = 64;
+
+template <class T, int QN>
+struct alignas(sizeof(T) * QN) Piece {
+    T e[QN];
+};
+
+template <class T, int QN, int QL>
+__global__ void __launch_bounds__(kSlots * QL) kb_gather_kernel(const int64_t* __restrict__ sup_off,
+                                                                const int32_t* __restrict__ sup_row,
+                                                                const T* __restrict__ sup_beta,
+                                                                const T* __restrict__ X, int64_t ldx, int nvec,
+                                                                T* __restrict__ C, int n_proj) {
+    using V = Piece<T, QN>;
+    using B4 = Piece<T, 4>;
+    constexpr int RL = 64 / QL, WV = kSlots / RL;
+    // rows of a slot loaded together: 4, or 2 where the FP64 operands of 4
+    // would halve the waves that the registers allow (886 against 704 us at 5 nm)
+    constexpr int DEEP = sizeof(T) == 8 && QL >= 16 ? 2 : 4;
+    __shared__ V part[WV][4][QL];
     // XCD-aware order (grid = 8 * per_xcd): consecutive atoms, which share
     // support rows (the device numbers atoms along the Hilbert curve), run on
     // the same XCD and read the shared rows from its L2
@@ -278,99 +274,101 @@ __global__ void __launch_bounds__(256) kb_gather_kernel(const int64_t* __restric
     if (a >= n_proj) return;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int v = (blockIdx.y * 64 + lane) * QN;
+    const int q = lane % QL;
+    const int v = (int(blockIdx.y) * QL + q) * QN;
     const bool ok = v < nvec;
     const int64_t j0 = sup_off[a], j1 = sup_off[a + 1];
-    V s0 = vzero<V>(), s1 = vzero<V>(), s2 = vzero<V>(), s3 = vzero<V>();
-    int64_t j = j0 + wave;
-    for (; j + 12 < j1; j += 16) {
-        V x[4];
-        T bt[4][4];
+    const B4* beta = reinterpret_cast<const B4*>(sup_beta);
+    V s[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t jj = j + 4 * u;
-            x[u] = ok ? *reinterpret_cast<const V*>(X + int64_t(sup_row[jj]) * ldx + v) : vzero<V>();
+    for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int m = 0; m < 4; ++m) bt[u][m] = sup_beta[4 * jj + m];
+        for (int e = 0; e < QN; ++e) s[m].e[e] = T(0);
+    auto row = [&](int64_t j) {
+        V x;
+#pragma unroll
+        for (int e = 0; e < QN; ++e) x.e[e] = T(0);
+        if (ok) x = *reinterpret_cast<const V*>(X + int64_t(sup_row[j]) * ldx + v);
+        return x;
+    };
+    auto add = [&](const B4& b, const V& x) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int e = 0; e < QN; ++e) s[m].e[e] = fma(b.e[m], x.e[e], s[m].e[e]);
+    };
+    // slot wave RL + row lane: the rows that a wave loads together are
+    // consecutive, and so are their indices and weights
+    int64_t j = j0 + wave * RL + lane / QL;
+    for (; j + (DEEP - 1) * kSlots < j1; j += DEEP * kSlots) {
+        V x[DEEP];
+        B4 b[DEEP];
+#pragma unroll
+        for (int d = 0; d < DEEP; ++d) {
+            x[d] = row(j + d * kSlots);
+            b[d] = beta[j + d * kSlots];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            s0 = vfma(bt[u][0], x[u], s0);
-            s1 = vfma(bt[u][1], x[u], s1);
-            s2 = vfma(bt[u][2], x[u], s2);
-            s3 = vfma(bt[u][3], x[u], s3);
-        }
+        for (int d = 0; d < DEEP; ++d) add(b[d], x[d]);
     }
-    for (; j < j1; j += 4) {
-        const V x = ok ? *reinterpret_cast<const V*>(X + int64_t(sup_row[j]) * ldx + v) : vzero<V>();
-        const T* b = sup_beta + 4 * j;
-        s0 = vfma(b[0], x, s0);
-        s1 = vfma(b[1], x, s1);
-        s2 = vfma(b[2], x, s2);
-        s3 = vfma(b[3], x, s3);
-    }
-    part[wave][0][lane] = s0;
-    part[wave][1][lane] = s1;
-    part[wave][2][lane] = s2;
-    part[wave][3][lane] = s3;
+    for (; j < j1; j += kSlots) add(beta[j], row(j));
+#pragma unroll
+    for (int off = QL; off < 64; off *= 2)
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int e = 0; e < QN; ++e) s[m].e[e] += __shfl_xor(s[m].e[e], off, 64);
+    if (lane < QL)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) part[wave][m][q] = s[m];
     __syncthreads();
-    if (ok) {
-        const int lm = wave;   // each wave finishes one channel
-        const V t = vadd(vadd(vadd(part[0][lm][lane], part[1][lm][lane]), part[2][lm][lane]), part[3][lm][lane]);
-        *reinterpret_cast<V*>(C + (int64_t(a) * 4 + lm) * nvec + v) = t;
+    for (int t = threadIdx.x; t < 4 * QL; t += 64 * WV) {
+        const int lm = t / QL, qq = t % QL;
+        const int vv = (int(blockIdx.y) * QL + qq) * QN;
+        if (vv >= nvec) continue;
+        V r[WV];
+#pragma unroll
+        for (int w = 0; w < WV; ++w) r[w] = part[w][lm][qq];
+#pragma unroll
+        for (int h = 1; h < WV; h *= 2)
+#pragma unroll
+            for (int w = 0; w < WV; w += 2 * h)
+#pragma unroll
+                for (int e = 0; e < QN; ++e) r[w].e[e] += r[w + h].e[e];
+        *reinterpret_cast<V*>(C + (int64_t(a) * 4 + lm) * nvec + vv) = r[0];
     }
 }
 
-// scalar variant for blocks whose width or alignment rules out 16-byte quads
-template <class T>
-__global__ void __launch_bounds__(256) kb_gather_scalar_kernel(const int64_t* __restrict__ sup_off,
-                                                               const int32_t* __restrict__ sup_row,
-                                                               const T* __restrict__ sup_beta,
-                                                               const T* __restrict__ X, int64_t ldx, int nvec,
-                                                               T* __restrict__ C) {
-    __shared__ T part[4][4][64];
-    const int a = blockIdx.x;
-    const int lane = threadIdx.x & 63;
-    const int slice = threadIdx.x >> 6;
-    const int v = blockIdx.y * 64 + lane;
-    const int64_t j0 = sup_off[a], j1 = sup_off[a + 1];
-    T s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-    if (v < nvec) {
-        for (int64_t j = j0 + slice; j < j1; j += 4) {
-            const T x = X[int64_t(sup_row[j]) * ldx + v];
-            const T* b = sup_beta + 4 * j;
-            s0 += b[0] * x;
-            s1 += b[1] * x;
-            s2 += b[2] * x;
-            s3 += b[3] * x;
-        }
-    }
-    part[slice][0][lane] = s0;
-    part[slice][1][lane] = s1;
-    part[slice][2][lane] = s2;
-    part[slice][3][lane] = s3;
-    __syncthreads();
-    if (v < nvec) {
-        const int lm = slice;
-        C[(int64_t(a) * 4 + lm) * nvec + v] = ((part[0][lm][lane] + part[1][lm][lane]) + part[2][lm][lane]) + part[3][lm][lane];
-    }
+template <class T, int QN>
+static void gather_launch(chf_ham* H, const T* beta, const T* X, int64_t ldx, int nvec, T* C, hipStream_t s) {
+    const int n = int(H->proj.n_proj), pieces = nvec / QN;
+    int ql = 16;
+    while (ql > 1 && ql / 2 >= pieces) ql /= 2;
+    const dim3 grid(unsigned(8 * ((n + 7) / 8)), unsigned((pieces + ql - 1) / ql));
+    auto go = [&](auto qlc) {
+        constexpr int QL = decltype(qlc)::value;
+        kb_gather_kernel<T, QN, QL><<<grid, dim3(kSlots * QL), 0, s>>>(
+            H->sup_off.as<int64_t>(), H->sup_row.as<int32_t>(), beta, X, ldx, nvec, C, n);
+    };
+    if (ql == 16) go(std::integral_constant<int, 16>{});
+    else if (ql == 8) go(std::integral_constant<int, 8>{});
+    else if (ql == 4) go(std::integral_constant<int, 4>{});
+    else if (ql == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 1>{});
+    LAUNCH_CHECK();
 }
 
+// pieces of 16 bytes where the width, the leading dimension and the base
+// address allow, else of 8 (FP32), else single elements
 template <class T>
 void launch_kb_gather(chf_ham* H, const T* X, int64_t ldx, int nvec, T* C, hipStream_t s) {
     if (H->proj.n_proj == 0) return;
-    constexpr int QN = Quad<T>::N;
+    constexpr int Q16 = 16 / int(sizeof(T));
     const T* beta = std::is_same<T, double>::value ? H->sup_beta64.as<T>() : H->sup_beta32.as<T>();
-    if (nvec % QN == 0 && ldx % QN == 0 && uintptr_t(X) % 16 == 0) {
-        dim3 grid(unsigned(8 * ((H->proj.n_proj + 7) / 8)), unsigned((nvec / QN + 63) / 64));
-        kb_gather_kernel<T><<<grid, dim3(256), 0, s>>>(H->sup_off.as<int64_t>(), H->sup_row.as<int32_t>(), beta, X, ldx,
-                                                       nvec, C, int(H->proj.n_proj));
-    } else {
-        dim3 grid(unsigned(H->proj.n_proj), unsigned((nvec + 63) / 64));
-        kb_gather_scalar_kernel<T><<<grid, dim3(256), 0, s>>>(H->sup_off.as<int64_t>(), H->sup_row.as<int32_t>(), beta,
-                                                              X, ldx, nvec, C);
-    }
-    LAUNCH_CHECK();
+    const auto fits = [&](int qn) { return nvec % qn == 0 && ldx % qn == 0 && uintptr_t(X) % (qn * sizeof(T)) == 0; };
+    if (fits(Q16)) gather_launch<T, Q16>(H, beta, X, ldx, nvec, C, s);
+    else if (Q16 == 4 && fits(2)) gather_launch<T, 2>(H, beta, X, ldx, nvec, C, s);
+    else gather_launch<T, 1>(H, beta, X, ldx, nvec, C, s);
 }
 
 // 8-byte lane values of the tiled kernel: two floats or one double

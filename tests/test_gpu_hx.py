@@ -276,3 +276,21 @@ def test_filter_rejects_overlapping_work(system):
     with pytest.raises(B.ChfError) as e:
         s["Hg"].filter(buf[:, :32], buf[:, 16:48], 3, a, b, a0)
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-12), (torch.float32, 2e-6)])
+@pytest.mark.parametrize("m,ld", [(2, 2), (3, 3), (6, 6), (12, 14), (66, 66), (132, 136), (257, 257)])
+def test_projector_coefficients_do_not_depend_on_the_width(system, dtype, tol, m, ld):
+    # the KB gather spreads a width over 1 to 16 lanes in pieces of 16, 8 or
+    # element bytes (odd widths and leading dimensions take single elements);
+    # its sums are the same bits however the block is cut
+    s = system
+    X = random_block(s["g"].n, m, 2800 + m)
+    Xg = to_rows(s, X, dtype, ld)
+    Y = torch.zeros_like(Xg)
+    s["Hg"].apply(Xg[:, :m], Y[:, :m], generic=True)
+    assert relerr(from_rows(s, Y, m), s["Ho"].apply(X)) < tol
+    for c0, w in ((0, 1), (m // 2, m - m // 2)):
+        Z = torch.zeros_like(Xg)
+        s["Hg"].apply(Xg[:, c0:c0 + w], Z[:, c0:c0 + w], generic=True)
+        assert torch.equal(Z[:, c0:c0 + w], Y[:, c0:c0 + w])
