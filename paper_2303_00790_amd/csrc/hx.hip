@@ -13,11 +13,10 @@
 //                     Y = alpha (H X - c X) - beta Z  (Z may alias Y).
 //  * hx_tile          the same operator on the Hilbert-blocked layout: one
 //                     workgroup per (8^3 block, 32-float / 16-double vector
-//                     chunk), z-march with a 20-deep register window per
-//                     column, x/y halos staged in LDS (double-buffered), the
-//                     block atoms' KB coefficients staged in LDS and the KB
-//                     term applied inside the march.
-//  * hx_tiled         the same tile without staging, for blocks touched by
+//                     chunk), z-march with a register window per column, x/y
+//                     halos and the block atoms' KB coefficients staged in
+//                     LDS, the KB term as MFMA products inside the march.
+//  * hx_tiled         a tile of the same shape without staging, for blocks touched by
 //                     more than kMaxBlockAtoms projector atoms, Laplacian-only
 //                     products and Hamiltonians without projectors.
 #include <atomic>
@@ -400,41 +399,6 @@ __device__ inline V lz() {
     return v;
 }
 
-// compile-time loop: f(integral_constant<int, K>) for K = B .. E-1
-template <int B, int E, class F>
-__device__ inline void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
-// value of lane K of this lane's 16-lane row (DPP row_newbcast).  All rows
-// and banks are written and the source lane is always valid, so no old value
-// is needed (mov_dpp leaves it undefined and saves a register clear).
-template <int K>
-__device__ inline int row_bcast(int v) {
-    return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xF, 0xF, false);
-}
-template <int K>
-__device__ inline float row_bcast(float v) {
-    return __builtin_bit_cast(float, row_bcast<K>(__builtin_bit_cast(int, v)));
-}
-template <int K>
-__device__ inline double row_bcast(double v) {
-    const int2 w = __builtin_bit_cast(int2, v);
-    return __builtin_bit_cast(double, make_int2(row_bcast<K>(w.x), row_bcast<K>(w.y)));
-}
-
-__device__ inline void load4(const float* p, float* o) {
-    const float4 v = *reinterpret_cast<const float4*>(p);
-    o[0] = v.x, o[1] = v.y, o[2] = v.z, o[3] = v.w;
-}
-__device__ inline void load4(const double* p, double* o) {
-    const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
-    o[0] = a.x, o[1] = a.y, o[2] = b.x, o[3] = b.y;
-}
-
 // raw buffer access (vector memory through a 128-bit resource descriptor)
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
@@ -654,444 +618,454 @@ __global__ void __launch_bounds__(64 * kLanes) hx_tiled_kernel(int64_t n_blocks,
 
 // ---------------------------------------------------------------------------
 // Staged tile kernel: the Hilbert-blocked H X + recurrence with the KB term
-// applied inside the z-march from coefficients staged in LDS (blocks touched
-// by at most kMaxBlockAtoms projector atoms).  Same tile shape as above: one
-// workgroup per (8^3 block, 128-byte vector chunk), 1024 threads = 64
-// columns x 16 lanes of 8 bytes; a wave holds 4 columns of one row of the
-// block's plane, i.e. one aligned quad of 4 consecutive grid rows.
+// from coefficients staged in LDS (blocks touched by at most kMaxBlockAtoms
+// projector atoms).  One workgroup per (8^3 block, 128-byte vector chunk), 512
+// threads = 64 columns x 8 lanes of 16 bytes; a wave is one x line (8 columns)
+// of the block's plane.  Per plane of the z-march: the x/y neighbours come
+// from the plane and its 6-deep halos in LDS (a 20 x 20 square), the z
+// neighbours from the column's register window.
 //
-// The KB term of row r is sum_e h_l beta_lm(e) C_lm[slot(e)].  Lane i of a
-// column holds entry i of its row (LDS byte offset of the slot's staged
-// coefficients and h_l beta_lm), loaded two planes ahead; the wave walks the
-// entries up to the largest count among its quad's 4 rows (a per-block table
-// gives that count per quad and plane, so the loop bound is wave-uniform and
-// the loop needs no per-lane tests); lanes past their row's count hold zero
-// weights and add exact zeros.  Per pair of entries: one DPP add per entry
-// forms the LDS address (broadcast offset + lane base), two 16-byte LDS reads
-// fetch the coefficients, and FMAs with a DPP broadcast operand (row_newbcast
-// of the 16-lane group) apply them (FP64: one entry at a time, which keeps
-// the kernel within 128 registers).  Every DPP sequence starts with s_nop 1,
-// and an accumulator is written at most once every four FMAs, so no DPP
-// operand is read within two instructions of the VALU write that made it.
+// KB term of a plane: out[row][vec] += sum over slots and channels of
+// beta[row][slot][lm] C[slot][lm][vec], a matrix product.  Rows are taken in
+// groups of 16 (two x lines); for each atom that touches a group a 16 x 4
+// matrix of weights (zero outside the support) is kept in memory in operand
+// order, the 4 x 16 coefficients are read from LDS, and one 16x16x4 MFMA (FP32
+// or FP64, full precision) adds the atom.  The product is transposed (rows of
+// the result = vectors), so a lane ends up with 4 vectors of one row; it goes
+// through LDS to the lanes that hold that row.
+//
+// The plane is single-buffered (two barriers per plane), which keeps a
+// workgroup within half of the 160 KB of LDS and its threads within 128
+// registers: two workgroups run on a CU, one marching while the other loads.
+//
+// What bounds it: the chain of dependent loads at the start of a tile and the
+// memory latency of a plane, and the traffic behind L2 (15.1 GB per 5 nm FP32
+// launch in 2.49 ms = 6.0 TB/s, three times the two blocks read and the one
+// written, for the halos).  One 1024-thread workgroup per CU, whose KB term was
+// applied entry by entry on the VALU, took 21.9 us per tile at every size,
+// 7.8 of them before the first plane; now 16.3.  us per launch, before -> now:
+// 5 nm, 256 FP32 vectors 3337 -> 2494; 8 nm 10815 -> 8112; 5 nm, 128 FP64
+// 3389 -> 2635; 3 nm, 128 FP64 1011 -> 783; 2.5 nm, 256 FP32 674 -> 509;
+// 1.1 nm, 128 FP64 154 -> 110; 2 nm, 97 FP64 (8-byte pieces) 470 -> 473.
 // ---------------------------------------------------------------------------
-template <int K>
-__device__ inline void bcast_add2(int v, int add, int& r0, int& r1) {
-    asm("s_nop 1\n\t"
-        "v_add_u32_dpp %0, %2, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_u32_dpp %1, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
-        : "=&v"(r0), "=&v"(r1)
-        : "v"(v), "v"(add), "n"(K), "n"(K + 1));
-}
+constexpr int kSlotBytes = 512;      // staged coefficients of an atom: 4 channels x 128 bytes
+constexpr int kRowGroup = 16;        // rows of a KB weight matrix
+constexpr int kGroups = kBlockPts / kRowGroup;
+constexpr int kKbStep = 4;           // a group's atom list is padded to this multiple
+// slots of the half-LDS variant; blocks touched by more atoms take the one
+// with kMaxBlockAtoms slots, one workgroup per CU
+constexpr int kFewSlots = 40;
+// a row's 16-byte pieces lie kKbPitch apart in the KB plane: 16 rows and 32
+// bytes, so that the 8 pieces of two rows fall on different banks
+constexpr int kKbPitch = 16 * 16 + 32;
+constexpr int kKbBytes = (kBlockPts / 8) / kRowGroup * 8 * kKbPitch;
+constexpr int kPlaneBytes = 400 * 128;
 
-// a0..a3 += entry K and K+1 of (b0..b3) times the staged coefficients
-// ca = {ch0 v0, ch0 v1, ch1 v0, ch1 v1}, cb = {ch2 v0, ch2 v1, ch3 v0, ch3 v1}
-template <int K>
-__device__ inline void kb_fma2(float& a0, float& a1, float& a2, float& a3, float b0, float b1, float b2, float b3,
-                               float4 ca, float4 cb, float4 da, float4 db) {
-    asm("s_nop 1\n\t"
-        "v_fmac_f32_dpp %0, %4, %8 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %4, %9 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %5, %10 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %5, %11 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %6, %12 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %6, %13 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %7, %14 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %7, %15 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %4, %16 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %4, %17 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %5, %18 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %5, %19 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %6, %20 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %6, %21 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %7, %22 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %7, %23 row_newbcast:%25 row_mask:0xf bank_mask:0xf"
-        : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)
-        : "v"(b0), "v"(b1), "v"(b2), "v"(b3), "v"(ca.x), "v"(ca.y), "v"(ca.z), "v"(ca.w), "v"(cb.x), "v"(cb.y),
-          "v"(cb.z), "v"(cb.w), "v"(da.x), "v"(da.y), "v"(da.z), "v"(da.w), "v"(db.x), "v"(db.y), "v"(db.z),
-          "v"(db.w), "n"(K), "n"(K + 1));
-}
-
-// FP64, one entry: a0..a3 += entry K of (b0..b3) times ca = {ch0, ch1}, cb = {ch2, ch3}
-template <int K>
-__device__ inline void kb_fma1(double& a0, double& a1, double& a2, double& a3, double b0, double b1, double b2,
-                               double b3, double2 ca, double2 cb) {
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %5, %9 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %6, %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, %7, %11 row_newbcast:%12 row_mask:0xf bank_mask:0xf"
-        : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)
-        : "v"(b0), "v"(b1), "v"(b2), "v"(b3), "v"(ca.x), "v"(ca.y), "v"(cb.x), "v"(cb.y), "n"(K));
-}
-
-template <int K>
-__device__ inline int bcast_add1(int v, int add) {
-    int r;
-    asm("s_nop 1\n\t"
-        "v_add_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-        : "=v"(r)
-        : "v"(v), "v"(add), "n"(K));
-    return r;
-}
-
+typedef float mf4 __attribute__((ext_vector_type(4)));
+typedef double md4 __attribute__((ext_vector_type(4)));
 template <class T>
-struct KbLds;
+struct Wide;
 template <>
-struct KbLds<float> {
-    using C = float4;   // coefficients of one channel pair for the lane's 2 vectors
+struct Wide<float> {
+    static constexpr int N = 4;
+    using A = mf4;
 };
 template <>
-struct KbLds<double> {
-    using C = double2;  // one channel pair for the lane's vector
+struct Wide<double> {
+    static constexpr int N = 2;
+    using A = md4;
 };
+__device__ inline mf4 mfma4(float a, float b, mf4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ inline md4 mfma4(double a, double b, md4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
-template <class V>
-__device__ inline V bload_s(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, voff, int(soff), 0));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes in pieces of PB bytes (8 where rows are only 8-byte aligned).
+// policy 2 = non-temporal: Y_{k-1} is read and Y_{k+1} written once per
+// launch, so they should not displace the X rows that neighbouring tiles read
+// again as halos.
+template <class V, int PB, int POLICY>
+__device__ inline V bload16(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+    if constexpr (PB == 16) {
+        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, voff, int(soff), POLICY));
+    } else {
+        const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(r, voff, int(soff), POLICY);
+        const u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(r, voff, int(soff) + 8, POLICY);
+        return __builtin_bit_cast(V, u32x4{lo.x, lo.y, hi.x, hi.y});
+    }
 }
-// streaming access (non-temporal cache policy): Y_{k-1} is read and Y_{k+1}
-// written once per launch, so they should not displace the X rows that
-// neighbouring tiles read again as halos
-template <class V>
-__device__ inline V bload_nt(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, voff, int(soff), 2));
-}
-template <class V>
-__device__ inline void bstore_nt(V v, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, int(soff), 2);
-}
 
-// LDS of the staged tile kernel: staged KB coefficients first (their
-// addresses fit the 16-bit offset field of the LDS instructions), then the
-// two x/y planes
-constexpr int kCstBytes = kMaxBlockAtoms * 2 * 16 * 2 * 8;      // [slot][pair][lane][2] x 8 B
-constexpr int kPlaneBytes = 2 * 400 * 16 * 8;                   // [2][400][lane] x 8 B
-constexpr int kSlotBytes = 2 * 16 * 2 * 8;                      // one slot: 512 B
+template <class T, int PB, int SLOTS>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SLOTS <= kFewSlots ? 4 : 2)))
+hx_tile_kernel(int n_blocks, int n_chunks, const int32_t* __restrict__ bnb, const uint64_t* __restrict__ bmask,
+               const T* __restrict__ veff, const int32_t* __restrict__ rg_off, const int32_t* __restrict__ rg_slot,
+               const T* __restrict__ rg_beta, const int32_t* __restrict__ blk_atom_off,
+               const int32_t* __restrict__ blk_atoms, const T* __restrict__ C, int nvec, const T* __restrict__ X,
+               int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, StepCoef<T> k) {
+    constexpr int N = Wide<T>::N;
+    using V = Piece<T, N>;
+    using A = typename Wide<T>::A;
+    constexpr int CH = 8 * N;                 // vectors of a chunk
+    constexpr bool f32 = sizeof(T) == 4;
+    __shared__ __align__(16) char lds[SLOTS * kSlotBytes + kPlaneBytes + kKbBytes];
+    char* const lds_kb = lds + SLOTS * kSlotBytes;
+    V (*plane)[8] = reinterpret_cast<V (*)[8]>(lds + SLOTS * kSlotBytes + kKbBytes);
 
-template <class T>
-__global__ void __launch_bounds__(1024) hx_tile_kernel(int64_t n_blocks, int n_chunks, const int32_t* __restrict__ bnb,
-                                                       const uint64_t* __restrict__ bmask, const T* __restrict__ veff,
-                                                       const int32_t* __restrict__ ent_off,
-                                                       const int32_t* __restrict__ ent_soff,
-                                                       const T* __restrict__ ent_beta,
-                                                       const uint64_t* __restrict__ qcnt,
-                                                       const int32_t* __restrict__ blk_atom_off,
-                                                       const int32_t* __restrict__ blk_atoms, const T* __restrict__ C,
-                                                       int nvec, const T* __restrict__ X, int64_t ldx, T* Y,
-                                                       int64_t ldy, const T* Z, int64_t ldz, StepCoef<T> k) {
-    using V = typename Lane<T>::V;
-    using CL = typename KbLds<T>::C;
-    constexpr int LANES = 16;
-    constexpr int LN = Lane<T>::N;
-    constexpr int CH = LANES * LN;
-    constexpr int NT = 64 * LANES;
-    constexpr int LSH = 4;
-    constexpr int CPW = 4;
-    __shared__ __align__(16) char lds[kCstBytes + kPlaneBytes];
-    V (*plane)[400][LANES] = reinterpret_cast<V (*)[400][LANES]>(lds + kCstBytes);
-    V (*cst)[2][LANES][2] = reinterpret_cast<V (*)[2][LANES][2]>(lds);
-
-    // XCD-aware tile order, as in the unstaged kernel: each XCD takes a
-    // contiguous run of the tile sequence.  FP32 tiles run block-major (a
-    // block's vector chunks adjacent, sharing its tables and staged
-    // coefficients in L2); FP64 tiles run chunk-major (each chunk's blocks
-    // along the Hilbert curve, so the tiles in flight on an XCD are
-    // neighbouring blocks whose halos overlap), which measured faster for
-    // the FP64 kernel, whose traffic sits near the copy ceiling.
-    const int64_t ntiles = n_blocks * n_chunks;
-    const int64_t per_xcd = (ntiles + 7) / 8;
-    const int64_t tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    // XCD-aware tile order: workgroup ids are dealt round-robin to the 8
+    // XCDs; each XCD takes a contiguous run of the tile sequence, a block's
+    // chunks one after the other: they share its tables and coefficients, and
+    // together they cover whole rows, which spreads the requests over all L2
+    // channels.  (One chunk of all blocks after the other shares more halos but
+    // reads 128 bytes of every row: 2494 -> 2672 us at 5 nm, 256 FP32 vectors.)
+    const unsigned ntiles = unsigned(n_blocks) * unsigned(n_chunks);
+    const unsigned per_xcd = (ntiles + 7) / 8;
+    const unsigned tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (tile >= ntiles) return;
+    const int blk = int(tile / unsigned(n_chunks));
+    const int chunk = int(tile % unsigned(n_chunks));
 
     const int t = threadIdx.x;
-    const int p = t & (LANES - 1);
-    const int col = t >> LSH;
-    const int cx = col & 7, cy = col >> 3;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const unsigned es = sizeof(T);
-    const unsigned blk_bytes = unsigned(kBlockPts) * unsigned(ldx) * es;
+    const int p = t & 7;
+    const int col = t >> 3;
+    const int cx = col & 7;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // = the y line of this wave's columns
+    const int lane = t & 63;
+    constexpr unsigned es = sizeof(T);
     constexpr unsigned kOOB = 0x80000000u;
+    // bytes of a block from its first to its last vector: the second piece of a
+    // ragged row's last lane may lie past the row, but never past this
+    auto blk_bytes = [&](int64_t ld) { return (unsigned(kBlockPts - 1) * unsigned(ld) + unsigned(nvec)) * es; };
     const unsigned plane_x = 64u * unsigned(ldx) * es;
     const unsigned plane_z = 64u * unsigned(ldz) * es;
     const unsigned plane_y = 64u * unsigned(ldy) * es;
-    const int ctr = (cy + 6) * 20 + (cx + 6);
+    const int ctr = (wave + 6) * 20 + (cx + 6);
     auto res_x = [&](int32_t nb) {
-        return make_rsrc(nb >= 0 ? X + int64_t(nb) * kBlockPts * ldx : X, nb >= 0 ? blk_bytes : 0u);
+        return make_rsrc(nb >= 0 ? X + int64_t(nb) * kBlockPts * ldx : X, nb >= 0 ? blk_bytes(ldx) : 0u);
     };
-
-    constexpr bool chunk_major = sizeof(T) == 8;
-    const int64_t blk = chunk_major ? tile % n_blocks : tile / n_chunks;
-    const int chunk = chunk_major ? int(tile / n_blocks) : int(tile - blk * n_chunks);
     int32_t nbs[6];
 #pragma unroll
-    for (int f = 0; f < 6; ++f) nbs[f] = bnb[6 * blk + f];
-    const int vbase = chunk * CH + p * LN;
+    for (int f = 0; f < 6; ++f) nbs[f] = bnb[6 * int64_t(blk) + f];
+    const int vbase = chunk * CH + p * N;
     const bool vok = vbase < nvec;
-    const unsigned off_x = vok ? (unsigned(cx + 8 * cy) * unsigned(ldx) + unsigned(vbase)) * es : kOOB;
-    const unsigned off_z = vok ? (unsigned(cx + 8 * cy) * unsigned(ldz) + unsigned(vbase)) * es : kOOB;
-    const __amdgpu_buffer_rsrc_t rOwn = res_x(int32_t(blk));
+    const unsigned vbytes = unsigned(vbase) * es;
+    const unsigned off_x = vok ? unsigned(col) * unsigned(ldx) * es + vbytes : kOOB;
+    const unsigned off_z = vok ? unsigned(col) * unsigned(ldz) * es + vbytes : kOOB;
+    const unsigned off_y = vok ? unsigned(col) * unsigned(ldy) * es + vbytes : kOOB;
+    const __amdgpu_buffer_rsrc_t rOwn = res_x(blk);
     const __amdgpu_buffer_rsrc_t rZm = res_x(nbs[4]);
     const __amdgpu_buffer_rsrc_t rZp = res_x(nbs[5]);
     const __amdgpu_buffer_rsrc_t rZ =
-        make_rsrc(Z ? Z + blk * kBlockPts * ldz : X, Z ? unsigned(kBlockPts) * unsigned(ldz) * es : 0u);
-    // halo slot u of a wave covers CPW consecutive halo rows, all on one side
+        make_rsrc(Z ? Z + int64_t(blk) * kBlockPts * ldz : X, Z ? blk_bytes(ldz) : 0u);
+    const __amdgpu_buffer_rsrc_t rY = make_rsrc(Y + int64_t(blk) * kBlockPts * ldy, blk_bytes(ldy));
+    // halo slot u of a wave: 8 consecutive halo rows, all on one side (48 rows
+    // per side)
     int hrow[3];
     __amdgpu_buffer_rsrc_t rH[3];
     unsigned hoff[3];
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
-        const int hr0 = CPW * wave + 64 * u;
-        const int side = __builtin_amdgcn_readfirstlane(hr0 / 48);
-        const int hr = col + 64 * u;
-        const int rem = hr - 48 * side;
-        int lx, ly, x, y, nb;
+        const int side = (8 * wave + 64 * u) / 48;
+        const int rem = col + 64 * u - 48 * side;
+        int lx, ly, x, y;
         if (side < 2) {
             const int c6 = rem % 6;
             ly = rem / 6;
             lx = side == 0 ? 2 + c6 : c6;
             x = side == 0 ? c6 - 6 : 8 + c6;
             y = ly;
-            nb = side == 0 ? nbs[0] : nbs[1];
         } else {
             const int r6 = rem / 8;
             lx = rem % 8;
             ly = side == 2 ? 2 + r6 : r6;
             x = lx;
             y = side == 2 ? r6 - 6 : 8 + r6;
-            nb = side == 2 ? nbs[2] : nbs[3];
         }
         hrow[u] = (y + 6) * 20 + (x + 6);
-        rH[u] = res_x(__builtin_amdgcn_readfirstlane(nb));
-        hoff[u] = vok ? (unsigned(lx + 8 * ly) * unsigned(ldx) + unsigned(vbase)) * es : kOOB;
+        rH[u] = res_x(side == 0 ? nbs[0] : side == 1 ? nbs[1] : side == 2 ? nbs[2] : nbs[3]);
+        hoff[u] = vok ? unsigned(lx + 8 * ly) * unsigned(ldx) * es + vbytes : kOOB;
     }
     auto load_plane = [&](int zz) -> V {
-        if (zz < 0) return bload_s<V>(rZm, off_x, unsigned(zz + 8) * plane_x);
-        if (zz >= 8) return bload_s<V>(rZp, off_x, unsigned(zz - 8) * plane_x);
-        return bload_s<V>(rOwn, off_x, unsigned(zz) * plane_x);
-    };
-    auto load_halo = [&](int z, V* hv) {
-#pragma unroll
-        for (int u = 0; u < 3; ++u) hv[u] = bload_s<V>(rH[u], hoff[u], unsigned(z) * plane_x);
-    };
-    auto store_halo = [&](int b, const V* hv) {
-#pragma unroll
-        for (int u = 0; u < 3; ++u) plane[b][hrow[u]][p] = hv[u];
+        if (zz < 0) return bload16<V, PB, 0>(rZm, off_x, unsigned(zz + 8) * plane_x);
+        if (zz >= 8) return bload16<V, PB, 0>(rZp, off_x, unsigned(zz - 8) * plane_x);
+        return bload16<V, PB, 0>(rOwn, off_x, unsigned(zz) * plane_x);
     };
 
-    const int64_t base = blk * kBlockPts;
-    const int lrow = cx + 8 * cy;
-    // KB entries of the block: a buffer over its entries, so that lanes past
-    // their row's count read zeros (out-of-range buffer loads return 0)
-    const int e_blk0 = ent_off[base];
-    const int e_cnt = ent_off[base + kBlockPts] - e_blk0;
-    const uint64_t qc8 = qcnt[blk * 16 + wave];
-    V cstage[4];
-    {
-        const int a0 = blk_atom_off[blk];
-        const int na = min(blk_atom_off[blk + 1] - a0, kMaxBlockAtoms);
+    // the X window of this column, the halos of plane 0, Y_{k-1} and V_eff
+    V w[20], hv[3];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = t + NT * u;         // (atom slot, lm, lane)
-            const int sl = e >> (LSH + 2), lm = (e >> LSH) & 3, lp = e & (LANES - 1);
-            const int vb = chunk * CH + lp * LN;
-            if (sl < na && vb < nvec)         // staged with alpha applied
-                cstage[u] = lscale(k.alpha, *reinterpret_cast<const V*>(C + (int64_t(blk_atoms[a0 + sl]) * 4 + lm) * nvec + vb));
-            else
-                cstage[u] = lz<V>();
-        }
-    }
-    const __amdgpu_buffer_rsrc_t rB = make_rsrc(ent_beta + 4 * int64_t(e_blk0), unsigned(e_cnt) * 4u * es);
-    const __amdgpu_buffer_rsrc_t rS = make_rsrc(ent_soff + e_blk0, unsigned(e_cnt) * 4u);
-    // entries of row z: lane i holds entry i (LDS byte offset of its slot's
-    // coefficients and its 4 weights); the row's entry range comes RL planes
-    // before the entries, which come PD planes before their use (both 1 for
-    // FP64, whose 4 weights take twice the registers)
-    constexpr int PD = sizeof(T) == 4 ? 2 : 1;
-    constexpr int RL = sizeof(T) == 4 ? 2 : 1;   // lead of the entry ranges over the entries
-    int2 e_rng[8];
-    int e_soff[8];
-    T e_b[8][4];
-    // (a dword-aligned 8-byte load: the row's first entry and the next row's)
-    auto load_range = [&](int z) { __builtin_memcpy(&e_rng[z], ent_off + base + lrow + 64 * z, sizeof(int2)); };
-    auto load_entries = [&](int z) {
-        const int en = e_rng[z].x + p;
-        const unsigned rel = unsigned(en - e_blk0);
-        const bool ok = en < e_rng[z].y;
-        e_soff[z] = int(__builtin_amdgcn_raw_buffer_load_b32(rS, ok ? rel * 4u : kOOB, 0, 0));
-        if constexpr (sizeof(T) == 4) {
-            const float4 b4 = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rB, ok ? rel * 16u : kOOB, 0, 0));
-            e_b[z][0] = b4.x, e_b[z][1] = b4.y, e_b[z][2] = b4.z, e_b[z][3] = b4.w;
+    for (int i = 0; i < 13; ++i) w[i] = load_plane(i - 6);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) hv[u] = bload16<V, PB, 0>(rH[u], hoff[u], 0u);
+
+    // KB coefficients of the block's atoms, alpha applied: 16 slots a round
+    const int a0 = blk_atom_off[blk];
+    const int na = min(blk_atom_off[blk + 1] - a0, SLOTS);
+    for (int sl = t >> 5; sl < na; sl += 16) {
+        const int lm = (t >> 3) & 3;
+        const T* src = C + (int64_t(blk_atoms[a0 + sl]) * 4 + lm) * nvec + vbase;
+        V c;
+#pragma unroll
+        for (int e = 0; e < N; ++e) c.e[e] = T(0);
+        if constexpr (PB == 16) {
+            if (vok) c = *reinterpret_cast<const V*>(src);
         } else {
-            const unsigned o = ok ? rel * 32u : kOOB;
-            const double2 b0 = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rB, o, 0, 0));
-            const double2 b1 = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rB, o, 16, 0));
-            e_b[z][0] = b0.x, e_b[z][1] = b0.y, e_b[z][2] = b1.x, e_b[z][3] = b1.y;
+#pragma unroll
+            for (int e = 0; e < N; ++e)
+                if (vbase + e < nvec) c.e[e] = src[e];
+        }
+#pragma unroll
+        for (int e = 0; e < N; ++e) c.e[e] *= k.alpha;
+        *reinterpret_cast<V*>(lds + sl * kSlotBytes + lm * 128 + p * 16) = c;
+    }
+    auto stage = [&](int z) {
+#pragma unroll
+        for (int u = 0; u < 3; ++u) plane[hrow[u]][p] = hv[u];
+        plane[ctr][p] = w[z + 6];
+    };
+    stage(0);
+
+    // KB product of a plane.  FP32: 4 row groups x 2 halves of the chunk, one
+    // for each wave.  FP64: 4 row groups, taken by waves 0-3 for even planes
+    // and 4-7 for odd ones.
+    const int grp = f32 ? wave >> 1 : wave & 3;
+    const int lk = lane >> 4, li = lane & 15;
+    // operand A of a slot: coefficient lm = lk of result row li, which is
+    // vector li of the half (FP32), or 4 (li % 4) + li / 4 (FP64, so that a
+    // lane's four result rows are consecutive vectors)
+    const int a_off = lk * 128 + (f32 ? (wave & 1) * 64 + li * 4 : (4 * (li & 3) + (li >> 2)) * 8);
+    auto kb_mine = [&](int z) { return f32 || (wave >> 2) == (z & 1); };
+    // this wave's entries, plane after plane (one row group's 8 planes are
+    // consecutive): the weights of the first 2 kKbStep entries of a plane are
+    // fetched ahead (kb_fetch), while the plane before it is worked on
+    int e_off[9];
+    const int64_t rg0 = int64_t(blk) * kGroups + grp * 8;
+#pragma unroll
+    for (int z = 0; z < 9; ++z) e_off[z] = rg_off[rg0 + z];
+    const __amdgpu_buffer_rsrc_t rW =
+        make_rsrc(rg_beta + int64_t(e_off[0]) * 64, unsigned(e_off[8] - e_off[0]) * 64u * es);
+    T kb_b[2 * kKbStep];
+    auto weight = [&](int e) {
+        const unsigned o = unsigned(e - e_off[0]) * 64u * es;
+        if constexpr (f32) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rW, unsigned(lane) * es, int(o), 0));
+        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rW, unsigned(lane) * es, int(o), 0));
+    };
+    auto kb_fetch = [&](int z, int part) {
+        if (!kb_mine(z)) return;
+#pragma unroll
+        for (int u = part * kKbStep; u < (part + 1) * kKbStep; ++u) kb_b[u] = weight(e_off[z] + u);
+    };
+    auto kb_step = [&](A acc, int e, const T* b) {
+        T a[kKbStep];
+#pragma unroll
+        for (int u = 0; u < kKbStep; ++u) a[u] = *reinterpret_cast<const T*>(lds + rg_slot[e + u] + a_off);
+#pragma unroll
+        for (int u = 0; u < kKbStep; ++u) acc = mfma4(a[u], b[u], acc);
+        return acc;
+    };
+    auto kb_plane = [&](int z) {
+        A acc = {0, 0, 0, 0};
+        if (!kb_mine(z)) return acc;
+        const int e0 = e_off[z], e1 = e_off[z + 1];
+        if (e0 < e1) acc = kb_step(acc, e0, kb_b);
+        if (e0 + kKbStep < e1) acc = kb_step(acc, e0 + kKbStep, kb_b + kKbStep);
+        for (int e = e0 + 2 * kKbStep; e < e1; e += kKbStep) {
+            T b[kKbStep];
+#pragma unroll
+            for (int u = 0; u < kKbStep; ++u) b[u] = weight(e + u);
+            acc = kb_step(acc, e, b);
+        }
+        return acc;
+    };
+    // row li of the group, pieces lk (FP32: of this half) or 2 lk, 2 lk + 1
+    char* const kb_w = lds_kb + (grp * 8 + (f32 ? (wave & 1) * 4 + lk : 2 * lk)) * kKbPitch + li * 16;
+    auto kb_store = [&](int z, A acc) {
+        if (!kb_mine(z)) return;
+        if constexpr (f32) {
+            *reinterpret_cast<A*>(kb_w) = acc;
+        } else {
+            *reinterpret_cast<V*>(kb_w) = V{{acc[0], acc[1]}};
+            *reinterpret_cast<V*>(kb_w + kKbPitch) = V{{acc[2], acc[3]}};
         }
     };
-#pragma unroll
-    for (int z = 0; z < PD + RL; ++z) load_range(z);
-    // the X window of this column, the first two halo planes, Y_{k-1} and
-    // V_eff of plane 0
-    // (X planes are loaded WL planes before the stencil first needs them: 2,
-    // or 1 for FP64 to stay within 128 registers)
-    constexpr int WL = sizeof(T) == 4 ? 2 : 1;
-    V w[20];
-#pragma unroll
-    for (int i = 0; i < 12 + WL; ++i) w[i] = load_plane(i - 6);
-    V hv0[3], hv[3];
-    load_halo(0, hv0);
-    load_halo(1, hv);
-    V zcur = bload_nt<V>(rZ, off_z, 0u);      // zero when there is no Z (empty buffer)
-    T vcur = veff[base + lrow];
-#pragma unroll
-    for (int z = 0; z < PD; ++z) load_entries(z);
-    store_halo(0, hv0);
-    plane[0][ctr][p] = w[6];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = t + NT * u;
-        const int sl = e >> (LSH + 2), lm = (e >> LSH) & 3, lp = e & (LANES - 1);
-        if (sl < kMaxBlockAtoms) cst[sl][lm >> 1][lp][lm & 1] = cstage[u];
-    }
+    const char* const kb_r = lds_kb + ((col >> 4) * 8 + p) * kKbPitch + (col & 15) * 16;
+    kb_fetch(0, 0);
+    __syncthreads();
+    kb_fetch(0, 1);
+    kb_store(0, kb_plane(0));
     __syncthreads();
 
-    const __amdgpu_buffer_rsrc_t rY = make_rsrc(Y + base * ldy, unsigned(kBlockPts) * unsigned(ldy) * es);
-    const unsigned off_y = vok ? (unsigned(lrow) * unsigned(ldy) + unsigned(vbase)) * es : kOOB;
-    const int lane_off = p * 16;           // this lane's 16 bytes within a slot's channel pair
+    const int64_t base = int64_t(blk) * kBlockPts;
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
-        const int b = z & 1;
+        // loads of this plane's update and of the next plane
+        const V zc = bload16<V, PB, 2>(rZ, off_z, unsigned(z) * plane_z);   // zero without Z (empty buffer)
+        const T vr = veff[base + col + 64 * z];
         if (z < 7) {
-            store_halo(b ^ 1, hv);
-            plane[b ^ 1][ctr][p] = w[z + 7];
+#pragma unroll
+            for (int u = 0; u < 3; ++u) hv[u] = bload16<V, PB, 0>(rH[u], hoff[u], unsigned(z + 1) * plane_x);
+            w[z + 13] = load_plane(z + 7);
         }
-        // loads, in the order they are needed: next plane's halos, Y_{k-1}
-        // and V_eff first, then the entries of plane z + PD, the entry range
-        // of plane z + PD + RL and the X plane z + 8
-        if (z < 6) load_halo(z + 2, hv);
-        V znext = lz<V>();
-        T vnext = T(0);
-        if (z < 7) {
-            znext = bload_nt<V>(rZ, off_z, unsigned(z + 1) * plane_z);
-            vnext = veff[base + lrow + 64 * (z + 1)];
-        }
-        if (z + PD < 8) load_entries(z + PD);
-        if (z + PD + RL < 8) load_range(z + PD + RL);
-        if (z + 6 + WL < 14) w[z + 12 + WL] = load_plane(z + 6 + WL);
 
         // alpha-scaled off-diagonal stencil; the diagonal is added last
-        V acc = lz<V>();
+        V acc = *reinterpret_cast<const V*>(kb_r);
 #pragma unroll
         for (int s = 1; s <= 6; ++s) {
-            V sum = ladd(w[z + 6 - s], w[z + 6 + s]);
-            sum = ladd(sum, plane[b][ctr - s][p]);
-            sum = ladd(sum, plane[b][ctr + s][p]);
-            sum = ladd(sum, plane[b][ctr - 20 * s][p]);
-            sum = ladd(sum, plane[b][ctr + 20 * s][p]);
-            acc = s == 1 ? lscale(k.ac[1], sum) : lfma(k.ac[s], sum, acc);
+            const V xm = plane[ctr - s][p], xp = plane[ctr + s][p], ym = plane[ctr - 20 * s][p],
+                    yp = plane[ctr + 20 * s][p];
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                T sum = w[z + 6 - s].e[e] + w[z + 6 + s].e[e];
+                sum += xm.e[e];
+                sum += xp.e[e];
+                sum += ym.e[e];
+                sum += yp.e[e];
+                acc.e[e] = fma(k.ac[s], sum, acc.e[e]);
+            }
         }
-        const V xc = w[z + 6];
-        {
-            // KB term of row z: entries in pairs up to the quad's largest count
-            const int qc = int((qc8 >> (8 * z)) & 0xffu);
-            T a[4];
-            if constexpr (sizeof(T) == 4) {
-                a[0] = acc.x, a[1] = acc.y, a[2] = 0.f, a[3] = 0.f;
-            } else {
-                a[0] = acc, a[1] = 0.0, a[2] = 0.0, a[3] = 0.0;
-            }
-            if constexpr (sizeof(T) == 4) {
-                static_for<0, 8>([&](auto gc) {
-                    constexpr int kk = 2 * decltype(gc)::value;
-                    if (kk < qc) {
-                        int ad0, ad1;
-                        bcast_add2<kk>(e_soff[z], lane_off, ad0, ad1);
-                        const CL ca = *reinterpret_cast<const CL*>(lds + ad0);
-                        const CL cb = *reinterpret_cast<const CL*>(lds + ad0 + 256);
-                        const CL da = *reinterpret_cast<const CL*>(lds + ad1);
-                        const CL db = *reinterpret_cast<const CL*>(lds + ad1 + 256);
-                        kb_fma2<kk>(a[0], a[1], a[2], a[3], e_b[z][0], e_b[z][1], e_b[z][2], e_b[z][3], ca, cb, da,
-                                    db);
-                    }
-                });
-            } else {
-                static_for<0, 16>([&](auto kc) {
-                    constexpr int kk = decltype(kc)::value;
-                    if (kk < qc) {
-                        const int ad = bcast_add1<kk>(e_soff[z], lane_off);
-                        const CL ca = *reinterpret_cast<const CL*>(lds + ad);
-                        const CL cb = *reinterpret_cast<const CL*>(lds + ad + 256);
-                        kb_fma1<kk>(a[0], a[1], a[2], a[3], e_b[z][0], e_b[z][1], e_b[z][2], e_b[z][3], ca, cb);
-                    }
-                });
-            }
-            if (qc > 16) {                    // rows with more than 16 entries: the rest from memory
-                int2 rng;
-                __builtin_memcpy(&rng, ent_off + base + lrow + 64 * z, sizeof(int2));
-                for (int en = rng.x + 16; en < rng.y; ++en) {
-                    const T* bb = ent_beta + 4 * int64_t(en);
-                    const char* cs = lds + ent_soff[en] + lane_off;
-                    const CL c01 = *reinterpret_cast<const CL*>(cs);
-                    const CL c23 = *reinterpret_cast<const CL*>(cs + 256);
-                    if constexpr (sizeof(T) == 4) {
-                        a[0] = fmaf(bb[0], c01.x, a[0]);
-                        a[1] = fmaf(bb[0], c01.y, a[1]);
-                        a[2] = fmaf(bb[1], c01.z, a[2]);
-                        a[3] = fmaf(bb[1], c01.w, a[3]);
-                        a[0] = fmaf(bb[2], c23.x, a[0]);
-                        a[1] = fmaf(bb[2], c23.y, a[1]);
-                        a[2] = fmaf(bb[3], c23.z, a[2]);
-                        a[3] = fmaf(bb[3], c23.w, a[3]);
-                    } else {
-                        a[0] = fma(bb[0], c01.x, a[0]);
-                        a[1] = fma(bb[1], c01.y, a[1]);
-                        a[2] = fma(bb[2], c23.x, a[2]);
-                        a[3] = fma(bb[3], c23.y, a[3]);
-                    }
-                }
-            }
-            if constexpr (sizeof(T) == 4)
-                acc = make_float2(a[0] + a[2], a[1] + a[3]);
-            else
-                acc = (a[0] + a[1]) + (a[2] + a[3]);
+        const T dg = fma(k.alpha, vr, k.d0);
+        // rows outside the sphere are stored as zero
+        const bool in = (unsigned(bmask[8 * int64_t(blk) + z] >> (8 * wave)) >> cx) & 1u;
+        V y;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const T v = fma(-k.beta, zc.e[e], fma(dg, w[z + 6].e[e], acc.e[e]));   // beta = 0 without Z
+            y.e[e] = in ? v : T(0);
         }
-        const T dg = T(fma(k.alpha, vcur, k.d0));
-        V y = lfma(dg, xc, acc);
-        y = lfma(-k.beta, zcur, y);            // beta = 0 when there is no Z
-        // rows outside the sphere are stored as zero: the wave's quad is rows
-        // 4 wave .. 4 wave + 3 of the plane, 16 lanes each
-        const uint64_t m4 = (bmask[8 * blk + z] >> (4 * wave)) & 0xfu;
-        const uint64_t spread = (m4 & 1u) | ((m4 & 2u) << 15) | ((m4 & 4u) << 30) | ((m4 & 8u) << 45);
-        const bool in = __builtin_amdgcn_inverse_ballot_w64(spread * 0xffffu);
-        bstore_nt<V>(in ? y : lz<V>(), rY, off_y, unsigned(z) * plane_y);
-        zcur = znext;
-        vcur = vnext;
-        __syncthreads();
+        // The plane's offset is part of the vector offset: a 128-bit store with
+        // a scalar offset register was seen to lose its last dword when the
+        // next instruction overwrites the data register; the compiler keeps
+        // that distance only for stores without one.
+        const u32x4 yb = __builtin_bit_cast(u32x4, y);
+        const unsigned oy = off_y + unsigned(z) * plane_y;
+        if constexpr (PB == 16) {
+            __builtin_amdgcn_raw_buffer_store_b128(yb, rY, oy, 0, 2);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{yb.x, yb.y}, rY, oy, 0, 2);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{yb.z, yb.w}, rY, vbase + N / 2 < nvec ? oy + 8 : kOOB, 0, 2);
+        }
+        if (z < 7) {
+            // (the weights are not fetched above the stencil, whose operands
+            // take the registers)
+            __builtin_amdgcn_sched_barrier(0);
+            kb_fetch(z + 1, 0);
+            if (f32) kb_fetch(z + 1, 1);
+            __syncthreads();
+            stage(z + 1);
+            if (!f32) kb_fetch(z + 1, 1);
+            kb_store(z + 1, kb_plane(z + 1));
+            __syncthreads();
+        }
     }
+}
+
+// weights of the KB row groups in MFMA operand order: lane 16 k + j of entry e
+// holds channel k of row j of the group, zero where the row is outside the
+// atom's support or the entry only pads the list
+template <class T>
+__global__ void __launch_bounds__(64) rg_beta_kernel(const int32_t* __restrict__ rg_off,
+                                                     const int32_t* __restrict__ rg_slot,
+                                                     const int32_t* __restrict__ rg_len,
+                                                     const int32_t* __restrict__ ent_off,
+                                                     const int32_t* __restrict__ ent_soff,
+                                                     const T* __restrict__ ent_beta, T* __restrict__ rg_beta) {
+    const int64_t rg = blockIdx.x;
+    const int lane = threadIdx.x;
+    const int64_t row = rg / kGroups * kBlockPts + rg % 8 * 64 + rg / 8 % 4 * kRowGroup + (lane & 15);
+    const int e0 = rg_off[rg], e1 = rg_off[rg + 1], n = rg_len[rg];
+    for (int e = e0; e < e1; ++e) {
+        T b = T(0);
+        if (e - e0 < n)
+            for (int en = ent_off[row]; en < ent_off[row + 1]; ++en)
+                if (ent_soff[en] == rg_slot[e]) b = ent_beta[4 * int64_t(en) + (lane >> 4)];
+        rg_beta[int64_t(e) * 64 + lane] = b;
+    }
+}
+
+// Row-group lists of the staged tile kernel (Hilbert layout, blocks of at most
+// kMaxBlockAtoms atoms): per group the LDS offsets of the slots whose atoms
+// touch it, and their weights.  Built from the entry tables at ham_build.
+void build_row_groups(chf_ham* H, hipStream_t s) {
+    const HostProj& P = H->proj;
+    if (H->grid.ordering != CHF_ORDER_HILBERT || P.n_proj == 0 || P.max_block_atoms > kMaxBlockAtoms) return;
+    const int64_t n_rg = H->grid.n_blocks * kGroups;
+    std::vector<int32_t> off(size_t(n_rg) + 1, 0), len(size_t(n_rg), 0), slot;
+    for (int64_t rg = 0; rg < n_rg; ++rg) {
+        // (block, x-line pair, plane): the planes of a pair are consecutive
+        const int64_t row = rg / kGroups * kBlockPts + rg % 8 * 64 + rg / 8 % 4 * kRowGroup;
+        uint64_t m = 0;
+        for (int64_t e = P.ent_off[size_t(row)]; e < P.ent_off[size_t(row + kRowGroup)]; ++e)
+            m |= uint64_t(1) << P.ent_slot[size_t(e)];
+        len[size_t(rg)] = __builtin_popcountll(m);
+        for (; m; m &= m - 1) slot.push_back(__builtin_ctzll(m) * kSlotBytes);
+        while (slot.size() % kKbStep) slot.push_back(0);
+        CHF_REQUIRE(slot.size() < (size_t(1) << 31), "ham_build: more than 2^31 row-group entries");
+        off[size_t(rg) + 1] = int32_t(slot.size());
+    }
+    DevBuf dlen;
+    upload(H->rg_off, off, s);
+    upload(H->rg_slot, slot, s);
+    upload(dlen, len, s);
+    auto fill = [&](auto* beta, const auto* src) {
+        using T = std::remove_pointer_t<decltype(beta)>;
+        rg_beta_kernel<T><<<dim3(unsigned(n_rg)), dim3(64), 0, s>>>(H->rg_off.as<int32_t>(), H->rg_slot.as<int32_t>(),
+                                                                   dlen.as<int32_t>(), H->ent_off32.as<int32_t>(),
+                                                                   H->ent_soff.as<int32_t>(), src, beta);
+        LAUNCH_CHECK();
+    };
+    if (H->dtypes & 2) {
+        H->rg_beta64.alloc(slot.size() * 64 * sizeof(double));
+        fill(H->rg_beta64.as<double>(), H->ent_beta64.as<double>());
+    }
+    if (H->dtypes & 1) {
+        H->rg_beta32.alloc(slot.size() * 64 * sizeof(float));
+        fill(H->rg_beta32.as<float>(), H->ent_beta32.as<float>());
+    }
+    HIP_CHECK(hipStreamSynchronize(s));   // the host lists and dlen go out of scope
+}
+
+template <class T, int PB, int SLOTS>
+static void launch_tile(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec,
+                        const T* C, const StepCoef<T>& coef, hipStream_t s) {
+    const int n_chunks = (nvec + 8 * Wide<T>::N - 1) / (8 * Wide<T>::N);
+    const int64_t nt = H->grid.n_blocks * int64_t(n_chunks);
+    const T* rg_beta = std::is_same<T, double>::value ? H->rg_beta64.as<T>() : H->rg_beta32.as<T>();
+    hx_tile_kernel<T, PB, SLOTS><<<dim3(unsigned(((nt + 7) / 8) * 8)), dim3(512), 0, s>>>(
+        int(H->grid.n_blocks), n_chunks, H->block_nbr.as<int32_t>(), H->block_mask.as<uint64_t>(), veff_of<T>(H),
+        H->rg_off.as<int32_t>(), H->rg_slot.as<int32_t>(), rg_beta, H->blk_atom_off.as<int32_t>(),
+        H->blk_atoms.as<int32_t>(), C, nvec, X, ldx, Y, ldy, Z, ldz, coef);
+    LAUNCH_CHECK();
 }
 
 template <class T>
 void launch_hx_tiled(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec,
                      const T* C, double alpha, double shift, double beta, hipStream_t s, bool lap_only) {
+    const bool kb = !lap_only && H->proj.n_proj > 0;
+    const StepCoef<T> coef = make_coef<T>(H, alpha, shift, beta);
+    if (kb && H->proj.max_block_atoms <= kMaxBlockAtoms) {
+        // rows of 16-byte pieces where widths, leading dimensions and base
+        // addresses allow, else of 8-byte ones
+        constexpr int N = Wide<T>::N;
+        const bool a16 = nvec % N == 0 && ldx % N == 0 && ldy % N == 0 && (!Z || ldz % N == 0) &&
+                         uintptr_t(X) % 16 == 0 && uintptr_t(Y) % 16 == 0 && uintptr_t(Z) % 16 == 0;
+        const bool few = H->proj.max_block_atoms <= kFewSlots;
+        auto go = [&](auto pb, auto slots) {
+            launch_tile<T, decltype(pb)::value, decltype(slots)::value>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, coef, s);
+        };
+        using std::integral_constant;
+        if (few && a16) go(integral_constant<int, 16>{}, integral_constant<int, kFewSlots>{});
+        else if (few) go(integral_constant<int, 8>{}, integral_constant<int, kFewSlots>{});
+        else if (a16) go(integral_constant<int, 16>{}, integral_constant<int, kMaxBlockAtoms>{});
+        else go(integral_constant<int, 8>{}, integral_constant<int, kMaxBlockAtoms>{});
+        return;
+    }
     constexpr int CH = kLanes * Lane<T>::N;
     const int n_chunks = (nvec + CH - 1) / CH;
     const int64_t nt = H->grid.n_blocks * int64_t(n_chunks);
     const dim3 grid(unsigned(((nt + 7) / 8) * 8)), block(64 * kLanes);
-    const bool kb = !lap_only && H->proj.n_proj > 0;
-    const bool stage = kb && H->proj.max_block_atoms <= kMaxBlockAtoms;
     const int32_t* eo = kb ? H->ent_off32.as<int32_t>() : nullptr;
-    const StepCoef<T> coef = make_coef<T>(H, alpha, shift, beta);
     const T* veff = lap_only ? nullptr : veff_of<T>(H);
-    if (stage)
-        hx_tile_kernel<T><<<grid, block, 0, s>>>(H->grid.n_blocks, n_chunks, H->block_nbr.as<int32_t>(),
-                                                H->block_mask.as<uint64_t>(), veff, eo, H->ent_soff.as<int32_t>(),
-                                                ent_beta_of<T>(H), H->quad_count.as<uint64_t>(),
-                                                H->blk_atom_off.as<int32_t>(), H->blk_atoms.as<int32_t>(), C, nvec, X,
-                                                ldx, Y, ldy, Z, ldz, coef);
-    else
-        hx_tiled_kernel<T><<<grid, block, 0, s>>>(H->grid.n_blocks, n_chunks, H->block_nbr.as<int32_t>(),
-                                                 H->block_mask.as<uint64_t>(), veff, eo, H->ent_atom.as<int32_t>(),
-                                                 ent_beta_of<T>(H), C, nvec, X, ldx, Y, ldy, Z, ldz, coef);
+    hx_tiled_kernel<T><<<grid, block, 0, s>>>(H->grid.n_blocks, n_chunks, H->block_nbr.as<int32_t>(),
+                                             H->block_mask.as<uint64_t>(), veff, eo, H->ent_atom.as<int32_t>(),
+                                             ent_beta_of<T>(H), C, nvec, X, ldx, Y, ldy, Z, ldz, coef);
     LAUNCH_CHECK();
 }
 

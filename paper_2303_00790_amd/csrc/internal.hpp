@@ -175,8 +175,11 @@ struct chf_ham {
     chf::DevBuf ent_off32;      // int32 [n_rows + 1] (pairs < 2^31)
     chf::DevBuf ent_atom;       // int32 [pairs]
     chf::DevBuf ent_soff;       // int32 [pairs] LDS byte offset of that slot's staged coefficients (slot * 512)
-    chf::DevBuf quad_count;     // uint64 [n_blocks][16]: byte z = largest entry count of the wave's
-                                //   4 rows (quad) in plane z, capped at 255
+    // row groups (16 rows) of the tiled kernel: the slots that touch each, as
+    // LDS byte offsets, and their weights in MFMA operand order
+    chf::DevBuf rg_off;         // int32 [32 n_blocks + 1]
+    chf::DevBuf rg_slot;        // int32 [entries]
+    chf::DevBuf rg_beta64, rg_beta32;  // [entries][64]
     chf::DevBuf blk_atom_off;   // int32 [n_blocks + 1]
     chf::DevBuf blk_atoms;      // int32 [sum of block atom counts]
     chf::DevBuf sup_beta64, ent_beta64;  // double [pairs][4]

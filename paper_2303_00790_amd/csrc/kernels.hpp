@@ -6,6 +6,8 @@ namespace chf {
 
 void launch_vloc(chf_ham* H, const double4* atoms, const double* width, int n_atoms, hipStream_t s);
 void launch_cast_veff(chf_ham* H, const double* src, double* d64, float* d32, int* bad_dev, hipStream_t s);
+// row-group tables of the tiled kernel (ham_build, after the entry tables)
+void build_row_groups(chf_ham* H, hipStream_t s);
 template <class T>
 void launch_kb_gather(chf_ham* H, const T* X, int64_t ldx, int nvec, T* C, hipStream_t s);
 // Y = alpha (H X - shift X) - beta Z ; Z may be null or alias Y.  force_kernel:

@@ -294,3 +294,38 @@ def test_projector_coefficients_do_not_depend_on_the_width(system, dtype, tol, m
         Z = torch.zeros_like(Xg)
         s["Hg"].apply(Xg[:, c0:c0 + w], Z[:, c0:c0 + w], generic=True)
         assert torch.equal(Z[:, c0:c0 + w], Y[:, c0:c0 + w])
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-12), (torch.float32, 2e-6)])
+@pytest.mark.parametrize("n_atoms", [1, 12, 39, 46])
+@pytest.mark.parametrize("m,ld", [(20, 24), (34, 34), (18, 19)])
+def test_row_groups_of_the_tiled_kernel(dtype, tol, n_atoms, m, ld):
+    # the KB term of the tiled kernel takes 16 rows and 4 list entries at a
+    # time: atoms packed so that the lists of a row group run from none over
+    # 1 to more than 8 entries and, with 46 atoms, so that a block is touched by
+    # more atoms than the half-LDS variant holds (40); the blocks' first row
+    # starts on 16 bytes or (odd leading dimension, columns from 1) does not
+    from paper_2303_00790_amd import binding as B
+    if dtype == torch.float32 and ld % 2:
+        ld += 1
+    rng = np.random.default_rng(40 + n_atoms)
+    pos = rng.uniform(-2.5, 2.5, size=(n_atoms, 3))
+    spc = np.zeros(n_atoms, np.int32)
+    pp = OH.PseudoParams(h_s=2.0, h_p=0.5)
+    radius = 9.0
+    g = G.build_grid(radius, H_SPACING)
+    Ho = OH.build_hamiltonian(g, pos, spc, pp)
+    Hg = B.Hamiltonian(pos, spc, pp, H_SPACING, radius, B.ORDER_HILBERT)
+    rows = torch.from_numpy(g.row_of_rank).cuda()
+    X = random_block(g.n, m, 2900 + n_atoms)
+    ref = Ho.apply(X)
+    for c0 in (0, 2 if dtype == torch.float32 else 1):
+        w = min(m, ld - c0)
+        Xg = torch.zeros((Hg.n_rows, ld), dtype=dtype, device="cuda")
+        Xg[rows, c0:c0 + w] = torch.from_numpy(X[:, :w]).to(device="cuda", dtype=dtype)
+        Yg = torch.full_like(Xg, float("nan"))
+        w -= w % (2 if dtype == torch.float32 else 1)
+        Hg.apply(Xg[:, c0:c0 + w], Yg[:, c0:c0 + w])
+        assert relerr(Yg[rows, c0:c0 + w].double().cpu().numpy(), ref[:, :w]) < tol
+        Yg[:, c0:c0 + w] = float("nan")
+        assert bool(torch.isnan(Yg).all())      # nothing outside the block was written
