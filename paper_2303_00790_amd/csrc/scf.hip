@@ -91,8 +91,7 @@ __global__ void lda_kernel(int64_t n, const double* __restrict__ rho, double* __
 constexpr int kNMom = 35;
 
 // exponents (a, b, c) of the Cartesian moments x^a y^b z^c, a + b + c <= 4,
-// by order, built at compile time into constant memory (every device gets
-// the table with the code object)
+// by order, known at compile time
 struct MomExp {
     int e[kNMom][3];
 };
@@ -109,41 +108,49 @@ constexpr MomExp make_mom_exponents() {
             }
     return t;
 }
-__constant__ MomExp c_mom = make_mom_exponents();
+constexpr MomExp kMom = make_mom_exponents();
 
 __global__ void __launch_bounds__(256) moments_kernel(int64_t n_rows, const int32_t* __restrict__ ijk4, double h,
                                                       const double* __restrict__ rho, double* __restrict__ part) {
-    __shared__ double sh[256];
+    __shared__ double sh[4][kNMom];
     double acc[kNMom];
+#pragma unroll
     for (int m = 0; m < kNMom; ++m) acc[m] = 0.0;
     for (int64_t row = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; row < n_rows;
          row += int64_t(gridDim.x) * blockDim.x) {
         if (!ijk4[4 * row + 3]) continue;
         const double q = rho[row];
         const double x = ijk4[4 * row] * h, y = ijk4[4 * row + 1] * h, z = ijk4[4 * row + 2] * h;
-        double px[5] = {1, x, x * x, x * x * x, x * x * x * x};
-        double py[5] = {1, y, y * y, y * y * y, y * y * y * y};
-        double pz[5] = {1, z, z * z, z * z * z, z * z * z * z};
-        for (int m = 0; m < kNMom; ++m) acc[m] += q * px[c_mom.e[m][0]] * py[c_mom.e[m][1]] * pz[c_mom.e[m][2]];
+        const double px[5] = {1, x, x * x, x * x * x, x * x * x * x};
+        const double py[5] = {1, y, y * y, y * y * y, y * y * y * y};
+        const double pz[5] = {1, z, z * z, z * z * z, z * z * z * z};
+#pragma unroll
+        for (int m = 0; m < kNMom; ++m) acc[m] += q * px[kMom.e[m][0]] * py[kMom.e[m][1]] * pz[kMom.e[m][2]];
     }
+#pragma unroll
     for (int m = 0; m < kNMom; ++m) {
-        sh[threadIdx.x] = acc[m];
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) part[int64_t(blockIdx.x) * kNMom + m] = sh[0];
-        __syncthreads();
+        const double v = wave_sum(acc[m]);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][m] = v;
     }
+    __syncthreads();
+    const int m = threadIdx.x;
+    if (m < kNMom) part[int64_t(m) * gridDim.x + blockIdx.x] = (sh[0][m] + sh[1][m]) + (sh[2][m] + sh[3][m]);
 }
 
-__global__ void moments_reduce_kernel(int nb, const double* __restrict__ part, double h3, double* __restrict__ mom) {
-    const int m = threadIdx.x;
-    if (m >= kNMom) return;
+// mom[m] = h^3 sum of moment m's partials, one workgroup of 256 per moment (one
+// thread per moment walked the 1024 partials in 240 us)
+__global__ void __launch_bounds__(256) moments_reduce_kernel(int nb, const double* __restrict__ part, double h3,
+                                                             double* __restrict__ mom) {
+    __shared__ double sh[256];
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += part[int64_t(b) * kNMom + m];
-    mom[m] = h3 * s;
+    for (int b = threadIdx.x; b < nb; b += 256) s += part[int64_t(blockIdx.x) * nb + b];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) mom[blockIdx.x] = h3 * sh[0];
 }
 
 __device__ inline int mom_index(int a, int b, int c) {
@@ -372,6 +379,309 @@ static void build_ghosts(chf_ham* H, hipStream_t s) {
     HIP_CHECK(hipStreamSynchronize(s));
 }
 
+// ---------------------------------------------------------------------------
+// Conjugate gradients for -L v = b on the Hilbert layout, two kernels per
+// iteration with every scalar on the device.
+//
+//  cg_stencil  rr = r.r from its partials; p = r + (rr / rr_prev) p_prev on the
+//              block and its halos, ap = -L p, partials of p.ap
+//  cg_update   x += a p, r -= a ap with a = rr / p.ap, partials of r.r
+//
+// A vector is 4 MB at 2.5 nm and stays in the caches, so an iteration costs
+// its launches and the latency of its passes: 12.2 us for the stencil and 6.9
+// for the update there, 6.5 and 3.9 at 1.1 nm.  Nine kernels and two host round
+// trips per iteration, with the stencil on 1 of the 16 lanes of the
+// multi-vector tile kernel, took 113 us at 2.5 nm (51 of them the stencil); a
+// solve from zero went from 44.4 to 7.8 ms.  Folding p's update into the
+// stencil's loads saves a pass and a kernel for a second read of the halos.  The partial sums of a launch are reduced by
+// every workgroup of the next one, in the same order, so all take the same
+// decision; once the residual is small enough the remaining launches of a
+// batch return at once, so the iterates are those of a loop that tests after
+// every iteration.
+// ---------------------------------------------------------------------------
+// most workgroups, and partials, of a launch: the 2 stencil workgroups that a
+// CU holds (1024 of one block each ran in two rounds: 16.2 against 12.2 us)
+constexpr int kCgParts = 512;
+
+struct CgState {
+    double rr[2];   // r.r of the even / odd iterations
+    double thr;     // rtol ||b||
+    double rr_now;  // r.r at the last check
+    int it;         // iterations done when `done` was set
+    int done;
+};
+
+struct CgCoef {
+    double c[7];    // -L: three times the centre weight, then |k| = 1..6
+};
+
+// sum over the workgroup, the same on all threads; sh holds one value per wave
+__device__ inline double group_sum(double v, double* sh) {
+    v = wave_sum(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    for (unsigned w = 0; w < blockDim.x / 64; ++w) s += sh[w];
+    return s;
+}
+__device__ inline double parts_sum(const double* part, int n, double* sh) {
+    double v = 0.0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) v += part[i];
+    return group_sum(v, sh);
+}
+
+// One workgroup per run of 8^3 blocks, one thread per point.  The three arms
+// are staged in LDS as lines of 20: [z][y][20 x], [z][20 y][x], [20 z][y][x].
+// START: r = b - (-L) x, partials of r.r and b.b.  Otherwise one CG product.
+template <bool START>
+__global__ void __launch_bounds__(512) cg_stencil_kernel(int n_blocks, int per_group, const int32_t* __restrict__ bnb,
+                                                         const uint64_t* __restrict__ bmask, CgCoef k,
+                                                         const double* __restrict__ u, const double* __restrict__ p_old,
+                                                         double* __restrict__ p_new, const double* __restrict__ b,
+                                                         double* __restrict__ out, int it, double rtol,
+                                                         const double* __restrict__ part_rr, int n_rr,
+                                                         const double* __restrict__ part_bb, int n_bb,
+                                                         double* __restrict__ part_a, double* __restrict__ part_b,
+                                                         CgState* __restrict__ st) {
+    constexpr int XS = 21;           // pitch of an x line
+    __shared__ double lines[64 * XS + 8 * 20 * 8 + 20 * 64], sh[8];
+    double* const xl = lines;
+    double* const yl = xl + 64 * XS;
+    double* const zl = yl + 8 * 20 * 8;
+    const int t = threadIdx.x;
+    const int lane = t & 63, x = t & 7, y = (t >> 3) & 7;
+    const int z = __builtin_amdgcn_readfirstlane(t >> 6);
+    const bool add = !START && it > 0;
+    // XCD-aware: each XCD takes a contiguous run of blocks (grid = 8 * per_xcd)
+    const int group = int(blockIdx.x % 8) * int(gridDim.x / 8) + int(blockIdx.x / 8);
+    const int first = group * per_group, last = min(n_blocks, first + per_group);
+    // Halo values: 6 sides x 6 depths x 64, a wave takes whole (side, depth)
+    // layers; along x, where a layer is 64 single values, 6 layers are dealt in
+    // memory order instead.  `at` is the value's place in `lines`.
+    double ur[5], pr[5], uv = 0.0, pv = 0.0;
+    int at[5], row[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+        const int item = z + 8 * j, side = item / 6, c = item % 6, d = side & 1;
+        if (side < 2) {
+            const int i = c * 64 + lane, cc = i % 6, line = i / 6;      // line = y + 8 z
+            row[j] = line * 8 + (d ? cc : 2 + cc);
+            at[j] = line * XS + (d ? 14 + cc : cc);
+        } else if (side < 4) {
+            row[j] = (lane >> 3) * 64 + (d ? c : 2 + c) * 8 + x;
+            at[j] = 64 * XS + ((lane >> 3) * 20 + (d ? 14 + c : c)) * 8 + x;
+        } else {
+            row[j] = (d ? c : 2 + c) * 64 + lane;
+            at[j] = 64 * XS + 1280 + (d ? 14 + c : c) * 64 + lane;
+        }
+    }
+    auto load = [&](int blk) {
+        const int64_t base = int64_t(blk) * kBlockPts;
+        uv = (u + base)[t];
+        if (add) pv = (p_old + base)[t];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            ur[j] = pr[j] = 0.0;
+            const int item = z + 8 * j;
+            if (item >= 36) continue;
+            const int nb = bnb[6 * int64_t(blk) + item / 6];
+            if (nb < 0) continue;
+            const int64_t off = int64_t(nb) * kBlockPts;
+            ur[j] = (u + off)[row[j]];
+            if (add) pr[j] = (p_old + off)[row[j]];
+        }
+    };
+    // (the first block's values are on their way while the scalars are formed)
+    if (first < last) load(first);
+    double beta = 0.0;
+    if constexpr (!START) {
+        // (`done` is read once: group 0 of this launch may set it)
+        __shared__ int done;
+        if (t == 0) done = st->done;
+        const double rr_prev = st->rr[(it + 1) & 1], thr_prev = st->thr;
+        const double rr = parts_sum(part_rr, n_rr, sh);
+        if (done) return;
+        const double thr = it == 0 ? rtol * sqrt(parts_sum(part_bb, n_bb, sh)) : thr_prev;
+        if (!(sqrt(rr) > thr)) {
+            if (blockIdx.x == 0 && t == 0) {
+                st->rr_now = rr;
+                st->thr = thr;
+                st->it = it;
+                st->done = 1;
+            }
+            return;
+        }
+        if (it > 0) beta = rr / rr_prev;
+        if (blockIdx.x == 0 && t == 0) {
+            st->rr[it & 1] = rr;
+            if (it == 0) st->thr = thr;
+        }
+    }
+    double sa = 0.0, sb = 0.0;
+    for (int blk = first; blk < last; ++blk) {
+        const int64_t me = int64_t(blk) * kBlockPts + t;
+        const double v = fma(beta, pv, uv);
+        __syncthreads();             // the last block's lines have been read
+        double* const cx = xl + (z * 8 + y) * XS + x + 6;
+        double* const cy = yl + (z * 20 + y + 6) * 8 + x;
+        double* const cz = zl + (z + 6) * 64 + lane;
+        *cx = *cy = *cz = v;
+#pragma unroll
+        for (int j = 0; j < 5; ++j)
+            if (z + 8 * j < 36) lines[at[j]] = fma(beta, pr[j], ur[j]);
+        if (blk + 1 < last) load(blk + 1);
+        __syncthreads();
+        double acc = k.c[0] * v;
+#pragma unroll
+        for (int s = 1; s <= 6; ++s) {
+            double sum = cz[-64 * s] + cz[64 * s];
+            sum += cx[-s];
+            sum += cx[s];
+            sum += cy[-8 * s];
+            sum += cy[8 * s];
+            acc = fma(k.c[s], sum, acc);
+        }
+        const bool in = (bmask[8 * int64_t(blk) + z] >> lane) & 1;
+        if (!in) acc = 0.0;
+        if constexpr (START) {
+            const double bv = b[me], rv = bv - acc;
+            out[me] = rv;
+            sa += rv * rv;
+            sb += bv * bv;
+        } else {
+            p_new[me] = v;
+            out[me] = acc;
+            sa += v * acc;
+        }
+    }
+    const double ta = group_sum(sa, sh);
+    if (t == 0) part_a[group] = ta;
+    if constexpr (START) {
+        const double tb = group_sum(sb, sh);
+        if (t == 0) part_b[group] = tb;
+    }
+}
+
+// n is a multiple of 512 (Hilbert rows)
+__global__ void __launch_bounds__(256) cg_update_kernel(int64_t n, int it, const double* __restrict__ p,
+                                                        const double* __restrict__ ap, double* __restrict__ x,
+                                                        double* __restrict__ r, const double* __restrict__ part_pap,
+                                                        int n_pap, double* __restrict__ part_rr,
+                                                        const CgState* __restrict__ st) {
+    __shared__ double sh[4];
+    const int64_t i0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 2;
+    double2 pv, av, xv, rv;
+    auto load = [&](int64_t i) {
+        pv = *reinterpret_cast<const double2*>(p + i);
+        av = *reinterpret_cast<const double2*>(ap + i);
+        xv = *reinterpret_cast<const double2*>(x + i);
+        rv = *reinterpret_cast<const double2*>(r + i);
+    };
+    load(i0);                        // i0 < n: the grid has at most n / 512 workgroups
+    const int done = st->done;
+    const double rr = st->rr[it & 1];
+    const double a = rr / parts_sum(part_pap, n_pap, sh);
+    if (done) return;
+    double s = 0.0;
+    for (int64_t i = i0; i < n; i += int64_t(gridDim.x) * 512) {
+        if (i != i0) load(i);
+        xv.x = fma(a, pv.x, xv.x);
+        xv.y = fma(a, pv.y, xv.y);
+        rv.x = fma(-a, av.x, rv.x);
+        rv.y = fma(-a, av.y, rv.y);
+        *reinterpret_cast<double2*>(x + i) = xv;
+        *reinterpret_cast<double2*>(r + i) = rv;
+        s += rv.x * rv.x;
+        s += rv.y * rv.y;
+    }
+    const double ts = group_sum(s, sh);
+    if (threadIdx.x == 0) part_rr[blockIdx.x] = ts;
+}
+
+// the test at the end of a batch: `it` iterations done
+__global__ void __launch_bounds__(256) cg_check_kernel(int it, double rtol, const double* __restrict__ part_rr, int n_rr,
+                                                       const double* __restrict__ part_bb, int n_bb,
+                                                       CgState* __restrict__ st) {
+    __shared__ double sh[4];
+    if (st->done) return;
+    const double rr = parts_sum(part_rr, n_rr, sh);
+    const double thr = it == 0 ? rtol * sqrt(parts_sum(part_bb, n_bb, sh)) : st->thr;
+    if (threadIdx.x != 0) return;
+    st->rr_now = rr;
+    st->thr = thr;
+    if (!(sqrt(rr) > thr)) {
+        st->it = it;
+        st->done = 1;
+    }
+}
+
+__global__ void cg_reset_kernel(CgState* __restrict__ st) { st->done = 0; }
+
+struct CgResult {
+    double rr, thr;
+    int it;
+};
+
+// x <- the solution of -L x = b (warm start from its contents).  r, p0 and ap
+// are work vectors; b's memory holds p of the odd iterations once the start
+// has read it.
+static CgResult cg_hilbert(chf_ham* H, chf_ctx* ctx, double* b, double* x, double* r, double* p0, double* ap,
+                           double rtol, int max_iter, hipStream_t s) {
+    const int64_t n = H->grid.n_rows;
+    const int nblk = int(H->grid.n_blocks);
+    const int per = (nblk + kCgParts - 1) / kCgParts;
+    const int groups = (nblk + per - 1) / per;
+    const unsigned grid = unsigned((groups + 7) / 8 * 8);        // workgroups past the last block write 0
+    const int n_upd = int(std::min<int64_t>(kCgParts, n / 512));
+    ctx->red.ensure(size_t(4) * kCgParts * sizeof(double));
+    double* part_bb = ctx->red.as<double>();
+    double* part_pap = part_bb + kCgParts;
+    double* part_rr[2] = {part_bb + 2 * kCgParts, part_bb + 3 * kCgParts};
+    CgState* st = reinterpret_cast<CgState*>(static_cast<char*>(ctx->info.p) + kInfoBytes / 2);
+    CgCoef k;
+    k.c[0] = 6.0 * H->coef[0];
+    for (int i = 1; i <= kHalf; ++i) k.c[i] = 2.0 * H->coef[i];
+    const int32_t* bnb = H->block_nbr.as<int32_t>();
+    const uint64_t* bmask = H->block_mask.as<uint64_t>();
+    cg_reset_kernel<<<1, 1, 0, s>>>(st);
+    cg_stencil_kernel<true><<<grid, 512, 0, s>>>(nblk, per, bnb, bmask, k, x, nullptr, nullptr, b, r, 0, rtol, nullptr, 0,
+                                                 nullptr, 0, part_rr[0], part_bb, nullptr);
+    LAUNCH_CHECK();
+    // partials of r.r: those of the start for iteration 0, then cg_update's
+    int it = 0, batch = 0;
+    CgState h{};
+    double rr0 = 0.0;
+    for (;;) {
+        for (const int end = it + batch; it < end; ++it) {
+            double* p = it & 1 ? b : p0;
+            const double* po = it & 1 ? p0 : b;
+            const int n_rr = it == 0 ? int(grid) : n_upd;
+            cg_stencil_kernel<false><<<grid, 512, 0, s>>>(nblk, per, bnb, bmask, k, r, po, p, nullptr, ap, it, rtol,
+                                                          part_rr[it & 1], n_rr, part_bb, int(grid), part_pap, nullptr,
+                                                          st);
+            cg_update_kernel<<<n_upd, 256, 0, s>>>(n, it, p, ap, x, r, part_pap, int(grid), part_rr[(it + 1) & 1], st);
+            LAUNCH_CHECK();
+        }
+        cg_check_kernel<<<1, 256, 0, s>>>(it, rtol, part_rr[it & 1], it == 0 ? int(grid) : n_upd, part_bb, int(grid), st);
+        LAUNCH_CHECK();
+        HIP_CHECK(hipMemcpyAsync(&h, st, sizeof(h), hipMemcpyDeviceToHost, s));
+        HIP_CHECK(hipStreamSynchronize(s));
+        if (h.done || it >= max_iter) return {h.rr_now, h.thr, h.done ? h.it : it};
+        // next batch: the iterations that the mean rate so far leaves, at most
+        // 64 (launches past the end cost ~5 us each), at least 4
+        if (it == 0) {
+            rr0 = h.rr_now;
+            batch = 16;
+        } else {
+            const double rate = 0.5 * std::log(rr0 / h.rr_now) / it;
+            const double left = 0.5 * std::log(h.rr_now / (h.thr * h.thr)) / rate;
+            batch = rate > 0 && left < 64.0 ? std::max(4, int(left)) : 64;
+        }
+        batch = std::min(batch, max_iter - it);
+    }
+}
+
 // Hartree potential into vh (warm start from its contents); returns CG iterations.
 int hartree_solve(chf_ham* H, chf_ctx* ctx, const double* rho, double* vh, double rtol, int max_iter, hipStream_t s) {
     build_ghosts(H, s);
@@ -392,7 +702,7 @@ int hartree_solve(chf_ham* H, chf_ctx* ctx, const double* rho, double* vh, doubl
     const int mb = int(std::min<int64_t>(1024, std::max<int64_t>(1, (n + 255) / 256)));
     moments_kernel<<<mb, 256, 0, s>>>(n, H->row_ijk4.as<int32_t>(), h, rho, ctx->red.as<double>());
     LAUNCH_CHECK();
-    moments_reduce_kernel<<<1, 64, 0, s>>>(mb, ctx->red.as<double>(), h * h * h, M);
+    moments_reduce_kernel<<<kNMom, 256, 0, s>>>(mb, ctx->red.as<double>(), h * h * h, M);
     LAUNCH_CHECK();
     if (H->n_ghost > 0) {
         ghost_values_kernel<<<nblk(H->n_ghost), 256, 0, s>>>(H->n_ghost, H->ghost_ijk.as<int32_t>(), h, M, vg);
@@ -405,29 +715,37 @@ int hartree_solve(chf_ham* H, chf_ctx* ctx, const double* rho, double* vh, doubl
     poisson_rhs_kernel<<<nblk(n), 256, 0, s>>>(n, H->row_inside.as<uint8_t>(), rho, H->ghost_owner.as<int32_t>(),
                                               H->ghost_k.as<int32_t>(), vg, ck, b);
     LAUNCH_CHECK();
-    // A v = -L v = 2 (-1/2 L) v on the inside points (padding stays zero)
-    auto apply_a = [&](const double* x, double* y) { hx_step<double>(H, x, 1, y, 1, nullptr, 0, 1, 2.0, 0.0, 0.0, s, 0, true); };
-    const double bn = std::sqrt(dot_host<double>(ctx, n, b, 1, b, 1, s));
-    apply_a(vh, ap);
-    axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, b, -1.0, ap, 0.0, nullptr, r);
-    LAUNCH_CHECK();
-    HIP_CHECK(hipMemcpyAsync(pv, r, size_t(n) * sizeof(double), hipMemcpyDeviceToDevice, s));
-    double rr = dot_host<double>(ctx, n, r, 1, r, 1, s);
+    double rr, thr;
     int it = 0;
-    while (std::sqrt(rr) > rtol * bn && it < max_iter) {
-        apply_a(pv, ap);
-        const double alpha = rr / dot_host<double>(ctx, n, pv, 1, ap, 1, s);
-        axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, vh, alpha, pv, 0.0, nullptr, vh);
-        axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, r, -alpha, ap, 0.0, nullptr, r);
+    if (H->grid.ordering == CHF_ORDER_HILBERT) {
+        const CgResult c = cg_hilbert(H, ctx, b, vh, r, pv, ap, rtol, max_iter, s);
+        rr = c.rr;
+        thr = c.thr;
+        it = c.it;
+    } else {
+        // A v = -L v = 2 (-1/2 L) v on the inside points
+        auto apply_a = [&](const double* x, double* y) { hx_step<double>(H, x, 1, y, 1, nullptr, 0, 1, 2.0, 0.0, 0.0, s, 0, true); };
+        thr = rtol * std::sqrt(dot_host<double>(ctx, n, b, 1, b, 1, s));
+        apply_a(vh, ap);
+        axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, b, -1.0, ap, 0.0, nullptr, r);
         LAUNCH_CHECK();
-        const double rr_new = dot_host<double>(ctx, n, r, 1, r, 1, s);
-        axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, r, rr_new / rr, pv, 0.0, nullptr, pv);
-        LAUNCH_CHECK();
-        rr = rr_new;
-        ++it;
+        HIP_CHECK(hipMemcpyAsync(pv, r, size_t(n) * sizeof(double), hipMemcpyDeviceToDevice, s));
+        rr = dot_host<double>(ctx, n, r, 1, r, 1, s);
+        while (std::sqrt(rr) > thr && it < max_iter) {
+            apply_a(pv, ap);
+            const double alpha = rr / dot_host<double>(ctx, n, pv, 1, ap, 1, s);
+            axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, vh, alpha, pv, 0.0, nullptr, vh);
+            axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, r, -alpha, ap, 0.0, nullptr, r);
+            LAUNCH_CHECK();
+            const double rr_new = dot_host<double>(ctx, n, r, 1, r, 1, s);
+            axpbypcz_kernel<<<nblk(n), 256, 0, s>>>(n, 1.0, r, rr_new / rr, pv, 0.0, nullptr, pv);
+            LAUNCH_CHECK();
+            rr = rr_new;
+            ++it;
+        }
     }
     if (!std::isfinite(rr)) fail(CHF_ENONFINITE, "chf_hartree: non-finite residual");
-    if (std::sqrt(rr) > rtol * bn) fail(CHF_ENOTCONV, "chf_hartree: CG did not reach %g in %d iterations", rtol, max_iter);
+    if (std::sqrt(rr) > thr) fail(CHF_ENOTCONV, "chf_hartree: CG did not reach %g in %d iterations", rtol, max_iter);
     return it;
 }
 

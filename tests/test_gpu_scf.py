@@ -82,6 +82,33 @@ def test_hartree(si35, centre):
     assert relerr(from_rows(s, vh), vref) < 1e-10
 
 
+@pytest.mark.parametrize("radius", [0.75, 2.0, 3.5, 9.1])
+def test_hartree_iteration_limit_and_small_grids(si35, radius):
+    # from a few points in one block to several hundred blocks: CG runs in
+    # batches on the device, and stops at the iteration that a test after every
+    # iteration would stop at: the limit at that count changes nothing, one
+    # less is an error
+    B = si35["B"]
+    g = G.build_grid(radius, 0.7)
+    nbr = G.neighbour_table(g)
+    pp = si35["pp"]
+    H = B.Hamiltonian(np.zeros((0, 3)), np.zeros(0, np.int32), pp, 0.7, radius, B.ORDER_HILBERT)
+    rho = np.zeros(H.n_rows)
+    rho[g.row_of_rank] = np.random.default_rng(5).random(g.n)
+    vref, _ = OS.hartree(g, OH.laplacian(g, nbr), nbr, rho[g.row_of_rank])
+    rho = torch.from_numpy(rho).cuda()
+    vh = torch.zeros_like(rho)
+    it = H.hartree(si35["ctx"], rho, vh, 1e-12)
+    assert relerr(vh[torch.from_numpy(g.row_of_rank).cuda()].cpu().numpy(), vref) < 1e-10
+    again = torch.zeros_like(rho)
+    assert H.hartree(si35["ctx"], rho, again, 1e-12, max_iter=it) == it and torch.equal(again, vh)
+    if it > 1:
+        with pytest.raises(B.ChfError) as e:
+            H.hartree(si35["ctx"], rho, again.zero_(), 1e-12, max_iter=it - 1)
+        assert e.value.code == -5
+    assert H.hartree(si35["ctx"], torch.zeros_like(rho), again.zero_(), 1e-12) == 0
+
+
 def test_scf_steps_fp64(si35):
     s = si35
     B = s["B"]
