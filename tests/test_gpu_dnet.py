@@ -7,6 +7,8 @@ input.  Between layers the device rounds activations to BF16 (relative
 at 3e-2 relative to their largest magnitude; the Adam update is compared
 exactly (same FP32 gradients on both sides, 1e-5).
 """
+import math
+
 import numpy as np
 import pytest
 
@@ -218,3 +220,75 @@ def test_density_fix_clamps_and_renormalises(grid_system):
     ref *= ne / (0.7 ** 3 * ref.sum())
     got = rows.cpu().numpy()[s["g"].row_of_rank]
     assert np.abs(got - ref).max() < 1e-13 * ref.max()
+
+
+def _torch_net(p, x):
+    """The network in plain PyTorch FP32 on the CPU: (output, parameters)."""
+    F = torch.nn.functional
+    q = {k: torch.from_numpy(v.astype(np.float32)).requires_grad_() for k, v in p.items()}
+
+    def conv(name, u, stride=1, act=True):
+        w = q[name + ".w"]
+        z = F.conv3d(u, w, q[name + ".b"], stride=stride, padding=w.shape[2] // 2)
+        return F.silu(z) if act else z
+
+    def up(u):
+        return u.repeat_interleave(2, 2).repeat_interleave(2, 3).repeat_interleave(2, 4)
+
+    e1 = conv("c1b", conv("c1a", x))
+    e2 = conv("c2b", conv("c2a", conv("d1", e1, 2)))
+    e3 = conv("c3b", conv("c3a", conv("d2", e2, 2)))
+    g = conv("c4b", conv("c4a", conv("d3", e3, 2)))
+    for k, e in (("5", e3), ("6", e2), ("7", e1)):
+        u = conv("u" + str(8 - int(k)), up(g))
+        g = conv("c" + k + "b", conv("c" + k + "a", torch.cat([u, e], 1)))
+    return conv("out", g, act=False), q
+
+
+@pytest.mark.parametrize("S", [8, 24, 56])
+def test_tiled_convolutions_at_ragged_edges(S):
+    # 32 channels: edges that leave part of a tile (56, 28, 14, 7; 24, 12, 6, 3)
+    # or less than one (8, 4, 2, 1); 56^3 takes the large tiles.  Two backward
+    # passes accumulate.
+    B, net, flat, x, t, S = _net_case(32, S)
+    p = to_oracle(net, flat)
+    xt = torch.from_numpy(x.astype(np.float32))[None, None]
+    tt = torch.from_numpy(t.astype(np.float32))
+    y_ref, q = _torch_net(p, xt)
+    ((y_ref[0, 0] - tt) ** 2).mean().backward()
+    g_ref = from_oracle_grad(net, {k: v.grad.double().numpy() for k, v in q.items()})
+    xg, tg = xt[0, 0].contiguous().cuda(), tt.cuda()
+    yg, dy = torch.zeros_like(xg), torch.zeros_like(xg)
+    net.forward(xg, yg)
+    net.mse(yg, tg, dy)
+    for k in (1, 2):
+        net.backward(dy)
+        g = net.get_grads().astype(np.float64)
+        for name, (info, off) in net.layers.items():
+            cin, cout, cin_p, cout_p, edge, _ = info
+            for sl in (slice(off[0], off[0] + cout_p * edge ** 3 * cin_p), slice(off[1], off[1] + cout)):
+                ref = k * g_ref[sl]
+                assert np.abs(g[sl] - ref).max() < 3e-2 * np.abs(ref).max() + 1e-12, (name, k)
+    ref = y_ref[0, 0].detach().numpy()
+    assert np.abs(yg.cpu().numpy() - ref).max() < 3e-2 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("D,sigma", [(5, 0.2), (40, 3.0), (72, 8.0), (70, 11.3)])
+def test_highpass_runs_of_eight(D, sigma):
+    # a thread forms 8 cells: boxes and radii around and below that, an infinite
+    # cell reaches exactly the cells within the radius along the axes
+    from paper_2303_00790_amd import binding as B
+    box = np.random.default_rng(D).standard_normal((D, D, D)).astype(np.float32)
+    ref = U.gaussian_highpass(box.astype(np.float64), sigma)
+
+    def highpass(b):
+        bg = torch.from_numpy(b).cuda()
+        out, work = torch.zeros_like(bg), torch.zeros(2 * D ** 3, device="cuda")
+        B.highpass(bg, D, sigma, out, work)
+        return out.cpu().numpy()
+    # three passes of at most 69 products of order 1 in FP32
+    assert np.abs(highpass(box) - ref).max() < 1e-5
+    box[D // 2, D // 2, D // 2] = np.inf
+    r = int(math.ceil(3.0 * sigma))
+    near = np.abs(np.arange(D) - D // 2) <= r
+    assert np.array_equal(~np.isfinite(highpass(box)), near[:, None, None] & near[None, :, None] & near[None, None, :])
