@@ -400,10 +400,10 @@ int ham_apply(chf_ham* H, chf_dtype dtype, const void* X, int64_t ldx, void* Y, 
         hipStream_t s = static_cast<hipStream_t>(stream);
         if (dtype == CHF_F64)
             hx_step<double>(H, static_cast<const double*>(X), ldx, static_cast<double*>(Y), ldy, nullptr, 0, nvec, 1.0, 0.0,
-                            0.0, s, 0);
+                            0.0, s, 0, false, nullptr, true);
         else
             hx_step<float>(H, static_cast<const float*>(X), ldx, static_cast<float*>(Y), ldy, nullptr, 0, nvec, 1.0, 0.0,
-                           0.0, s, 0);
+                           0.0, s, 0, false, nullptr, true);
     });
 }
 

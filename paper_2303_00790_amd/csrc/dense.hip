@@ -14,6 +14,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "reduce.hpp"
 
 namespace chf {
 
@@ -575,14 +576,119 @@ void rayleigh_ritz_t(chf_ham* H, chf_ctx* ctx, T* X, int64_t ldx, int m, double*
     }
 }
 
-// three vectors of n_rows as 2-column blocks
-static size_t lanczos_vec_bytes(int64_t n_rows) { return size_t(n_rows) * 2 * 3 * sizeof(double); }
+// three vectors of n_rows as 2-column blocks, and the scalars and partials of
+// the device-side iteration
+constexpr int kLanParts = 512;
+static size_t lanczos_vec_bytes(int64_t n_rows) { return (size_t(n_rows) * 2 * 3 + 3 * kLanParts + 192) * sizeof(double); }
 
-void lanczos_run(chf_ham* H, chf_ctx* ctx, const double* v0, int k, double* out3, hipStream_t s) {
+// w_0 = v0 / |v0| from the partials of |v0|^2, with the partials of |w_0|^2
+__global__ void __launch_bounds__(256) lanczos_start_kernel(int64_t n, const double* __restrict__ v0,
+                                                            const double* __restrict__ part_v0, double* __restrict__ w,
+                                                            double* __restrict__ part_out, double* __restrict__ v0_norm2) {
+    __shared__ double sh[4];
+    const double vv = parts_sum(part_v0, int(gridDim.x), sh), inv = 1.0 / sqrt(vv);
+    double s = 0.0;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
+        const double o = v0[i] * inv;
+        w[i] = o;
+        s += o * o;
+    }
+    const double t = group_sum(s, sh);
+    if (threadIdx.x == 0) part_out[blockIdx.x] = t;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *v0_norm2 = vv;
+}
+
+// Lanczos step j on unnormalised vectors w_j = beta_j v_j.  With f = H w_j and the
+// partials of w_j.f and of |w_j|^2 = beta_j^2:
+//   alpha_j = w_j.f / beta_j^2,  w_{j+1} = f / beta_j - alpha_j v_j - beta_j v_{j-1},
+// written over w_{j-1}, with the partials of |w_{j+1}|^2.  Each workgroup adds the
+// two lists of partials for itself; its first loads are under way meanwhile.
+__global__ void __launch_bounds__(256) lanczos_update_kernel(int64_t n, int j, const double* __restrict__ f,
+                                                             const double* __restrict__ w, double* __restrict__ wp,
+                                                             const double* __restrict__ part_wf, int n_wf,
+                                                             const double* __restrict__ part_ww, int n_ww,
+                                                             double* __restrict__ part_out, double* __restrict__ alpha,
+                                                             double* __restrict__ norm2) {
+    __shared__ double sh[4];
+    const double prev2 = j > 0 ? norm2[j - 1] : 1.0;
+    const int64_t i0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 2;
+    double2 fv, wv, pv = {0.0, 0.0};
+    auto load = [&](int64_t i) {
+        fv = *reinterpret_cast<const double2*>(f + i);
+        wv = *reinterpret_cast<const double2*>(w + i);
+        if (j > 0) pv = *reinterpret_cast<const double2*>(wp + i);
+    };
+    load(i0);                     // i0 < n: the grid has at most n / 512 workgroups
+    const double ww = parts_sum(part_ww, n_ww, sh), wf = parts_sum(part_wf, n_wf, sh);
+    const double be = sqrt(ww), inv = 1.0 / be, al = wf / ww, bp = j > 0 ? be / sqrt(prev2) : 0.0;
+    const double aw = al * inv;
+    double s = 0.0;
+    for (int64_t i = i0; i < n; i += int64_t(gridDim.x) * 512) {
+        if (i != i0) load(i);
+        double2 o;
+        o.x = fma(-aw, wv.x, fma(-bp, pv.x, fv.x * inv));
+        o.y = fma(-aw, wv.y, fma(-bp, pv.y, fv.y * inv));
+        *reinterpret_cast<double2*>(wp + i) = o;
+        s += o.x * o.x;
+        s += o.y * o.y;
+    }
+    const double t = group_sum(s, sh);
+    if (threadIdx.x == 0) part_out[blockIdx.x] = t;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        alpha[j] = al;
+        norm2[j] = ww;
+    }
+}
+
+__global__ void __launch_bounds__(256) lanczos_last_kernel(const double* __restrict__ part, int n, double* __restrict__ out) {
+    __shared__ double sh[4];
+    const double s = parts_sum(part, n, sh);
+    if (threadIdx.x == 0) *out = s;
+}
+
+// The k steps without a host round trip: the gather, H x with its dot product
+// and one update kernel per step; alpha_j, beta_j^2 (beta_k: the last
+// residual's norm) and the start vector's norm come back once.  A step is three
+// dependent kernels, 23 (H x) + 13 + 10 us at 3 nm; eight kernels and two round
+// trips per step took 149 us.
+static void lanczos_device(chf_ham* H, chf_ctx* ctx, const double* v0, int k, double* alpha_host, double* norm2_host,
+                           hipStream_t s) {
+    const int64_t n = H->grid.n_rows;
+    double* w = ctx->vec.as<double>();
+    double* wp = w + n;
+    double* f = w + 2 * n;
+    double* part_wf = w + 6 * n;
+    double* part_ww[2] = {part_wf + kLanParts, part_wf + 2 * kLanParts};
+    double* alpha = part_wf + 3 * kLanParts;
+    double* norm2 = alpha + 64;          // [0..k], then |v0|^2
+    const int nu = int(std::min<int64_t>(kLanParts, n / 512));       // Hilbert rows: a multiple of 512
+    dot_partial_kernel<double><<<nu, 256, 0, s>>>(n, v0, 1, v0, 1, part_ww[1]);
+    LAUNCH_CHECK();
+    lanczos_start_kernel<<<nu, 256, 0, s>>>(n, v0, part_ww[1], w, part_ww[0], norm2 + k + 1);
+    LAUNCH_CHECK();
+    for (int j = 0; j < k; ++j) {
+        const int nd = hx_dot(H, w, f, part_wf, s);
+        lanczos_update_kernel<<<nu, 256, 0, s>>>(n, j, f, w, wp, part_wf, nd, part_ww[j & 1], nu, part_ww[(j + 1) & 1],
+                                                 alpha, norm2);
+        LAUNCH_CHECK();
+        std::swap(w, wp);
+    }
+    lanczos_last_kernel<<<1, 256, 0, s>>>(part_ww[k & 1], nu, norm2 + k);
+    LAUNCH_CHECK();
+    double h[64 + 66];
+    HIP_CHECK(hipMemcpyAsync(h, alpha, sizeof(double) * size_t(64 + k + 2), hipMemcpyDeviceToHost, s));
+    HIP_CHECK(hipStreamSynchronize(s));
+    std::copy(h, h + k, alpha_host);
+    std::copy(h + 64, h + 64 + k + 2, norm2_host);
+}
+
+// the same steps through the block kernels (lexicographic layout, blocks with
+// more atoms than the one-vector kernel stages); returns the last residual's norm
+static double lanczos_blocks(chf_ham* H, chf_ctx* ctx, const double* v0, int k, std::vector<double>& d,
+                             std::vector<double>& e, hipStream_t s) {
     const int64_t n = H->grid.n_rows;
     // three vectors stored as 2-column blocks (second column zero) so the
     // tiled kernel's 16-byte rows apply
-    ctx->vec.ensure(lanczos_vec_bytes(n));
     double* base = ctx->vec.as<double>();
     HIP_CHECK(hipMemsetAsync(base, 0, size_t(n) * 2 * 3 * sizeof(double), s));
     double* v = base;
@@ -591,7 +697,6 @@ void lanczos_run(chf_ham* H, chf_ctx* ctx, const double* v0, int k, double* out3
     const double nrm = std::sqrt(dot_host<double>(ctx, n, v0, 1, v0, 1, s));
     if (!(nrm > 0) || !std::isfinite(nrm)) fail(CHF_EINVAL, "lanczos_bound: zero or non-finite start vector");
     lincomb(n, 1.0 / nrm, v0, 1, 0.0, nullptr, 0, v, 2, s);
-    std::vector<double> d, e;
     hx_step<double>(H, v, 2, f, 2, nullptr, 0, 2, 1.0, 0.0, 0.0, s, 0);
     double alpha = dot_host<double>(ctx, n, v, 2, f, 2, s);
     lincomb(n, 1.0, f, 2, -alpha, v, 2, f, 2, s);
@@ -608,7 +713,31 @@ void lanczos_run(chf_ham* H, chf_ctx* ctx, const double* v0, int k, double* out3
         d.push_back(alpha);
         e.push_back(beta);
     }
-    const double fn = std::sqrt(dot_host<double>(ctx, n, f, 2, f, 2, s));
+    return std::sqrt(dot_host<double>(ctx, n, f, 2, f, 2, s));
+}
+
+void lanczos_run(chf_ham* H, chf_ctx* ctx, const double* v0, int k, double* out3, hipStream_t s) {
+    const int64_t n = H->grid.n_rows;
+    ctx->vec.ensure(lanczos_vec_bytes(n));
+    std::vector<double> d, e;
+    double fn = 0.0;
+    if (hx_dot_ok(H)) {
+        double al[64], n2[66];
+        lanczos_device(H, ctx, v0, k, al, n2, s);
+        const double nrm = std::sqrt(n2[k + 1]);
+        if (!(nrm > 0) || !std::isfinite(nrm)) fail(CHF_EINVAL, "lanczos_bound: zero or non-finite start vector");
+        d.push_back(al[0]);
+        int j = 1;
+        for (; j < k; ++j) {
+            const double beta = std::sqrt(n2[j]);
+            if (!(beta > 0)) break;   // invariant subspace found: what follows is not used
+            d.push_back(al[j]);
+            e.push_back(beta);
+        }
+        fn = std::sqrt(n2[j]);
+    } else {
+        fn = lanczos_blocks(H, ctx, v0, k, d, e, s);
+    }
     const double tmax = tridiag_eig(d, e, 1), tmin = tridiag_eig(d, e, 0);
     out3[0] = tmax + fn;
     out3[1] = tmin;

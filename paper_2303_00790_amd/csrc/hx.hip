@@ -16,6 +16,8 @@
 //                     chunk), z-march with a register window per column, x/y
 //                     halos and the block atoms' KB coefficients staged in
 //                     LDS, the KB term as MFMA products inside the march.
+//  * hx_narrow        the same operator for one row piece of at most 16 bytes
+//                     (1 or 2 FP64, 2 or 4 FP32 vectors), one thread per point.
 //  * hx_tiled         a tile of the same shape without staging, for blocks touched by
 //                     more than kMaxBlockAtoms projector atoms, Laplacian-only
 //                     products and Hamiltonians without projectors.
@@ -26,6 +28,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "reduce.hpp"
 
 namespace chf {
 
@@ -1070,6 +1073,202 @@ void launch_hx_tiled(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, con
 }
 
 // ---------------------------------------------------------------------------
+// Narrow H X: blocks of one row piece (1 or 2 FP64, 2 or 4 FP32 vectors: Lanczos,
+// residual checks).  One workgroup per run of 8^3 blocks, one thread per point;
+// the three arms of the stencil are staged in LDS as lines of 20, [z][y][20 x],
+// [z][20 y][x], [20 z][y][x], the coefficients of the block's atoms beside them,
+// and each thread walks its row's entries.  The vector tile kernel has 1 or 2
+// of 16 lanes working on such blocks: 63 us per launch at 3 nm for 2 FP64
+// vectors (1491 blocks, 12 MB of X), this one 38, and 23 for one FP64 vector.
+// Bound by latency: one round of loads, two barriers and 36 LDS reads per block
+// at 3 workgroups per CU or fewer.
+// ---------------------------------------------------------------------------
+// most workgroups of a launch, 2 per CU: each takes a run of blocks, and with
+// `part` leaves one partial of x.y
+constexpr int kNarrowGroups = 512;
+
+template <class T, int N>
+__global__ void __launch_bounds__(512) hx_narrow_kernel(int n_blocks, int per_group, const int32_t* __restrict__ bnb,
+                                                        const uint64_t* __restrict__ bmask, const T* __restrict__ veff,
+                                                        const int32_t* __restrict__ ent_off,
+                                                        const int32_t* __restrict__ ent_soff,
+                                                        const T* __restrict__ ent_beta,
+                                                        const int32_t* __restrict__ blk_atom_off,
+                                                        const int32_t* __restrict__ blk_atoms, const T* __restrict__ C,
+                                                        const T* __restrict__ X, int64_t ldx, T* Y, int64_t ldy, const T* Z,
+                                                        int64_t ldz, StepCoef<T> k, double* __restrict__ part) {
+    using V = Piece<T, N>;
+    using B4 = Piece<T, 4>;
+    constexpr int XS = 21, YL = 64 * XS, ZL = YL + 8 * 20 * 8;
+    __shared__ V lines[ZL + 20 * 64];
+    __shared__ V cst[kMaxBlockAtoms * 4];
+    __shared__ double sh[8];
+    const int t = threadIdx.x, lane = t & 63, x = t & 7, y = (t >> 3) & 7;
+    const int z = __builtin_amdgcn_readfirstlane(t >> 6);
+    // XCD-aware: each XCD takes a contiguous run of blocks (grid = 8 * per_xcd)
+    const int group = int(blockIdx.x % 8) * int(gridDim.x / 8) + int(blockIdx.x / 8);
+    const int first = group * per_group, last = min(n_blocks, first + per_group);
+    // halo values: 6 sides x 6 depths x 64, a wave takes whole (side, depth)
+    // layers; along x, where a layer is 64 single values, 6 layers are dealt in
+    // memory order instead
+    int at[5], row[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+        const int item = z + 8 * j, side = item / 6, c = item % 6, d = side & 1;
+        if (side < 2) {
+            const int i = c * 64 + lane, cc = i % 6, line = i / 6;      // line = y + 8 z
+            row[j] = line * 8 + (d ? cc : 2 + cc);
+            at[j] = line * XS + (d ? 14 + cc : cc);
+        } else if (side < 4) {
+            row[j] = (lane >> 3) * 64 + (d ? c : 2 + c) * 8 + x;
+            at[j] = YL + ((lane >> 3) * 20 + (d ? 14 + c : c)) * 8 + x;
+        } else {
+            row[j] = (d ? c : 2 + c) * 64 + lane;
+            at[j] = ZL + (d ? 14 + c : c) * 64 + lane;
+        }
+    }
+    V zero;
+#pragma unroll
+    for (int e = 0; e < N; ++e) zero.e[e] = T(0);
+    auto load = [&](int64_t r) { return *reinterpret_cast<const V*>(X + r * ldx); };
+    double dot = 0.0;
+    for (int blk = first; blk < last; ++blk) {
+        const int64_t base = int64_t(blk) * kBlockPts;
+        const V v = load(base + t);
+        V hv[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            hv[j] = zero;
+            const int item = z + 8 * j;
+            if (item >= 36) continue;
+            const int nb = bnb[6 * int64_t(blk) + item / 6];
+            if (nb >= 0) hv[j] = load(int64_t(nb) * kBlockPts + row[j]);
+        }
+        const V zv = Z ? *reinterpret_cast<const V*>(Z + (base + t) * ldz) : zero;
+        const T vr = veff[base + t];
+        int e0 = 0, e1 = 0, na = 0, a0 = 0;
+        V cv = zero;
+        if (ent_off) {
+            e0 = ent_off[base + t];
+            e1 = ent_off[base + t + 1];
+            a0 = blk_atom_off[blk];
+            na = min(blk_atom_off[blk + 1] - a0, kMaxBlockAtoms);
+            if (t < 4 * na)
+                cv = *reinterpret_cast<const V*>(C + (int64_t(blk_atoms[a0 + (t >> 2)]) * 4 + (t & 3)) * N);
+        }
+        __syncthreads();             // the last block's lines have been read
+        V* const cx = lines + (z * 8 + y) * XS + x + 6;
+        V* const cy = lines + YL + (z * 20 + y + 6) * 8 + x;
+        V* const cz = lines + ZL + (z + 6) * 64 + lane;
+        *cx = *cy = *cz = v;
+#pragma unroll
+        for (int j = 0; j < 5; ++j)
+            if (z + 8 * j < 36) lines[at[j]] = hv[j];
+        if (t < 4 * na) cst[t] = cv;
+        __syncthreads();
+        // (an entry's weights and slot are loaded one entry ahead)
+        V kb = zero;
+        int so = 0;
+        B4 bb{};
+        if (e0 < e1) {
+            so = ent_soff[e0];
+            bb = *reinterpret_cast<const B4*>(ent_beta + 4 * int64_t(e0));
+        }
+        // unrolled by 2 the kernel takes fewer registers, so more waves share a CU:
+        // 28 -> 23 us for one FP64 vector at 3 nm, 33 -> 26 for 4 FP32; 2 FP64
+        // vectors do not fit 3 workgroups either way and lose (7.5 -> 16 us at
+        // 1.1 nm)
+        constexpr int U = sizeof(T) == 8 && N == 2 ? 6 : 2;
+        V acc;
+#pragma unroll
+        for (int e = 0; e < N; ++e) acc.e[e] = T(0);
+#pragma unroll U
+        for (int s = 1; s <= 6; ++s) {
+            const V zm = cz[-64 * s], zp = cz[64 * s], xm = cx[-s], xp = cx[s], ym = cy[-8 * s], yp = cy[8 * s];
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                T sum = zm.e[e] + zp.e[e];
+                sum += xm.e[e];
+                sum += xp.e[e];
+                sum += ym.e[e];
+                sum += yp.e[e];
+                acc.e[e] = fma(k.ac[s], sum, acc.e[e]);
+            }
+        }
+        for (int en = e0; en < e1; ++en) {
+            const V* const c = cst + (so / kSlotBytes) * 4;
+            const B4 b = bb;
+            if (en + 1 < e1) {
+                so = ent_soff[en + 1];
+                bb = *reinterpret_cast<const B4*>(ent_beta + 4 * int64_t(en + 1));
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int e = 0; e < N; ++e) kb.e[e] = fma(b.e[m], c[m].e[e], kb.e[e]);
+        }
+        const T dg = fma(k.alpha, vr, k.d0);
+        const bool in = (bmask[8 * int64_t(blk) + z] >> lane) & 1;
+        V out;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const T r = fma(-k.beta, zv.e[e], fma(dg, v.e[e], fma(k.alpha, kb.e[e], acc.e[e])));
+            out.e[e] = in ? r : T(0);
+        }
+        *reinterpret_cast<V*>(Y + (base + t) * ldy) = out;
+        dot += double(v.e[0]) * double(out.e[0]);
+    }
+    if (part) {
+        const double s = group_sum(dot, sh);
+        if (t == 0) part[group] = s;
+    }
+}
+
+// whether a block of nvec vectors is one row piece that the kernel can load,
+// on a handle with the tables it reads
+template <class T>
+static bool narrow_ok(const chf_ham* H, const void* X, int64_t ldx, const void* Y, int64_t ldy, const void* Z, int64_t ldz,
+                      int nvec) {
+    const int64_t bytes = int64_t(nvec) * int64_t(sizeof(T));
+    if (H->grid.ordering != CHF_ORDER_HILBERT || H->proj.max_block_atoms > kMaxBlockAtoms) return false;
+    if (bytes != 8 && bytes != 16) return false;
+    return ldx % nvec == 0 && ldy % nvec == 0 && (!Z || ldz % nvec == 0) && uintptr_t(X) % bytes == 0 &&
+           uintptr_t(Y) % bytes == 0 && uintptr_t(Z) % bytes == 0;
+}
+
+// launches it and returns the number of workgroups (= partials)
+template <class T>
+static int launch_narrow(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec,
+                         const T* C, double alpha, double shift, double beta, double* part, hipStream_t s) {
+    const int nblk = int(H->grid.n_blocks);
+    const int per = (nblk + kNarrowGroups - 1) / kNarrowGroups;
+    const unsigned grid = unsigned(((nblk + per - 1) / per + 7) / 8 * 8);
+    const bool kb = H->proj.n_proj > 0;
+    auto go = [&](auto n) {
+        hx_narrow_kernel<T, decltype(n)::value><<<grid, 512, 0, s>>>(
+            nblk, per, H->block_nbr.as<int32_t>(), H->block_mask.as<uint64_t>(), veff_of<T>(H),
+            kb ? H->ent_off32.as<int32_t>() : nullptr, H->ent_soff.as<int32_t>(), ent_beta_of<T>(H),
+            H->blk_atom_off.as<int32_t>(), H->blk_atoms.as<int32_t>(), C, X, ldx, Y, ldy, Z, ldz,
+            make_coef<T>(H, alpha, shift, beta), part);
+    };
+    constexpr int N8 = 8 / int(sizeof(T));
+    if (nvec == N8) go(std::integral_constant<int, N8>{});
+    else go(std::integral_constant<int, 2 * N8>{});
+    LAUNCH_CHECK();
+    return int(grid);
+}
+
+bool hx_dot_ok(const chf_ham* H) {
+    return H->grid.ordering == CHF_ORDER_HILBERT && H->proj.max_block_atoms <= kMaxBlockAtoms;
+}
+
+int hx_dot(chf_ham* H, const double* x, double* y, double* part, hipStream_t s) {
+    H->kb_coef.ensure(kb_coef_bytes(H, 1, sizeof(double)));
+    launch_kb_gather<double>(H, x, 1, 1, H->kb_coef.as<double>(), s);
+    return launch_narrow<double>(H, x, 1, y, 1, nullptr, 0, 1, H->kb_coef.as<double>(), 1.0, 0.0, 0.0, part, s);
+}
+
+// ---------------------------------------------------------------------------
 // optional per-kernel timing: HIP events recorded on the launch stream
 // around every H X and KB-gather launch while enabled
 // ---------------------------------------------------------------------------
@@ -1141,7 +1340,7 @@ size_t kb_coef_bytes(const chf_ham* H, int nvec, size_t elem_bytes) {
 
 template <class T>
 void hx_step(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec, double alpha,
-             double shift, double beta, hipStream_t s, int force_kernel, bool lap_only, T* C_ext) {
+             double shift, double beta, hipStream_t s, int force_kernel, bool lap_only, T* C_ext, bool narrow) {
     // the KB coefficients go to the handle's scratch (grown on demand), or to
     // the caller's C_ext (no allocation, no kernel timing)
     T* C = C_ext;
@@ -1155,7 +1354,9 @@ void hx_step(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z,
     };
     if (H->proj.n_proj > 0 && !lap_only) run(1, [&] { launch_kb_gather<T>(H, X, ldx, nvec, C, s); });
     const bool tiled = force_kernel != 1 && tiled_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec);
-    if (tiled) {
+    if (tiled && narrow && !lap_only && narrow_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec)) {
+        run(0, [&] { launch_narrow<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, nullptr, s); });
+    } else if (tiled) {
         run(0, [&] { launch_hx_tiled<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, s, lap_only); });
     } else {
         if (!H->has_nbr) fail(CHF_EUNSUPPORTED, "generic H X needs the neighbour table (keep_nbr) for this layout");
@@ -1184,18 +1385,21 @@ void filter_run(chf_ham* H, T* X, int64_t ldx, T* W, int64_t ldw, int nvec, int 
     int64_t nb = std::min<int64_t>(nvec, std::min<int64_t>(ldw, max_cols));
     if (nb < nvec && nb >= 64) nb -= nb % 64;
     else if (nb < nvec && nb >= 4) nb -= nb % 4;
+    // (by the whole call's width, so that a column block of a wider call has
+    // the arithmetic of its neighbours)
+    const bool narrow = nvec * int(sizeof(T)) <= 16;
     for (int c0 = 0; c0 < nvec; c0 += int(nb)) {
         const int w = int(std::min<int64_t>(nb, nvec - c0));
         T* Xc = X + c0;
         double sigma = sigma1;
-        hx_step<T>(H, Xc, ldx, W, ldw, nullptr, 0, w, sigma1 / e, c, 0.0, s, force_kernel, false, C_ext);
+        hx_step<T>(H, Xc, ldx, W, ldw, nullptr, 0, w, sigma1 / e, c, 0.0, s, force_kernel, false, C_ext, narrow);
         for (int k = 2; k <= m; ++k) {
             const double sigma_next = 1.0 / (2.0 / sigma1 - sigma);
             const double alpha = 2.0 * sigma_next / e, beta = sigma * sigma_next;
             if (k % 2 == 0)
-                hx_step<T>(H, W, ldw, Xc, ldx, Xc, ldx, w, alpha, c, beta, s, force_kernel, false, C_ext);
+                hx_step<T>(H, W, ldw, Xc, ldx, Xc, ldx, w, alpha, c, beta, s, force_kernel, false, C_ext, narrow);
             else
-                hx_step<T>(H, Xc, ldx, W, ldw, W, ldw, w, alpha, c, beta, s, force_kernel, false, C_ext);
+                hx_step<T>(H, Xc, ldx, W, ldw, W, ldw, w, alpha, c, beta, s, force_kernel, false, C_ext, narrow);
             sigma = sigma_next;
         }
         if (m % 2 == 1)
@@ -1278,9 +1482,9 @@ void timer_read(double* ms, int64_t* launches) {
 }
 
 template void hx_step<float>(chf_ham*, const float*, int64_t, float*, int64_t, const float*, int64_t, int, double,
-                             double, double, hipStream_t, int, bool, float*);
+                             double, double, hipStream_t, int, bool, float*, bool);
 template void hx_step<double>(chf_ham*, const double*, int64_t, double*, int64_t, const double*, int64_t, int,
-                              double, double, double, hipStream_t, int, bool, double*);
+                              double, double, double, hipStream_t, int, bool, double*, bool);
 template void launch_kb_gather<float>(chf_ham*, const float*, int64_t, int, float*, hipStream_t);
 template void launch_kb_gather<double>(chf_ham*, const double*, int64_t, int, double*, hipStream_t);
 

@@ -14,10 +14,17 @@ void launch_kb_gather(chf_ham* H, const T* X, int64_t ldx, int nvec, T* C, hipSt
 // 0 = best available, 1 = generic neighbour-table kernel.  lap_only: H is
 // replaced by -1/2 L (no V_eff, no projectors).
 // C_ext: caller-provided KB-coefficient scratch for nvec vectors (no
-// allocation, no kernel timing); NULL uses the handle's scratch.
+// allocation, no kernel timing); NULL uses the handle's scratch.  narrow: a
+// block of one row piece of 8 or 16 bytes may take the one-thread-per-point
+// kernel (whose sums run in another order than the vector tile's).
 template <class T>
 void hx_step(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec, double alpha,
-             double shift, double beta, hipStream_t s, int force_kernel, bool lap_only = false, T* C_ext = nullptr);
+             double shift, double beta, hipStream_t s, int force_kernel, bool lap_only = false, T* C_ext = nullptr,
+             bool narrow = false);
+// y = H x for one FP64 vector, with the partials of x.y (at most 512) in part;
+// returns their number.  hx_dot_ok: whether the handle has the tables for it.
+bool hx_dot_ok(const chf_ham* H);
+int hx_dot(chf_ham* H, const double* x, double* y, double* part, hipStream_t s);
 
 // Degree-m scaled Chebyshev filter in place over X and the work block W
 // (column blocks of min(nvec, ldw) vectors)

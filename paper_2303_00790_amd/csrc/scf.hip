@@ -16,15 +16,11 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "reduce.hpp"
 
 namespace chf {
 
 constexpr double kPi = 3.14159265358979323846;
-
-__device__ inline double wave_sum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 
 // ---------------------------------------------------------------------------
 // density: rho[row] = (2 / h^3) sum_{i < n_occ} X[row][i]^2, one wave per row
@@ -414,22 +410,6 @@ struct CgState {
 struct CgCoef {
     double c[7];    // -L: three times the centre weight, then |k| = 1..6
 };
-
-// sum over the workgroup, the same on all threads; sh holds one value per wave
-__device__ inline double group_sum(double v, double* sh) {
-    v = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (unsigned w = 0; w < blockDim.x / 64; ++w) s += sh[w];
-    return s;
-}
-__device__ inline double parts_sum(const double* part, int n, double* sh) {
-    double v = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) v += part[i];
-    return group_sum(v, sh);
-}
 
 // One workgroup per run of 8^3 blocks, one thread per point.  The three arms
 // are staged in LDS as lines of 20: [z][y][20 x], [z][20 y][x], [20 z][y][x].

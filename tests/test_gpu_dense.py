@@ -93,6 +93,38 @@ def test_lanczos_bound(system):
     assert np.allclose(got, ref, rtol=1e-10, atol=1e-10)
 
 
+@pytest.mark.parametrize("k", [2, 7, 32])
+@pytest.mark.parametrize("ordering", ["hilbert", "lexicographic"])
+@pytest.mark.parametrize("radius,scale", [(2.0, 1.0), (9.0, 1e-150), (9.0, 1e150)])
+def test_lanczos_bound_small_grids(k, ordering, radius, scale):
+    # both loops (all steps on the device; the general one for the
+    # lexicographic layout), from a grid with fewer 512-row runs than
+    # workgroups, at the ends of k and of the start vector's norm.  Without
+    # reorthogonalisation rounding is amplified as Ritz values converge, so
+    # beyond a few steps the extreme values are compared to 1e-8.
+    from oracle import grid as G
+    from oracle import hamiltonian as OH
+    from paper_2303_00790_amd import binding as B
+    pos, spc = np.array([[0.1, -0.2, 0.3], [1.5, 0.4, -0.8]]), np.zeros(2, np.int32)
+    pp = OH.PseudoParams(h_s=2.0, h_p=0.5)
+    lex = ordering == "lexicographic"
+    g = G.build_grid(radius, 0.7, G.ORDER_LEX if lex else G.ORDER_HILBERT)
+    Ho = OH.build_hamiltonian(g, pos, spc, pp)
+    H = B.Hamiltonian(pos, spc, pp, 0.7, radius, B.ORDER_LEX if lex else B.ORDER_HILBERT)
+    ctx = B.Context(0)
+    v0 = random_block(g.n, 1, 3002)[:, 0]
+    vec = torch.zeros(H.n_rows, dtype=torch.float64, device="cuda")
+    vec[slice(0, g.n) if lex else torch.from_numpy(g.row_of_rank).cuda()] = torch.from_numpy(v0 * scale).cuda()
+    b, tmin, tmax = H.lanczos_bound(ctx, vec, k)
+    rb, rmin, rmax = OC.lanczos_bound(Ho.apply, v0, k)
+    tol = 1e-10 if k < 10 else 1e-8
+    assert abs(tmin - rmin) < tol * rmax and abs(tmax - rmax) < tol * rmax
+    if k < 10:
+        assert abs(b - rb) < tol * rb
+    with pytest.raises(B.ChfError):
+        H.lanczos_bound(ctx, torch.zeros_like(vec), k)
+
+
 def test_orthonormalize_f64(system):
     s = system
     X = random_block(s["g"].n, 96, 2400)

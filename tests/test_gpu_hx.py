@@ -329,3 +329,50 @@ def test_row_groups_of_the_tiled_kernel(dtype, tol, n_atoms, m, ld):
         assert relerr(Yg[rows, c0:c0 + w].double().cpu().numpy(), ref[:, :w]) < tol
         Yg[:, c0:c0 + w] = float("nan")
         assert bool(torch.isnan(Yg).all())      # nothing outside the block was written
+
+
+@pytest.mark.parametrize("dtype,tol,m", [(torch.float64, 1e-12, 1), (torch.float64, 1e-12, 2),
+                                         (torch.float32, 2e-6, 2), (torch.float32, 2e-6, 4)])
+@pytest.mark.parametrize("n_atoms,radius", [(0, 2.0), (1, 9.0), (64, 9.0), (90, 9.0)])
+def test_narrow_blocks(dtype, tol, m, n_atoms, radius):
+    # blocks of one row piece: from a grid of a few 8^3 blocks without
+    # projectors to blocks touched by 64 atoms (all staged) and by more (the
+    # general kernel); columns of a wider block at a multiple of the piece (the
+    # narrow kernel) and off it (the general one)
+    from paper_2303_00790_amd import binding as B
+    rng = np.random.default_rng(50 + n_atoms)
+    pos = rng.uniform(-3.0, 3.0, size=(max(n_atoms, 1), 3)) if n_atoms != 64 else rng.uniform(-1.0, 1.0, size=(64, 3))
+    spc = np.full(len(pos), 0 if n_atoms else 1, np.int32)      # hydrogen has no projectors
+    pp = OH.PseudoParams(h_s=2.0, h_p=0.5)
+    g = G.build_grid(radius, H_SPACING)
+    Ho = OH.build_hamiltonian(g, pos, spc, pp)
+    Hg = B.Hamiltonian(pos, spc, pp, H_SPACING, radius, B.ORDER_HILBERT, keep_nbr=True)
+    rows = torch.from_numpy(g.row_of_rank).cuda()
+    X = random_block(g.n, m, 3000 + n_atoms)
+    ref = Ho.apply(X)
+    for ld, c0 in ((m, 0), (3 * m, m), (3 * m + 1, 1), (3 * m, 1)):
+        if dtype == torch.float32 and m == 2 and ld % 2:
+            ld += 1
+        Xg = torch.zeros((Hg.n_rows, ld), dtype=dtype, device="cuda")
+        Xg[rows, c0:c0 + m] = torch.from_numpy(X).to(device="cuda", dtype=dtype)
+        Yg = torch.full_like(Xg, float("nan"))
+        Hg.apply(Xg[:, c0:c0 + m], Yg[:, c0:c0 + m])
+        assert relerr(Yg[rows, c0:c0 + m].double().cpu().numpy(), ref) < tol, (ld, c0)
+        Yg[:, c0:c0 + m] = float("nan")
+        assert bool(torch.isnan(Yg).all())      # nothing outside the block was written
+
+
+@pytest.mark.parametrize("dtype,tol,m", [(torch.float64, 1e-10, 2), (torch.float32, 5e-5, 4)])
+def test_filter_of_one_row_piece(system, dtype, tol, m):
+    # the narrow kernel with its third operand, in place on the previous iterate;
+    # half the columns at a time give the same bits
+    s = system
+    a, b, a0 = _bounds(s)
+    X = random_block(s["g"].n, m, 3100 + m)
+    ref = OC.chebyshev_filter(s["Ho"].apply, X, 6, a, b, a0)
+    Xg = to_rows(s, X, dtype)
+    Xh = Xg.clone()
+    s["Hg"].filter(Xg, torch.empty_like(Xg), 6, a, b, a0)
+    assert relerr(from_rows(s, Xg, m), ref) < tol
+    s["Hg"].filter(Xh, torch.empty_like(Xg[:, :m // 2].contiguous()), 6, a, b, a0)
+    assert torch.equal(Xg, Xh)
