@@ -3,11 +3,10 @@
 //
 // Paper: ChFSI orthonormalises the filtered block and projects H onto it
 // (the CheFSI paragraph; details of the PARSEC implementation are deferred to
-// its ChFSI reference).  The Gram products X^T X and X^T (H X) and the
-// N x M x M block updates X R^{-1} and X Q are plain GEMMs (rocBLAS on MFMA;
-// the Gram in row slices whose partials are summed in FP64); the M x M
-// Cholesky factorisation and symmetric eigensolve run in FP64 through
-// rocSOLVER.
+// its ChFSI reference).  The Gram products X^T X and X^T (H X) are kernels of
+// gram.hip; the N x M x M block updates X R^{-1} and X Q are plain triangular
+// solves and GEMMs (rocBLAS on MFMA); the M x M Cholesky factorisation and
+// symmetric eigensolve run in FP64 through rocSOLVER.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -126,123 +125,8 @@ static double tridiag_eig(const std::vector<double>& d, const std::vector<double
 }
 
 
-// ---------------------------------------------------------------------------
-// Gram products S = A^T B
-// ---------------------------------------------------------------------------
-// S[i][j] (+)= sum over row slices of part[s][i][j], in FP64 and in slice
-// order (accumulate: add to S, for the slice groups after the first); with a
-// symmetric product only i <= j is summed and mirrored, so S is exactly
-// symmetric.
-template <class P>
-__global__ void gram_slices_reduce_kernel(int m, int n, int n_slices, const P* __restrict__ part,
-                                          double* __restrict__ S, int64_t lds, int symmetric, int accumulate) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= int64_t(m) * n) return;
-    const int i = int(idx / n), j = int(idx % n);
-    if (symmetric && i > j) return;
-    const int64_t stride = int64_t(m) * n;
-    double acc = accumulate ? S[int64_t(i) * lds + j] : 0.0;
-    for (int k = 0; k < n_slices; ++k) acc += double(part[k * stride + idx]);
-    S[int64_t(i) * lds + j] = acc;
-    if (symmetric && i < j) S[int64_t(j) * lds + i] = acc;
-}
-
-static rocblas_status gemm_sb(rocblas_handle h, rocblas_int M, rocblas_int N, rocblas_int K, const float* A,
-                              rocblas_int lda, rocblas_stride sa, const float* B, rocblas_int ldb, rocblas_stride sb,
-                              float* C, rocblas_int ldc, rocblas_stride sc, rocblas_int batch) {
-    const float one = 1.f, zero = 0.f;
-    return rocblas_sgemm_strided_batched(h, rocblas_operation_none, rocblas_operation_transpose, M, N, K, &one, A, lda,
-                                         sa, B, ldb, sb, &zero, C, ldc, sc, batch);
-}
-static rocblas_status gemm_sb(rocblas_handle h, rocblas_int M, rocblas_int N, rocblas_int K, const double* A,
-                              rocblas_int lda, rocblas_stride sa, const double* B, rocblas_int ldb, rocblas_stride sb,
-                              double* C, rocblas_int ldc, rocblas_stride sc, rocblas_int batch) {
-    const double one = 1.0, zero = 0.0;
-    return rocblas_dgemm_strided_batched(h, rocblas_operation_none, rocblas_operation_transpose, M, N, K, &one, A, lda,
-                                         sa, B, ldb, sb, &zero, C, ldc, sc, batch);
-}
-
-// Gram S = A^T B over n_rows rows.  X^T X is a plain GEMM, so the products of
-// row slices run as strided-batched rocBLAS GEMMs (MFMA, accumulating in the
-// block precision within a slice) into partials that are summed in FP64.
-// Slices hold at most kGramSliceRows rows whatever the width, so an FP32
-// sum never runs over more rows than that (the slice count grows with the
-// grid instead); every GEMM operand spans fewer than kBlasMaxElems elements
-// (the BLAS calls take 32-bit sizes and offsets); the slices run in groups
-// of at most kGramMaxSlices whose partials fit kGramPartBytes, each group's
-// sum added to S in slice order.
-constexpr int64_t kGramSliceRows = 8192;
-constexpr int64_t kGramMaxSlices = 256;
-constexpr size_t kGramPartBytes = size_t(1) << 30;
+// the rocBLAS calls take 32-bit sizes and offsets
 constexpr int64_t kBlasMaxElems = (int64_t(1) << 31) - (int64_t(1) << 20);
-
-struct GramSlices {
-    int64_t rows;      // rows per slice
-    int64_t full;      // slices of exactly `rows` rows
-    int64_t tail;      // rows of the last, shorter slice (0: none)
-    int64_t group;     // slices per batched GEMM (their partials at once)
-    size_t part_bytes; // partials scratch
-};
-
-static GramSlices gram_slices(int64_t n_rows, int m, int n, size_t elem_bytes, int64_t ld) {
-    const size_t per = size_t(m) * size_t(n) * elem_bytes;
-    const int64_t ns = std::max<int64_t>(1, (n_rows + kGramSliceRows - 1) / kGramSliceRows);
-    const int64_t max_group =
-        std::max<int64_t>(1, std::min<int64_t>(kGramMaxSlices, int64_t(kGramPartBytes / std::max<size_t>(1, per))));
-    GramSlices g;
-    g.rows = std::max<int64_t>(1, (n_rows + ns - 1) / ns);     // <= kGramSliceRows, balanced
-    g.rows = std::min<int64_t>(g.rows, std::max<int64_t>(1, kBlasMaxElems / std::max<int64_t>(1, ld)));
-    g.full = n_rows / g.rows;
-    g.tail = n_rows - g.full * g.rows;
-    const int64_t total = g.full + (g.tail > 0 ? 1 : 0);
-    g.group = std::max<int64_t>(1, std::min<int64_t>(total, max_group));
-    g.part_bytes = size_t(std::max<int64_t>(1, g.group)) * per;
-    return g;
-}
-
-template <class T>
-void gram_product(chf_ctx* ctx, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t n_rows, int m, int n,
-                  double* S, int64_t lds, hipStream_t s) {
-    const bool symmetric = (A == B) && (m == n) && (lda == ldb);
-    const size_t per = size_t(m) * size_t(n) * sizeof(T);
-    const GramSlices g = gram_slices(n_rows, m, n, sizeof(T), std::max(lda, ldb));
-    const int64_t R = g.rows;
-    const int64_t n_slices = g.full + (g.tail > 0 ? 1 : 0);
-    CHF_REQUIRE(R <= INT32_MAX && lda <= INT32_MAX && ldb <= INT32_MAX, "gram: dimensions beyond 32-bit BLAS");
-    ctx->scratch2.ensure(g.part_bytes);
-    T* part = ctx->scratch2.as<T>();
-    ROCBLAS_CHECK(rocblas_set_stream(ctx->blas, s));
-    const int64_t tot = int64_t(m) * n;
-    if (n_slices == 0) {
-        HIP_CHECK(hipMemsetAsync(part, 0, per, s));
-        gram_slices_reduce_kernel<T><<<unsigned((tot + 255) / 256), 256, 0, s>>>(m, n, 1, part, S, lds,
-                                                                                symmetric ? 1 : 0, 0);
-        LAUNCH_CHECK();
-        return;
-    }
-    for (int64_t s0 = 0; s0 < n_slices; s0 += g.group) {
-        const int64_t cnt = std::min<int64_t>(g.group, n_slices - s0);
-        // full slices of this group, then (in the last group) the tail
-        const int64_t nfull = std::max<int64_t>(0, std::min<int64_t>(cnt, g.full - s0));
-        const T* A0 = A + s0 * R * lda;
-        const T* B0 = B + s0 * R * ldb;
-        // column-major view: part_k (n x m, ld n) = B_k (n x R, ld ldb) * A_k^T
-        if (nfull > 0)
-            ROCBLAS_CHECK(gemm_sb(ctx->blas, n, m, rocblas_int(R), B0, rocblas_int(ldb), R * ldb, A0,
-                                  rocblas_int(lda), R * lda, part, n, int64_t(m) * n, rocblas_int(nfull)));
-        if (nfull < cnt)
-            ROCBLAS_CHECK(gemm_sb(ctx->blas, n, m, rocblas_int(g.tail), B0 + nfull * R * ldb, rocblas_int(ldb), 0,
-                                  A0 + nfull * R * lda, rocblas_int(lda), 0, part + nfull * int64_t(m) * n, n, 0, 1));
-        gram_slices_reduce_kernel<T><<<unsigned((tot + 255) / 256), 256, 0, s>>>(
-            m, n, int(cnt), part, S, lds, symmetric ? 1 : 0, s0 > 0 ? 1 : 0);
-        LAUNCH_CHECK();
-    }
-}
-
-template void gram_product<float>(chf_ctx*, const float*, int64_t, const float*, int64_t, int64_t, int, int, double*,
-                                  int64_t, hipStream_t);
-template void gram_product<double>(chf_ctx*, const double*, int64_t, const double*, int64_t, int64_t, int, int,
-                                   double*, int64_t, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // small element-wise helpers for the dense steps
@@ -371,46 +255,6 @@ __global__ void __launch_bounds__(256) pivot_ratio_kernel(int m, const double* _
 constexpr double kPivotRelF64 = 1e-13;
 constexpr double kPivotRelF32 = 1e-5;
 
-__global__ void cast_panel_kernel(int64_t rows, int m, const float* __restrict__ X, int64_t ldx,
-                                  double* __restrict__ D) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= rows * m) return;
-    const int64_t r = idx / m;
-    const int c = int(idx - r * m);
-    D[idx] = double(X[r * ldx + c]);
-}
-
-// S[i][j] = S[j][i] for i > j (row-major): mirror the upper triangle
-__global__ void mirror_upper_kernel(int m, double* __restrict__ S) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= int64_t(m) * m) return;
-    const int i = int(idx / m), j = int(idx % m);
-    if (i > j) S[idx] = S[int64_t(j) * m + i];
-}
-
-// S = X^T X of an FP32 block with FP64 products and sums: row panels of X are
-// widened to FP64 (at most kGramPartBytes of scratch) and accumulated into S
-// by FP64 GEMMs in panel order, then the upper triangle is mirrored.
-static void gram_f32_in_f64(chf_ctx* ctx, const float* X, int64_t ldx, int64_t n_rows, int m, double* S,
-                            hipStream_t s) {
-    const int64_t P = std::max<int64_t>(1, std::min<int64_t>(n_rows, int64_t(kGramPartBytes / (size_t(m) * 8))));
-    CHF_REQUIRE(P <= INT32_MAX, "gram: panel beyond 32-bit BLAS");
-    ctx->scratch2.ensure(size_t(P) * size_t(m) * 8);
-    double* D = ctx->scratch2.as<double>();
-    ROCBLAS_CHECK(rocblas_set_stream(ctx->blas, s));
-    const double one = 1.0, zero = 0.0;
-    for (int64_t r0 = 0; r0 < n_rows; r0 += P) {
-        const int64_t rows = std::min(P, n_rows - r0);
-        cast_panel_kernel<<<unsigned((rows * m + 255) / 256), 256, 0, s>>>(rows, m, X + r0 * ldx, ldx, D);
-        LAUNCH_CHECK();
-        // column-major D is m x rows (ld m); S (col-major = row-major) += D D^T
-        ROCBLAS_CHECK(rocblas_dgemm(ctx->blas, rocblas_operation_none, rocblas_operation_transpose, m, m,
-                                    rocblas_int(rows), &one, D, m, D, m, r0 == 0 ? &zero : &one, S, m));
-    }
-    mirror_upper_kernel<<<unsigned((int64_t(m) * m + 255) / 256), 256, 0, s>>>(m, S);
-    LAUNCH_CHECK();
-}
-
 // One Cholesky-QR pass: S = X^T X (in the block precision, or in FP64 for an
 // FP32 block when gram64), S = R^T R in FP64, X <- X R^{-1} in the block
 // precision.  Returns 0, or the rocSOLVER info (> 0: leading minor not
@@ -422,10 +266,8 @@ static int cholqr_once(chf_ctx* ctx, T* X, int64_t ldx, int64_t n_rows, int m, d
     constexpr bool f64 = std::is_same<T, double>::value;
     double* S = mm_scratch(ctx, m, cholqr_extra(m));
     double* diag = reinterpret_cast<double*>(reinterpret_cast<char*>(S) + size_t(m) * m * (sizeof(double) + sizeof(float)) + 256);
-    if (!f64 && gram64)
-        gram_f32_in_f64(ctx, reinterpret_cast<const float*>(X), ldx, n_rows, m, S, s);
-    else
-        gram_product<T>(ctx, X, ldx, X, ldx, n_rows, m, m, S, m, s);
+    if (gram64) gram_product<T, double>(ctx, X, ldx, X, ldx, n_rows, m, m, S, m, s);
+    else gram_product<T, T>(ctx, X, ldx, X, ldx, n_rows, m, m, S, m, s);
     if (shift_rel > 0) {
         double* tr = reinterpret_cast<double*>(ctx->info.p);
         trace_kernel<<<1, 256, 0, s>>>(m, S, tr);
@@ -531,7 +373,7 @@ void rayleigh_ritz_t(chf_ham* H, chf_ctx* ctx, T* X, int64_t ldx, int m, double*
     for (int c = 0; c < m; c += nb) {
         const int w = std::min(nb, m - c);
         hx_step<T>(H, X + c, ldx, W, ldw, nullptr, 0, w, 1.0, 0.0, 0.0, s, 0);
-        gram_product<T>(ctx, X, ldx, W, ldw, n_rows, m, w, Hs + c, m, s);
+        gram_product<T, T>(ctx, X, ldx, W, ldw, n_rows, m, w, Hs + c, m, s);
     }
     symmetrize_kernel<<<unsigned((int64_t(m) * m + 255) / 256), 256, 0, s>>>(m, Hs);
     LAUNCH_CHECK();
@@ -800,10 +642,10 @@ int gram(chf_ctx* ctx, chf_dtype dtype, const void* A, int64_t lda, const void* 
         if (!S || lds < n || n_rows < 1) fail(CHF_EINVAL, "gram: bad output or row count");
         hipStream_t s = static_cast<hipStream_t>(stream);
         if (dtype == CHF_F64)
-            gram_product<double>(ctx, static_cast<const double*>(A), lda, static_cast<const double*>(B), ldb, n_rows, m, n,
+            gram_product<double, double>(ctx, static_cast<const double*>(A), lda, static_cast<const double*>(B), ldb, n_rows, m, n,
                                  S, lds, s);
         else
-            gram_product<float>(ctx, static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, n_rows, m, n,
+            gram_product<float, float>(ctx, static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, n_rows, m, n,
                                 S, lds, s);
     });
 }
@@ -864,14 +706,15 @@ static WsNeed ws_need(const chf_ham* H, int op, chf_dtype dtype, int nvec, int64
         break;
     case CHF_WS_ORTHONORMALIZE:
         w.scratch = mm_scratch_bytes(nvec, cholqr_extra(nvec));
-        w.scratch2 = gram_slices(n_rows, nvec, nvec, es, nvec).part_bytes;
+        w.scratch2 = gram_slices(n_rows, nvec, nvec, es, es, nvec, true).part_bytes;
         break;
     case CHF_WS_RAYLEIGH_RITZ: {
         if (ldw <= 0) fail(CHF_EINVAL, "chf_workspace_bytes: Rayleigh-Ritz needs the work leading dimension");
         const int nb = int(std::min<int64_t>(nvec, ldw));
         w.kb = kb_coef_bytes(H, nb, es);
         w.scratch = mm_scratch_bytes(nvec, rr_extra(nvec));
-        w.scratch2 = gram_slices(n_rows, nvec, nb, es, nvec).part_bytes;
+        w.scratch2 = gram_slices(n_rows, nvec, nb, es, es, nvec, false).part_bytes;
+        if (nvec % nb) w.scratch2 = std::max(w.scratch2, gram_slices(n_rows, nvec, nvec % nb, es, es, nvec, false).part_bytes);
         break;
     }
     case CHF_WS_LANCZOS:

@@ -63,8 +63,19 @@ template <class T>
 void rayleigh_ritz_t(chf_ham* H, chf_ctx* ctx, T* X, int64_t ldx, int m, double* eig_host, T* W, int64_t ldw,
                      hipStream_t s);
 void lanczos_run(chf_ham* H, chf_ctx* ctx, const double* v0, int k, double* out3, hipStream_t s);
-template <class T>
-void gram_product(chf_ctx* ctx, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t n_rows, int m, int n,
+
+// S = A^T B (m x n, FP64, row stride lds) over n_rows rows of TI, multiplied and
+// added in TA within a row slice, the slices' partials in FP64 (gram.hip)
+struct GramSlices {
+    int64_t tiles;        // pieces of S per slice
+    int64_t rows;         // rows per slice
+    int64_t group;        // slices whose partials are held at once
+    int64_t part_stride;  // values of one partial
+    size_t part_bytes;    // partials scratch
+};
+GramSlices gram_slices(int64_t n_rows, int m, int n, size_t acc_bytes, size_t in_bytes, int64_t ld, bool symmetric);
+template <class TI, class TA>
+void gram_product(chf_ctx* ctx, const TI* A, int64_t lda, const TI* B, int64_t ldb, int64_t n_rows, int m, int n,
                   double* S, int64_t lds, hipStream_t s);
 
 }  // namespace chf

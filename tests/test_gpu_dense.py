@@ -55,6 +55,37 @@ def test_gram_f32(system, n, m):
     assert np.array_equal(S.cpu().numpy(), S.cpu().numpy().T)
 
 
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-15), (torch.float32, 1e-7)])
+@pytest.mark.parametrize("m,k", [(1, 0), (16, 0), (17, 0), (32, 0), (33, 0), (64, 0), (65, 0), (128, 0), (129, 0), (257, 0),
+                                 (1, 1), (3, 64), (65, 16), (130, 5), (5, 130), (64, 33)])
+@pytest.mark.parametrize("n", [1, 31, 257, 9001])
+def test_gram_tile_edges(system, dtype, tol, m, k, n):
+    # widths at the edges of the 16, 32, 64 and 128 column pieces, row counts
+    # around the unrolled steps and slices; the blocks are columns of wider ones,
+    # off any alignment and with NaN beside them.  A sum of n products of N(0, 1)
+    # pairs in one order is off by eps sqrt(n) per term of a random walk: below
+    # 8 eps max(n, 8) by far.
+    B = system["B"]
+    rng = np.random.default_rng(m + 7 * k + n)
+
+    def block(w, pad, off):
+        X = torch.full((n, w + pad), float("nan"), dtype=dtype, device="cuda")
+        X[:, off:off + w] = torch.from_numpy(rng.standard_normal((n, w))).to(device="cuda", dtype=dtype)
+        return X[:, off:off + w]
+
+    for pad, off in ((0, 0), (3, 1), (4, 4), (8, 0)):
+        At = block(m, pad, off)
+        Bt = block(k, 5, 2) if k else At
+        S = torch.full((m, Bt.shape[1] + 1), -7.0, dtype=torch.float64, device="cuda")
+        B.gram(system["ctx"], At, Bt, S[:, :-1])
+        ref = At.double().cpu().numpy().T @ Bt.double().cpu().numpy()
+        got = S.cpu().numpy()
+        assert np.abs(got[:, :-1] - ref).max() < 8 * tol * max(n, 8), (pad, off)
+        assert (got[:, -1] == -7.0).all()
+        if not k:
+            assert np.array_equal(got[:, :-1], got[:, :-1].T)
+
+
 def test_gram_f32_wide_block_norms_unbiased(system):
     """FP32 Gram of a wide block over many rows (1,048,576 x 8192, unit
     columns): the diagonal, the columns' squared norms, is what FP32
