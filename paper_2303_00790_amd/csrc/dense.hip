@@ -4,8 +4,8 @@
 // Paper: ChFSI orthonormalises the filtered block and projects H onto it
 // (the CheFSI paragraph; details of the PARSEC implementation are deferred to
 // its ChFSI reference).  The Gram products X^T X and X^T (H X) are kernels of
-// gram.hip; the N x M x M block updates X R^{-1} and X Q are plain triangular
-// solves and GEMMs (rocBLAS on MFMA); the M x M Cholesky factorisation and
+// gram.hip; the solve X R^{-1} is trsolve.hip; the N x M x M block update X Q is a
+// plain GEMM (rocBLAS on MFMA); the M x M Cholesky factorisation and
 // symmetric eigensolve run in FP64 through rocSOLVER.
 #include <algorithm>
 #include <cmath>
@@ -137,14 +137,6 @@ __global__ void cast_matrix_kernel(int64_t n, const double* __restrict__ src, T*
     if (i < n) dst[i] = T(src[i]);
 }
 
-// column-major upper triangle kept, strictly lower part zeroed (M x M, ld M)
-__global__ void keep_upper_kernel(int m, double* __restrict__ R) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= int64_t(m) * m) return;
-    const int col = int(idx / m), row = int(idx % m);
-    if (row > col) R[idx] = 0.0;
-}
-
 __global__ void symmetrize_kernel(int m, double* __restrict__ S) {
     const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (idx >= int64_t(m) * m) return;
@@ -198,16 +190,17 @@ static int guard(F&& f) {
 
 // S (row-major M x M, FP64) lives at the start of ctx->scratch; the rest holds
 // the cast factor for FP32 updates and rocSOLVER's info word.
-static size_t mm_scratch_bytes(int m, size_t extra_bytes) {
-    return size_t(m) * m * (sizeof(double) + sizeof(float)) + extra_bytes + 256;
-}
+static size_t mm_tail(int m) { return (size_t(m) * m * (sizeof(double) + sizeof(float)) + 256 + 255) / 256 * 256; }
+static size_t mm_scratch_bytes(int m, size_t extra_bytes) { return mm_tail(m) + extra_bytes; }
 static double* mm_scratch(chf_ctx* ctx, int m, size_t extra_bytes) {
     ctx->scratch.ensure(mm_scratch_bytes(m, extra_bytes));
     return ctx->scratch.as<double>();
 }
-// extra bytes after the M x M matrices: Cholesky-QR keeps the Gram diagonal,
-// Rayleigh-Ritz the eigenvalues and the eigensolver's off-diagonal
-static size_t cholqr_extra(int m) { return size_t(m) * sizeof(double); }
+// extra bytes after the M x M matrices: Cholesky-QR keeps the Gram diagonal and
+// solve_upper's scratch, Rayleigh-Ritz the eigenvalues and the eigensolver's off-diagonal
+static size_t cholqr_extra(int m, size_t elem_bytes) {
+    return size_t(m + 1) / 2 * 2 * sizeof(double) + size_t(solve_upper_values(m)) * elem_bytes;
+}
 static size_t rr_extra(int m) { return size_t(m) * sizeof(double) * 2; }
 
 __global__ void diag_copy_kernel(int m, const double* __restrict__ S, double* __restrict__ d) {
@@ -264,8 +257,8 @@ template <class T>
 static int cholqr_once(chf_ctx* ctx, T* X, int64_t ldx, int64_t n_rows, int m, double shift_rel, bool gram64,
                        hipStream_t s) {
     constexpr bool f64 = std::is_same<T, double>::value;
-    double* S = mm_scratch(ctx, m, cholqr_extra(m));
-    double* diag = reinterpret_cast<double*>(reinterpret_cast<char*>(S) + size_t(m) * m * (sizeof(double) + sizeof(float)) + 256);
+    double* S = mm_scratch(ctx, m, cholqr_extra(m, sizeof(T)));
+    double* diag = reinterpret_cast<double*>(reinterpret_cast<char*>(S) + mm_tail(m));
     if (gram64) gram_product<T, double>(ctx, X, ldx, X, ldx, n_rows, m, m, S, m, s);
     else gram_product<T, T>(ctx, X, ldx, X, ldx, n_rows, m, m, S, m, s);
     if (shift_rel > 0) {
@@ -296,31 +289,8 @@ static int cholqr_once(chf_ctx* ctx, T* X, int64_t ldx, int64_t n_rows, int m, d
     if (info != 0) return info;
     const double thr = (f64 || gram64) ? kPivotRelF64 : kPivotRelF32;
     if (shift_rel == 0 && !(piv[0] >= thr)) return int(piv[1]) + 1;
-    keep_upper_kernel<<<unsigned((int64_t(m) * m + 255) / 256), 256, 0, s>>>(m, S);
-    LAUNCH_CHECK();
-    // X is row-major [n_rows][ldx] = column-major Xc [m][n_rows] (ld ldx).
-    // X R^{-1}  <=>  Xc <- R^{-T} Xc : left-side solve with U^T.
-    // (in row panels: each call's block spans fewer than kBlasMaxElems elements)
-    const int64_t pt = std::max<int64_t>(1, std::min<int64_t>(n_rows, kBlasMaxElems / std::max<int64_t>(1, ldx)));
-    float* R32 = reinterpret_cast<float*>(reinterpret_cast<char*>(S) + size_t(m) * m * sizeof(double));
-    if (!f64) {
-        cast_matrix_kernel<float><<<unsigned((int64_t(m) * m + 255) / 256), 256, 0, s>>>(int64_t(m) * m, S, R32);
-        LAUNCH_CHECK();
-    }
-    for (int64_t r0 = 0; r0 < n_rows; r0 += pt) {
-        const int64_t rows = std::min(pt, n_rows - r0);
-        if (f64) {
-            const double one = 1.0;
-            ROCBLAS_CHECK(rocblas_dtrsm(ctx->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_transpose,
-                                        rocblas_diagonal_non_unit, m, rocblas_int(rows), &one, S, m,
-                                        reinterpret_cast<double*>(X + r0 * ldx), rocblas_int(ldx)));
-        } else {
-            const float one = 1.0f;
-            ROCBLAS_CHECK(rocblas_strsm(ctx->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_transpose,
-                                        rocblas_diagonal_non_unit, m, rocblas_int(rows), &one, R32, m,
-                                        reinterpret_cast<float*>(X + r0 * ldx), rocblas_int(ldx)));
-        }
-    }
+    // X is row-major, S = R column-major (its strictly lower part is not read)
+    solve_upper<T>(X, ldx, n_rows, m, S, reinterpret_cast<T*>(diag + (m + 1) / 2 * 2), s);
     return 0;
 }
 
@@ -365,7 +335,7 @@ void rayleigh_ritz_t(chf_ham* H, chf_ctx* ctx, T* X, int64_t ldx, int m, double*
                             hipStream_t s) {
     const int64_t n_rows = H->grid.n_rows;
     double* Hs = mm_scratch(ctx, m, rr_extra(m));
-    double* evals = reinterpret_cast<double*>(reinterpret_cast<char*>(Hs) + size_t(m) * m * (sizeof(double) + sizeof(float)) + 256);
+    double* evals = reinterpret_cast<double*>(reinterpret_cast<char*>(Hs) + mm_tail(m));
     double* E = evals + m;
     int* dinfo = reinterpret_cast<int*>(reinterpret_cast<char*>(Hs) + size_t(m) * m * (sizeof(double) + sizeof(float)));
     // Hs[:, c:c+nb] = X^T (H X[:, c:c+nb]), blockwise through W
@@ -705,7 +675,7 @@ static WsNeed ws_need(const chf_ham* H, int op, chf_dtype dtype, int nvec, int64
         w.kb = kb_coef_bytes(H, nvec, es);
         break;
     case CHF_WS_ORTHONORMALIZE:
-        w.scratch = mm_scratch_bytes(nvec, cholqr_extra(nvec));
+        w.scratch = mm_scratch_bytes(nvec, cholqr_extra(nvec, es));
         w.scratch2 = gram_slices(n_rows, nvec, nvec, es, es, nvec, true).part_bytes;
         break;
     case CHF_WS_RAYLEIGH_RITZ: {

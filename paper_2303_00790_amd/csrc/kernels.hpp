@@ -78,4 +78,10 @@ template <class TI, class TA>
 void gram_product(chf_ctx* ctx, const TI* A, int64_t lda, const TI* B, int64_t ldb, int64_t n_rows, int m, int n,
                   double* S, int64_t lds, hipStream_t s);
 
+// X <- X R^{-1} in place: R upper triangular, column-major m x m (its lower part
+// is not read); work: solve_upper_values(m) values of T (trsolve.hip)
+int64_t solve_upper_values(int m);
+template <class T>
+void solve_upper(T* X, int64_t ldx, int64_t n_rows, int m, const double* R, T* work, hipStream_t s);
+
 }  // namespace chf

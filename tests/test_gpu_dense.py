@@ -380,3 +380,26 @@ def test_absurd_reservation_reports_out_of_memory(system):
     s["Hg"].apply(X, Y)
     torch.cuda.synchronize()
     assert bool(torch.isfinite(Y).all())
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-13), (torch.float32, 2e-6)])
+@pytest.mark.parametrize("n,m", [(40, 1), (131, 16), (500, 17), (1000, 127), (1000, 128), (1000, 129), (3001, 257), (5000, 400)])
+def test_orthonormalize_panel_edges(system, dtype, tol, n, m):
+    # widths around the 16 columns of a product and the 128 of a panel, rows not
+    # a multiple of a wave's 32, a leading dimension off any alignment with NaN
+    # in the columns beside the block, which stay.  A well-conditioned block: Q
+    # R = X and Q^T Q = 1 to the rounding of sums of up to m terms of the last
+    # pass, eps (sqrt(m) + 2) and a factor of 4 for the condition number (~3).
+    B = system["B"]
+    rng = np.random.default_rng(n + m)
+    X = rng.standard_normal((n, m)) * np.exp(rng.uniform(-3, 3, m))
+    Xg = torch.full((n, m + 3), float("nan"), dtype=dtype, device="cuda")
+    Xg[:, 1:1 + m] = torch.from_numpy(X).to(device="cuda", dtype=dtype)
+    X = Xg[:, 1:1 + m].double().cpu().numpy()
+    B.orthonormalize(system["ctx"], Xg[:, 1:1 + m])
+    Q = Xg[:, 1:1 + m].double().cpu().numpy()
+    ref, R = np.linalg.qr(X)
+    ref *= np.sign(np.diag(R))
+    assert np.abs(Q.T @ Q - np.eye(m)).max() < tol * (np.sqrt(m) + 2)
+    assert np.abs(Q - ref).max() < 4 * tol * (np.sqrt(m) + 2) * np.abs(ref).max()
+    assert bool(torch.isnan(Xg[:, 0]).all()) and bool(torch.isnan(Xg[:, 1 + m:]).all())
