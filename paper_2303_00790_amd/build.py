@@ -17,7 +17,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libchfsi.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
-SOURCES = ["host_grid.cpp", "capi.cpp", "hx.hip", "dense.hip", "gram.hip", "trsolve.hip", "scf.hip", "dnet.hip"]
+SOURCES = ["host_grid.cpp", "capi.cpp", "hx.hip", "dense.hip", "gram.hip", "trsolve.hip", "eig.hip", "scf.hip", "dnet.hip"]
 
 # Packed FP32 instructions are disabled for all device code; host code is
 # compiled without floating-point contraction so that the grid / projector

@@ -197,11 +197,11 @@ static double* mm_scratch(chf_ctx* ctx, int m, size_t extra_bytes) {
     return ctx->scratch.as<double>();
 }
 // extra bytes after the M x M matrices: Cholesky-QR keeps the Gram diagonal and
-// solve_upper's scratch, Rayleigh-Ritz the eigenvalues and the eigensolver's off-diagonal
+// solve_upper's scratch, Rayleigh-Ritz the eigenvalues and the eigensolver's off-diagonal and scratch
 static size_t cholqr_extra(int m, size_t elem_bytes) {
     return size_t(m + 1) / 2 * 2 * sizeof(double) + size_t(solve_upper_values(m)) * elem_bytes;
 }
-static size_t rr_extra(int m) { return size_t(m) * sizeof(double) * 2; }
+static size_t rr_extra(int m) { return size_t(m) * sizeof(double) * 2 + eig_work_bytes(m); }
 
 __global__ void diag_copy_kernel(int m, const double* __restrict__ S, double* __restrict__ d) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -348,7 +348,7 @@ void rayleigh_ritz_t(chf_ham* H, chf_ctx* ctx, T* X, int64_t ldx, int m, double*
     symmetrize_kernel<<<unsigned((int64_t(m) * m + 255) / 256), 256, 0, s>>>(m, Hs);
     LAUNCH_CHECK();
     ROCBLAS_CHECK(rocblas_set_stream(ctx->blas, s));
-    ROCBLAS_CHECK(rocsolver_dsyevd(ctx->blas, rocblas_evect_original, rocblas_fill_upper, m, Hs, m, evals, E, dinfo));
+    sym_eig(ctx, m, Hs, evals, E, E + m, dinfo, s);
     int info = 0;
     HIP_CHECK(hipMemcpyAsync(&info, dinfo, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipMemcpyAsync(eig_host, evals, size_t(m) * sizeof(double), hipMemcpyDeviceToHost, s));

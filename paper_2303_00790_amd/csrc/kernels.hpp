@@ -84,4 +84,10 @@ int64_t solve_upper_values(int m);
 template <class T>
 void solve_upper(T* X, int64_t ldx, int64_t n_rows, int m, const double* R, T* work, hipStream_t s);
 
+// eigenvalues (ascending) and eigenvectors (columns, over S) of the symmetric
+// m x m S; E: m doubles, work: eig_work_bytes(m) (eig.hip)
+constexpr int kEigMax = 192;
+size_t eig_work_bytes(int m);
+void sym_eig(chf_ctx* ctx, int m, double* S, double* evals, double* E, double* work, int* info, hipStream_t s);
+
 }  // namespace chf

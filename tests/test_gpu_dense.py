@@ -403,3 +403,32 @@ def test_orthonormalize_panel_edges(system, dtype, tol, n, m):
     assert np.abs(Q.T @ Q - np.eye(m)).max() < tol * (np.sqrt(m) + 2)
     assert np.abs(Q - ref).max() < 4 * tol * (np.sqrt(m) + 2) * np.abs(ref).max()
     assert bool(torch.isnan(Xg[:, 0]).all()) and bool(torch.isnan(Xg[:, 1 + m:]).all())
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 16, 63, 64, 65, 127, 128, 129, 191, 192, 193])
+@pytest.mark.parametrize("kind", ["random", "invariant"])
+def test_rayleigh_ritz_eigensolver_edges(system, m, kind):
+    # the own reduction to tridiagonal form (M <= 192) at the edges of its
+    # variants and the library's beyond.  "invariant":
+    # unit vectors far apart, whose projected matrix is (nearly) diagonal with
+    # many close entries, so that reflectors vanish.  Eigenvalues to
+    # 1e-13 of the matrix norm times m (backward error of the reduction and
+    # of divide and conquer, ~m eps), columns orthonormal to the same.
+    s = system
+    n = s["g"].n
+    if kind == "random":
+        X = np.linalg.qr(np.random.default_rng(m).standard_normal((n, m)))[0]
+    else:
+        X = np.zeros((n, m))
+        X[np.linspace(0, n - 1, m).astype(int), np.arange(m)] = 1.0
+    P = X.T @ s["Ho"].apply(X)
+    P = 0.5 * (P + P.T)
+    ref = np.linalg.eigvalsh(P)
+    Xg = to_rows(s, X, torch.float64)
+    W = torch.zeros_like(Xg)
+    eig = s["B"].rayleigh_ritz(s["Hg"], s["ctx"], Xg, W)
+    Q = from_rows(s, Xg, m)
+    tol = 1e-13 * max(m, 10)
+    assert np.abs(np.asarray(eig) - ref).max() < tol * np.abs(ref).max()
+    assert np.abs(Q.T @ Q - np.eye(m)).max() < tol
+    assert np.abs(Q.T @ s["Ho"].apply(Q) - np.diag(np.asarray(eig))).max() < tol * max(np.abs(P).max(), np.abs(ref).max())
