@@ -4,9 +4,9 @@
 // Paper: ChFSI orthonormalises the filtered block and projects H onto it
 // (the CheFSI paragraph; details of the PARSEC implementation are deferred to
 // its ChFSI reference).  The Gram products X^T X and X^T (H X) are kernels of
-// gram.hip; the solve X R^{-1} is trsolve.hip; the N x M x M block update X Q is a
-// plain GEMM (rocBLAS on MFMA); the M x M Cholesky factorisation and
-// symmetric eigensolve run in FP64 through rocSOLVER.
+// gram.hip, the FP64 Cholesky factorisation and the solve X R^{-1} trsolve.hip, the
+// M x M symmetric eigensolve eig.hip (FP64, around rocSOLVER); the N x M x M block
+// update X Q is a plain GEMM (rocBLAS on MFMA).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -197,14 +197,16 @@ static double* mm_scratch(chf_ctx* ctx, int m, size_t extra_bytes) {
     return ctx->scratch.as<double>();
 }
 // extra bytes after the M x M matrices: Cholesky-QR keeps the Gram diagonal and
-// solve_upper's scratch, Rayleigh-Ritz the eigenvalues and the eigensolver's off-diagonal and scratch
+// the factorisation's scratch, Rayleigh-Ritz the eigenvalues and the eigensolver's
+// off-diagonal and scratch
 static size_t cholqr_extra(int m, size_t elem_bytes) {
-    return size_t(m + 1) / 2 * 2 * sizeof(double) + size_t(solve_upper_values(m)) * elem_bytes;
+    return size_t(m + 1) / 2 * 2 * sizeof(double) + cholesky_work_bytes(m, elem_bytes);
 }
 static size_t rr_extra(int m) { return size_t(m) * sizeof(double) * 2 + eig_work_bytes(m); }
 
-__global__ void diag_copy_kernel(int m, const double* __restrict__ S, double* __restrict__ d) {
+__global__ void diag_copy_kernel(int m, const double* __restrict__ S, double* __restrict__ d, int* __restrict__ info) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *info = 0;
     if (i < m) d[i] = S[int64_t(i) * m + i];
 }
 
@@ -250,7 +252,7 @@ constexpr double kPivotRelF32 = 1e-5;
 
 // One Cholesky-QR pass: S = X^T X (in the block precision, or in FP64 for an
 // FP32 block when gram64), S = R^T R in FP64, X <- X R^{-1} in the block
-// precision.  Returns 0, or the rocSOLVER info (> 0: leading minor not
+// precision.  Returns 0, or the factorisation's info (> 0: leading minor not
 // positive definite), or the 1-based index of a pivot below the threshold of
 // the Gram's precision; X is unchanged unless 0 is returned.
 template <class T>
@@ -270,14 +272,13 @@ static int cholqr_once(chf_ctx* ctx, T* X, int64_t ldx, int64_t n_rows, int m, d
         add_diag_kernel<<<(m + 255) / 256, 256, 0, s>>>(m, S, shift_rel * htr / m);
         LAUNCH_CHECK();
     }
-    ROCBLAS_CHECK(rocblas_set_stream(ctx->blas, s));
-    // row-major S equals its column-major view (symmetric); potrf(upper) gives
-    // column-major U with S = U^T U, i.e. R = U.
+    // row-major S equals its column-major view (symmetric)
     int* dinfo = reinterpret_cast<int*>(reinterpret_cast<char*>(S) + size_t(m) * m * sizeof(double) +
                                         size_t(m) * m * sizeof(float));
-    diag_copy_kernel<<<(m + 255) / 256, 256, 0, s>>>(m, S, diag);
+    diag_copy_kernel<<<(m + 255) / 256, 256, 0, s>>>(m, S, diag, dinfo);
     LAUNCH_CHECK();
-    ROCBLAS_CHECK(rocsolver_dpotrf(ctx->blas, rocblas_fill_upper, m, S, m, dinfo));
+    void* work = diag + (m + 1) / 2 * 2;
+    cholesky<T>(S, m, work, dinfo, s);
     double piv[2] = {1.0, 0.0};
     double* pr = reinterpret_cast<double*>(ctx->info.p) + 2;
     pivot_ratio_kernel<<<1, 256, 0, s>>>(m, S, diag, pr);
@@ -290,7 +291,7 @@ static int cholqr_once(chf_ctx* ctx, T* X, int64_t ldx, int64_t n_rows, int m, d
     const double thr = (f64 || gram64) ? kPivotRelF64 : kPivotRelF32;
     if (shift_rel == 0 && !(piv[0] >= thr)) return int(piv[1]) + 1;
     // X is row-major, S = R column-major (its strictly lower part is not read)
-    solve_upper<T>(X, ldx, n_rows, m, S, reinterpret_cast<T*>(diag + (m + 1) / 2 * 2), s);
+    solve_upper<T>(X, ldx, n_rows, m, S, work, s);
     return 0;
 }
 

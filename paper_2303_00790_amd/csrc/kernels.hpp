@@ -78,11 +78,15 @@ template <class TI, class TA>
 void gram_product(chf_ctx* ctx, const TI* A, int64_t lda, const TI* B, int64_t ldb, int64_t n_rows, int m, int n,
                   double* S, int64_t lds, hipStream_t s);
 
-// X <- X R^{-1} in place: R upper triangular, column-major m x m (its lower part
-// is not read); work: solve_upper_values(m) values of T (trsolve.hip)
-int64_t solve_upper_values(int m);
+// Cholesky factor and solve of a Cholesky-QR pass (trsolve.hip): S = R^T R, R upper,
+// column-major, over the upper triangle of S (*info as LAPACK's potrf; set it to
+// 0 before), then X <- X R^{-1} in place with the same work, cholesky_work_bytes
+// long and 16-byte aligned
+size_t cholesky_work_bytes(int m, size_t elem_bytes);
 template <class T>
-void solve_upper(T* X, int64_t ldx, int64_t n_rows, int m, const double* R, T* work, hipStream_t s);
+void cholesky(double* S, int m, void* work, int* info, hipStream_t s);
+template <class T>
+void solve_upper(T* X, int64_t ldx, int64_t n_rows, int m, const double* R, void* work, hipStream_t s);
 
 // eigenvalues (ascending) and eigenvectors (columns, over S) of the symmetric
 // m x m S; E: m doubles, work: eig_work_bytes(m) (eig.hip)

@@ -432,3 +432,16 @@ def test_rayleigh_ritz_eigensolver_edges(system, m, kind):
     assert np.abs(np.asarray(eig) - ref).max() < tol * np.abs(ref).max()
     assert np.abs(Q.T @ Q - np.eye(m)).max() < tol
     assert np.abs(Q.T @ s["Ho"].apply(Q) - np.diag(np.asarray(eig))).max() < tol * max(np.abs(P).max(), np.abs(ref).max())
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("col", [0, 15, 16, 127, 128, 200])
+def test_orthonormalize_reports_the_failing_column(system, dtype, col):
+    # a zero column has no direction: every pass's factorisation stops at it,
+    # in whichever 16 x 16 or 128-column block it lies
+    B = system["B"]
+    X = np.random.default_rng(col).standard_normal((2000, 201))
+    X[:, col] = 0.0
+    Xg = torch.from_numpy(X).to(device="cuda", dtype=dtype)
+    with pytest.raises(B.ChfError, match=rf"minor {col + 1}\b"):
+        B.orthonormalize(system["ctx"], Xg)
