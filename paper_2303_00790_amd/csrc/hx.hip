@@ -649,7 +649,8 @@ __global__ void __launch_bounds__(64 * kLanes) hx_tiled_kernel(int64_t n_blocks,
 // 7.8 of them before the first plane; now 16.3.  us per launch, before -> now:
 // 5 nm, 256 FP32 vectors 3337 -> 2494; 8 nm 10815 -> 8112; 5 nm, 128 FP64
 // 3389 -> 2635; 3 nm, 128 FP64 1011 -> 783; 2.5 nm, 256 FP32 674 -> 509;
-// 1.1 nm, 128 FP64 154 -> 110; 2 nm, 97 FP64 (8-byte pieces) 470 -> 473.
+// 1.1 nm, 128 FP64 154 -> 110; 2 nm, 97 FP64 (rows on 8 bytes, PB = 8) 470 -> 380,
+// 474 with every 16 bytes in two pieces of 8.
 // ---------------------------------------------------------------------------
 constexpr int kSlotBytes = 512;      // staged coefficients of an atom: 4 channels x 128 bytes
 constexpr int kRowGroup = 16;        // rows of a KB weight matrix
@@ -682,19 +683,12 @@ __device__ inline mf4 mfma4(float a, float b, mf4 c) { return __builtin_amdgcn_m
 __device__ inline md4 mfma4(double a, double b, md4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-// 16 bytes in pieces of PB bytes (8 where rows are only 8-byte aligned).
-// policy 2 = non-temporal: Y_{k-1} is read and Y_{k+1} written once per
+// 16 bytes from any multiple of 4.  policy 2 = non-temporal: Y_{k-1} is read and Y_{k+1} written once per
 // launch, so they should not displace the X rows that neighbouring tiles read
 // again as halos.
-template <class V, int PB, int POLICY>
+template <class V, int POLICY>
 __device__ inline V bload16(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    if constexpr (PB == 16) {
-        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, voff, int(soff), POLICY));
-    } else {
-        const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(r, voff, int(soff), POLICY);
-        const u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(r, voff, int(soff) + 8, POLICY);
-        return __builtin_bit_cast(V, u32x4{lo.x, lo.y, hi.x, hi.y});
-    }
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, voff, int(soff), POLICY));
 }
 
 template <class T, int PB, int SLOTS>
@@ -787,9 +781,9 @@ hx_tile_kernel(int n_blocks, int n_chunks, const int32_t* __restrict__ bnb, cons
         hoff[u] = vok ? unsigned(lx + 8 * ly) * unsigned(ldx) * es + vbytes : kOOB;
     }
     auto load_plane = [&](int zz) -> V {
-        if (zz < 0) return bload16<V, PB, 0>(rZm, off_x, unsigned(zz + 8) * plane_x);
-        if (zz >= 8) return bload16<V, PB, 0>(rZp, off_x, unsigned(zz - 8) * plane_x);
-        return bload16<V, PB, 0>(rOwn, off_x, unsigned(zz) * plane_x);
+        if (zz < 0) return bload16<V, 0>(rZm, off_x, unsigned(zz + 8) * plane_x);
+        if (zz >= 8) return bload16<V, 0>(rZp, off_x, unsigned(zz - 8) * plane_x);
+        return bload16<V, 0>(rOwn, off_x, unsigned(zz) * plane_x);
     };
 
     // the X window of this column, the halos of plane 0, Y_{k-1} and V_eff
@@ -797,7 +791,7 @@ hx_tile_kernel(int n_blocks, int n_chunks, const int32_t* __restrict__ bnb, cons
 #pragma unroll
     for (int i = 0; i < 13; ++i) w[i] = load_plane(i - 6);
 #pragma unroll
-    for (int u = 0; u < 3; ++u) hv[u] = bload16<V, PB, 0>(rH[u], hoff[u], 0u);
+    for (int u = 0; u < 3; ++u) hv[u] = bload16<V, 0>(rH[u], hoff[u], 0u);
 
     // KB coefficients of the block's atoms, alpha applied: 16 slots a round
     const int a0 = blk_atom_off[blk];
@@ -900,11 +894,11 @@ hx_tile_kernel(int n_blocks, int n_chunks, const int32_t* __restrict__ bnb, cons
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         // loads of this plane's update and of the next plane
-        const V zc = bload16<V, PB, 2>(rZ, off_z, unsigned(z) * plane_z);   // zero without Z (empty buffer)
+        const V zc = bload16<V, 2>(rZ, off_z, unsigned(z) * plane_z);   // zero without Z (empty buffer)
         const T vr = veff[base + col + 64 * z];
         if (z < 7) {
 #pragma unroll
-            for (int u = 0; u < 3; ++u) hv[u] = bload16<V, PB, 0>(rH[u], hoff[u], unsigned(z + 1) * plane_x);
+            for (int u = 0; u < 3; ++u) hv[u] = bload16<V, 0>(rH[u], hoff[u], unsigned(z + 1) * plane_x);
             w[z + 13] = load_plane(z + 7);
         }
 
@@ -942,8 +936,10 @@ hx_tile_kernel(int n_blocks, int n_chunks, const int32_t* __restrict__ bnb, cons
         if constexpr (PB == 16) {
             __builtin_amdgcn_raw_buffer_store_b128(yb, rY, oy, 0, 2);
         } else {
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{yb.x, yb.y}, rY, oy, 0, 2);
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{yb.z, yb.w}, rY, vbase + N / 2 < nvec ? oy + 8 : kOOB, 0, 2);
+            // a row's last piece may be half inside
+            const bool whole = vbase + N / 2 < nvec;
+            __builtin_amdgcn_raw_buffer_store_b128(yb, rY, whole ? oy : kOOB, 0, 2);
+            if (nvec % N) __builtin_amdgcn_raw_buffer_store_b64(u32x2{yb.x, yb.y}, rY, whole ? kOOB : oy, 0, 2);
         }
         if (z < 7) {
             // (the weights are not fetched above the stencil, whose operands
