@@ -11,7 +11,7 @@
 // more than the L1 holds until the other halves are wanted.
 //
 // Measured against the library's triangular solve (ms): 440,000 x 1024 FP32
-// 6.6 -> 4.6, 440,000 x 600 FP64 5.9 -> 3.3, 120,000 x 128 FP64 0.15 -> 0.066.
+// 6.6 -> 4.8, 440,000 x 600 FP64 5.9 -> 3.3, 120,000 x 128 FP64 0.15 -> 0.066.
 // Bound by the matrix cores: 64 FP32 (32 FP64) products, 2048 cycles, per 10
 // loads of 1 KB.  32 x 128 because the rows' earlier panels, too many to stay in
 // an L2, are read again for each panel: (M / 128 - 1) / 2 times in all.
@@ -338,7 +338,13 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
     const T* xr[RT];
 #pragma unroll
     for (int p = 0; p < RT; ++p) xr[p] = X + min(row0 + 16 * p + l, n_rows - 1) * ldx + N * kq;
-    Acc<T> acc[RT][CT];
+    // FP32: the products are summed over kTriBlock of k at a time, from zero, and the
+    // sums taken from the panel one after the other, as the blocked solve of a
+    // library does: one chain over all k rounds m / 4 times at the size of the whole
+    // (error against 64 bits at 600 columns 1.3e-6, in blocks 0.8e-6).  FP64
+    // has no registers for it: there the panel is where the products are added.
+    constexpr bool APART = sizeof(T) == 4;
+    Acc<T> acc[RT][CT], own[APART ? RT : 1][APART ? CT : 1];
     // columns past the end repeat the last one
     auto start = [&](int j0) {
 #pragma unroll
@@ -347,8 +353,12 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
             for (int q = 0; q < CT; ++q) {
                 const int64_t col = min(j0 + 16 * q + l, m - 1);
 #pragma unroll
-                for (int reg = 0; reg < 4; ++reg)
-                    acc[p][q][reg] = X[min(row0 + 16 * p + result_row<T>(reg, lane), n_rows - 1) * ldx + col];
+                for (int reg = 0; reg < 4; ++reg) {
+                    const T x = X[min(row0 + 16 * p + result_row<T>(reg, lane), n_rows - 1) * ldx + col];
+                    if constexpr (APART) own[p][q][reg] = x;
+                    else acc[p][q][reg] = x;
+                }
+                if constexpr (APART) acc[p][q] = Acc<T>{0, 0, 0, 0};
             }
     };
     start(0);
@@ -357,7 +367,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
         // two sets of operands: one is multiplied while the other is loaded; of X
         // two groups at a time, whole cache lines of its rows.  FP32: the order is
         // kept and the sums stay in accumulation registers, one wave per SIMD
-        // (4.6 ms at 440,000 x 1024; 5.2 as the compiler orders it for two waves).
+        // (4.8 ms at 440,000 x 1024; 5.2 as the compiler orders it for two waves).
         // FP64: two waves, whose products are long enough to cover the loads
         // (3.3 ms at 440,000 x 600; 3.6 with one).
         auto keep_order = [] {
@@ -419,6 +429,17 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
             fetch_b(S0{}, k0 + 4 * KG);
             keep_order();
             multiply(S1{}, S1{}, S1{});
+            if constexpr (APART) {
+                if ((k0 + 4 * KG) % kTriBlock == 0) {
+#pragma unroll
+                    for (int p = 0; p < RT; ++p)
+#pragma unroll
+                        for (int q = 0; q < CT; ++q) {
+                            own[p][q] += acc[p][q];
+                            acc[p][q] = Acc<T>{0, 0, 0, 0};
+                        }
+                }
+            }
         }
         // X_j - sum, turned from the result layout to the operand layout; columns
         // past the end count as zero
@@ -430,7 +451,12 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
             for (int p = 0; p < RT; ++p)
 #pragma unroll
                 for (int reg = 0; reg < 4; ++reg)
-                    tw[(p * 16 + result_row<T>(reg, lane)) * LP + l] = in ? acc[p][q][reg] : T(0);
+                {
+                    T x;
+                    if constexpr (APART) x = own[p][q][reg];
+                    else x = acc[p][q][reg];
+                    tw[(p * 16 + result_row<T>(reg, lane)) * LP + l] = in ? x : T(0);
+                }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
             for (int p = 0; p < RT; ++p)
