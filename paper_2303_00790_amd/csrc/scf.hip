@@ -384,8 +384,8 @@ static void build_ghosts(chf_ham* H, hipStream_t s) {
 //  cg_update   x += a p, r -= a ap with a = rr / p.ap, partials of r.r
 //
 // A vector is 4 MB at 2.5 nm and stays in the caches, so an iteration costs
-// its launches and the latency of its passes: 12.2 us for the stencil and 6.9
-// for the update there, 6.5 and 3.9 at 1.1 nm.  Nine kernels and two host round
+// its launches and the latency of its passes: 11.9 us for the stencil and 6.9
+// for the update there, 6.3 and 4.4 at 1.1 nm.  Nine kernels and two host round
 // trips per iteration, with the stencil on 1 of the 16 lanes of the
 // multi-vector tile kernel, took 113 us at 2.5 nm (51 of them the stencil); a
 // solve from zero went from 44.4 to 7.8 ms.  Folding p's update into the
@@ -513,7 +513,9 @@ __global__ void __launch_bounds__(512) cg_stencil_kernel(int n_blocks, int per_g
         if (blk + 1 < last) load(blk + 1);
         __syncthreads();
         double acc = k.c[0] * v;
-#pragma unroll
+        // (rolled: fewer registers leave the next block's loads more room; unrolled it
+        // took 12.2 instead of 11.9 us at 2.5 nm, 14.5 instead of 13.8 at 3 nm)
+#pragma unroll 1
         for (int s = 1; s <= 6; ++s) {
             double sum = cz[-64 * s] + cz[64 * s];
             sum += cx[-s];
