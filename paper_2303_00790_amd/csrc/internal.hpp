@@ -188,11 +188,6 @@ struct chf_ham {
     chf::DevBuf flag;           // int: set by the V_eff cast when a value is NaN or Inf
     int dtypes = 0;
     bool has_nbr = false;
-    // Poisson exterior stencil points (built on first use, scf.hip)
-    chf::DevBuf ghost_owner;    // int32 [n_ghost] row of the inside point
-    chf::DevBuf ghost_k;        // int32 [n_ghost] |offset| 1..6
-    chf::DevBuf ghost_ijk;      // int32 [n_ghost][3]
-    int64_t n_ghost = -1;
     hipStream_t stream = nullptr;  // stream of the last call (for destroy)
 };
 

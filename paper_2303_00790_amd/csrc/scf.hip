@@ -9,7 +9,6 @@
 // integral of the squared difference of the last two potentials -- is below
 // 1e-4 Ry.
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstring>
 #include <memory>
@@ -149,7 +148,7 @@ __global__ void __launch_bounds__(256) moments_reduce_kernel(int nb, const doubl
     if (threadIdx.x == 0) mom[blockIdx.x] = h3 * sh[0];
 }
 
-__device__ inline int mom_index(int a, int b, int c) {
+__host__ __device__ constexpr int mom_index(int a, int b, int c) {
     // position of (a, b, c) in the n-major, a-descending, b-descending order
     const int n = a + b + c;
     int k = 0;
@@ -159,65 +158,118 @@ __device__ inline int mom_index(int a, int b, int c) {
     return k + (n - a - b);
 }
 
-__device__ inline double mom(const double* M, int a, int b, int c) { return M[mom_index(a, b, c)]; }
-
 // sum over |alpha| = n of n! / alpha! x^alpha f(alpha)
-template <class F>
-__device__ inline double contract(int n, double x, double y, double z, F f) {
-    const double fact[5] = {1, 1, 2, 6, 24};
-    double px[5] = {1, x, x * x, x * x * x, x * x * x * x};
-    double py[5] = {1, y, y * y, y * y * y, y * y * y * y};
-    double pz[5] = {1, z, z * z, z * z * z, z * z * z * z};
+template <int N, class F>
+__device__ inline double contract(const double* px, const double* py, const double* pz, F f) {
+    constexpr double fact[5] = {1, 1, 2, 6, 24};
     double s = 0.0;
-    for (int a = n; a >= 0; --a)
-        for (int b = n - a; b >= 0; --b) {
-            const int c = n - a - b;
-            s += fact[n] / (fact[a] * fact[b] * fact[c]) * px[a] * py[b] * pz[c] * f(a, b, c);
+#pragma unroll
+    for (int a = N; a >= 0; --a)
+#pragma unroll
+        for (int b = N - a; b >= 0; --b) {
+            const int c = N - a - b;
+            s += fact[N] / (fact[a] * fact[b] * fact[c]) * px[a] * py[b] * pz[c] * f(a, b, c);
         }
     return s;
 }
 
-__global__ void ghost_values_kernel(int64_t n_ghost, const int32_t* __restrict__ gijk, double h,
-                                    const double* __restrict__ M, double* __restrict__ vg) {
-    const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g >= n_ghost) return;
-    const double x = gijk[3 * g] * h, y = gijk[3 * g + 1] * h, z = gijk[3 * g + 2] * h;
+// the potential of the moments M outside the charge, to fourth order
+__device__ inline double multipole_potential(double x, double y, double z, const double* M) {
+    const double px[5] = {1, x, x * x, x * x * x, x * x * x * x};
+    const double py[5] = {1, y, y * y, y * y * y, y * y * y * y};
+    const double pz[5] = {1, z, z * z, z * z * z, z * z * z * z};
     const double r2 = x * x + y * y + z * z;
     const double r = sqrt(r2);
-    auto plain = [&](int a, int b, int c) { return mom(M, a, b, c); };
-    auto tr1 = [&](int a, int b, int c) { return mom(M, a + 2, b, c) + mom(M, a, b + 2, c) + mom(M, a, b, c + 2); };
-    const double T0 = mom(M, 0, 0, 0);
-    const double T1 = contract(1, x, y, z, plain);
-    const double T2 = contract(2, x, y, z, plain);
-    const double T3 = contract(3, x, y, z, plain);
-    const double T4 = contract(4, x, y, z, plain);
+    auto plain = [&](int a, int b, int c) { return M[mom_index(a, b, c)]; };
+    auto tr1 = [&](int a, int b, int c) {
+        return M[mom_index(a + 2, b, c)] + M[mom_index(a, b + 2, c)] + M[mom_index(a, b, c + 2)];
+    };
+    const double T0 = plain(0, 0, 0);
+    const double T1 = contract<1>(px, py, pz, plain);
+    const double T2 = contract<2>(px, py, pz, plain);
+    const double T3 = contract<3>(px, py, pz, plain);
+    const double T4 = contract<4>(px, py, pz, plain);
     const double S0 = tr1(0, 0, 0);
-    const double S1 = contract(1, x, y, z, tr1);
-    const double S2 = contract(2, x, y, z, tr1);
-    const double Q0 = mom(M, 4, 0, 0) + mom(M, 0, 4, 0) + mom(M, 0, 0, 4) +
-                      2.0 * (mom(M, 2, 2, 0) + mom(M, 2, 0, 2) + mom(M, 0, 2, 2));
+    const double S1 = contract<1>(px, py, pz, tr1);
+    const double S2 = contract<2>(px, py, pz, tr1);
+    const double Q0 = plain(4, 0, 0) + plain(0, 4, 0) + plain(0, 0, 4) +
+                      2.0 * (plain(2, 2, 0) + plain(2, 0, 2) + plain(0, 2, 2));
     const double ir = 1.0 / r, ir2 = ir * ir;
     double v = T0 * ir;
     v += T1 * ir * ir2;
     v += (3.0 * T2 - r2 * S0) * 0.5 * ir * ir2 * ir2;
     v += (5.0 * T3 - 3.0 * r2 * S1) * 0.5 * ir * ir2 * ir2 * ir2;
     v += (35.0 * T4 - 30.0 * r2 * S2 + 3.0 * r2 * r2 * Q0) * 0.125 * ir * ir2 * ir2 * ir2 * ir2;
-    vg[g] = v;
+    return v;
 }
 
-// b[row] = 4 pi rho[row] + sum_{ghosts g of row} (c_|k| / h^2) V(g); 0 on padding
-__global__ void poisson_rhs_kernel(int64_t n_rows, const uint8_t* __restrict__ inside, const double* __restrict__ rho,
-                                   const int32_t* __restrict__ goff, const int32_t* __restrict__ gk,
-                                   const double* __restrict__ vg, const double* __restrict__ ck, double* __restrict__ b) {
-    const int64_t row = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (row >= n_rows) return;
-    if (!inside[row]) {
-        b[row] = 0.0;
-        return;
+struct RhsCoef {
+    double c[7];    // c_|k| / h^2
+};
+
+// b[row] = 4 pi rho[row] + sum over the stencil points g outside the sphere of
+// (c_|k| / h^2) V(g); 0 on padding.  Few rows have such points and those up to 36:
+// per axis a wave lists its rows' outside points, evaluates the list 64 at a time
+// and each lane adds its own in order.  (They were listed for every row on the
+// host at the first use of a Hamiltonian, 35 ms at 2.5 nm, and kept in memory.)
+__global__ void __launch_bounds__(256) poisson_rhs_kernel(int64_t n_rows, const int32_t* __restrict__ row_ijk4, int n_r,
+                                                          int64_t thr, double h, const double* __restrict__ rho,
+                                                          RhsCoef ck, const double* __restrict__ M,
+                                                          double* __restrict__ b) {
+    constexpr int kSide = 2 * kHalf;
+    __shared__ double val[4][64 * kSide];
+    __shared__ uint16_t code[4][64 * kSide];
+    __shared__ int pos[4][3][64];
+    __shared__ double sm[kNMom];
+    if (threadIdx.x < kNMom) sm[threadIdx.x] = M[threadIdx.x];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t row = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    const bool live = row < n_rows;
+    const int4 at = live ? reinterpret_cast<const int4*>(row_ijk4)[row] : int4{0, 0, 0, 0};
+    const bool in = live && at.w != 0;
+    pos[wave][0][lane] = at.x;
+    pos[wave][1][lane] = at.y;
+    pos[wave][2][lane] = at.z;
+    __syncthreads();
+    double s = in ? 4.0 * kPi * rho[row] : 0.0;
+    auto inside = [&](int64_t i, int64_t j, int64_t k) {
+        return i >= -n_r && i <= n_r && j >= -n_r && j <= n_r && k >= -n_r && k <= n_r && i * i + j * j + k * k <= thr;
+    };
+    for (int axis = 0; axis < 3; ++axis) {
+        unsigned mask = 0;
+        if (in)
+            for (int q = 0; q < kSide; ++q) {
+                const int st = q < kHalf ? q - kHalf : q - kHalf + 1;
+                if (!inside(at.x + (axis == 0 ? st : 0), at.y + (axis == 1 ? st : 0), at.z + (axis == 2 ? st : 0)))
+                    mask |= 1u << q;
+            }
+        const int cnt = __popc(mask);
+        int end = cnt;
+        for (int off = 1; off < 64; off *= 2) {
+            const int o = __shfl_up(end, off, 64);
+            if (lane >= off) end += o;
+        }
+        const int total = __shfl(end, 63, 64);
+        if (total == 0) continue;
+        int first = end - cnt;
+        for (unsigned m = mask; m; m &= m - 1) code[wave][first++] = uint16_t(lane * 16 + __ffs(m) - 1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int i = lane; i < total; i += 64) {
+            const int c = code[wave][i], o = c >> 4, q = c & 15;
+            const int st = q < kHalf ? q - kHalf : q - kHalf + 1;
+            const double x = (pos[wave][0][o] + (axis == 0 ? st : 0)) * h, y = (pos[wave][1][o] + (axis == 1 ? st : 0)) * h,
+                         z = (pos[wave][2][o] + (axis == 2 ? st : 0)) * h;
+            val[wave][i] = multipole_potential(x, y, z, sm);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        first = end - cnt;
+        for (unsigned m = mask; m; m &= m - 1) {
+            const int q = __ffs(m) - 1;
+            s += ck.c[q < kHalf ? kHalf - q : q - kHalf + 1] * val[wave][first++];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    double s = 4.0 * kPi * rho[row];
-    for (int g = goff[row]; g < goff[row + 1]; ++g) s += ck[gk[g]] * vg[g];
-    b[row] = s;
+    if (live) b[row] = s;
 }
 
 // v = a x + b y + c z (any of y, z may be null)
@@ -335,47 +387,6 @@ static double sum_host(chf_ctx* ctx, int nparts, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// exterior stencil points of the Poisson problem (host build, first use)
-// ---------------------------------------------------------------------------
-static void build_ghosts(chf_ham* H, hipStream_t s) {
-    if (H->n_ghost >= 0) return;
-    const HostGrid& g = H->grid;
-    std::vector<int32_t> off(size_t(g.n_rows) + 1, 0), kk, ijk;
-    std::vector<std::vector<int32_t>> per_row_k(0);
-    // rows in ascending order; ghosts of a row in neighbour-column order
-    std::vector<int64_t> rank_rows(g.row_of_rank);
-    std::vector<int32_t> cnt(size_t(g.n_rows), 0);
-    std::vector<std::pair<int64_t, std::array<int32_t, 4>>> items;
-    for (int64_t p = 0; p < g.n; ++p) {
-        const int i = g.ijk[size_t(3 * p)], j = g.ijk[size_t(3 * p + 1)], k = g.ijk[size_t(3 * p + 2)];
-        const int64_t row = g.row_of_rank[size_t(p)];
-        for (int axis = 0; axis < 3; ++axis)
-            for (int st = -kHalf; st <= kHalf; ++st) {
-                if (st == 0) continue;
-                const int a = i + (axis == 0 ? st : 0), b = j + (axis == 1 ? st : 0), c = k + (axis == 2 ? st : 0);
-                if (g.inside(a, b, c)) continue;
-                items.push_back({row, {std::abs(st), a, b, c}});
-            }
-    }
-    std::stable_sort(items.begin(), items.end(), [](const auto& x, const auto& y) { return x.first < y.first; });
-    kk.reserve(items.size());
-    ijk.reserve(items.size() * 3);
-    for (auto& it : items) {
-        off[size_t(it.first) + 1]++;
-        kk.push_back(it.second[0]);
-        ijk.push_back(it.second[1]);
-        ijk.push_back(it.second[2]);
-        ijk.push_back(it.second[3]);
-    }
-    for (int64_t r = 0; r < g.n_rows; ++r) off[size_t(r) + 1] += off[size_t(r)];
-    upload(H->ghost_owner, off, s);
-    upload(H->ghost_k, kk, s);
-    upload(H->ghost_ijk, ijk, s);
-    H->n_ghost = int64_t(kk.size());
-    HIP_CHECK(hipStreamSynchronize(s));
-}
-
-// ---------------------------------------------------------------------------
 // Conjugate gradients for -L v = b on the Hilbert layout, two kernels per
 // iteration with every scalar on the device.
 //
@@ -389,9 +400,9 @@ static void build_ghosts(chf_ham* H, hipStream_t s) {
 // trips per iteration, with the stencil on 1 of the 16 lanes of the
 // multi-vector tile kernel, took 113 us at 2.5 nm (51 of them the stencil); a
 // solve from zero went from 44.4 to 7.8 ms.  Folding p's update into the
-// stencil's loads saves a pass and a kernel for a second read of the halos.  The partial sums of a launch are reduced by
-// every workgroup of the next one, in the same order, so all take the same
-// decision; once the residual is small enough the remaining launches of a
+// stencil's loads saves a pass and a kernel for a second read of the halos.  The
+// partial sums of a launch are reduced by every workgroup of the next one, in
+// the same order, so all take the same decision; once the residual is small enough the remaining launches of a
 // batch return at once, so the iterates are those of a loop that tests after
 // every iteration.
 // ---------------------------------------------------------------------------
@@ -666,18 +677,15 @@ static CgResult cg_hilbert(chf_ham* H, chf_ctx* ctx, double* b, double* x, doubl
 
 // Hartree potential into vh (warm start from its contents); returns CG iterations.
 int hartree_solve(chf_ham* H, chf_ctx* ctx, const double* rho, double* vh, double rtol, int max_iter, hipStream_t s) {
-    build_ghosts(H, s);
     const int64_t n = H->grid.n_rows;
-    // workspace: b, r, p, Ap (n each) + ghost values + moments
-    const size_t need = size_t(n) * 4 * sizeof(double) + size_t(std::max<int64_t>(1, H->n_ghost)) * sizeof(double) + 4096;
+    // workspace: b, r, p, Ap (n each) + moments
+    const size_t need = size_t(n) * 4 * sizeof(double) + 4096;
     ctx->vec.ensure(need);
     double* b = ctx->vec.as<double>();
     double* r = b + n;
     double* pv = r + n;
     double* ap = pv + n;
-    double* vg = ap + n;
-    double* M = vg + std::max<int64_t>(1, H->n_ghost);
-    double* ck = M + 64;
+    double* M = ap + n;
     ctx->red.ensure(size_t(1024) * kNMom * sizeof(double));
     const double h = H->h;
     // moments
@@ -686,16 +694,10 @@ int hartree_solve(chf_ham* H, chf_ctx* ctx, const double* rho, double* vh, doubl
     LAUNCH_CHECK();
     moments_reduce_kernel<<<kNMom, 256, 0, s>>>(mb, ctx->red.as<double>(), h * h * h, M);
     LAUNCH_CHECK();
-    if (H->n_ghost > 0) {
-        ghost_values_kernel<<<nblk(H->n_ghost), 256, 0, s>>>(H->n_ghost, H->ghost_ijk.as<int32_t>(), h, M, vg);
-        LAUNCH_CHECK();
-    }
-    // c_k / h^2 for |k| = 1..6 (index by |k|): Laplacian weights = -2 coef
-    double ckh[8] = {0};
-    for (int k = 1; k <= kHalf; ++k) ckh[k] = -2.0 * H->coef[k];
-    HIP_CHECK(hipMemcpyAsync(ck, ckh, sizeof(ckh), hipMemcpyHostToDevice, s));
-    poisson_rhs_kernel<<<nblk(n), 256, 0, s>>>(n, H->row_inside.as<uint8_t>(), rho, H->ghost_owner.as<int32_t>(),
-                                              H->ghost_k.as<int32_t>(), vg, ck, b);
+    // c_k / h^2 for |k| = 1..6: Laplacian weights = -2 coef
+    RhsCoef ck{};
+    for (int k = 1; k <= kHalf; ++k) ck.c[k] = -2.0 * H->coef[k];
+    poisson_rhs_kernel<<<nblk(n), 256, 0, s>>>(n, H->row_ijk4.as<int32_t>(), H->grid.n_r, H->grid.thr, h, rho, ck, M, b);
     LAUNCH_CHECK();
     double rr, thr;
     int it = 0;
