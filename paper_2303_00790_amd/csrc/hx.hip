@@ -693,7 +693,7 @@ __device__ inline V bload16(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned so
 
 template <class T, int PB, int SLOTS>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SLOTS <= kFewSlots ? 4 : 2)))
-hx_tile_kernel(int n_blocks, int n_chunks, const int32_t* __restrict__ bnb, const uint64_t* __restrict__ bmask,
+hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict__ bnb, const uint64_t* __restrict__ bmask,
                const T* __restrict__ veff, const int32_t* __restrict__ rg_off, const int32_t* __restrict__ rg_slot,
                const T* __restrict__ rg_beta, const int32_t* __restrict__ blk_atom_off,
                const int32_t* __restrict__ blk_atoms, const T* __restrict__ C, int nvec, const T* __restrict__ X,
@@ -707,18 +707,15 @@ hx_tile_kernel(int n_blocks, int n_chunks, const int32_t* __restrict__ bnb, cons
     char* const lds_kb = lds + SLOTS * kSlotBytes;
     V (*plane)[8] = reinterpret_cast<V (*)[8]>(lds + SLOTS * kSlotBytes + kKbBytes);
 
-    // XCD-aware tile order: workgroup ids are dealt round-robin to the 8
-    // XCDs; each XCD takes a contiguous run of the tile sequence, a block's
-    // chunks one after the other: they share its tables and coefficients, and
-    // together they cover whole rows, which spreads the requests over all L2
-    // channels.  (One chunk of all blocks after the other shares more halos but
-    // reads 128 bytes of every row: 2494 -> 2672 us at 5 nm, 256 FP32 vectors.)
-    const unsigned ntiles = unsigned(n_blocks) * unsigned(n_chunks);
-    const unsigned per_xcd = (ntiles + 7) / 8;
-    const unsigned tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (tile >= ntiles) return;
-    const int blk = int(tile / unsigned(n_chunks));
-    const int chunk = int(tile % unsigned(n_chunks));
+    // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs; an
+    // XCD takes a contiguous run of blocks, `group` chunks of all of them after the
+    // other: fewer chunks at a time leave more neighbouring blocks, whose halos
+    // overlap, in its L2, more share a block's tables and whole cache lines.
+    const unsigned per_xcd = (unsigned(n_blocks) + 7) / 8;
+    const unsigned id = blockIdx.x / 8, first = id / (per_xcd * group) * group;
+    const unsigned wide = min(unsigned(group), unsigned(n_chunks) - first), rest = id - per_xcd * first;
+    const int blk = int(blockIdx.x % 8 * per_xcd + rest / wide), chunk = int(first + rest % wide);
+    if (rest >= per_xcd * wide || blk >= n_blocks) return;
 
     const int t = threadIdx.x;
     const int p = t & 7;
@@ -1025,10 +1022,16 @@ template <class T, int PB, int SLOTS>
 static void launch_tile(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec,
                         const T* C, const StepCoef<T>& coef, hipStream_t s) {
     const int n_chunks = (nvec + 8 * Wide<T>::N - 1) / (8 * Wide<T>::N);
-    const int64_t nt = H->grid.n_blocks * int64_t(n_chunks);
+    // Chunks at a time: 2 where rows are whole cache lines, all where chunks share
+    // lines.  us per launch for 1, 2, 4, all: 5 nm 256 FP32 2358, 2360, 2454, 2494;
+    // 5 nm 128 FP64 2682, 2561, 2619, 2632; 3 nm 256 FP64 1478, 1478, 1536, 1596;
+    // 1.1 nm 128 FP64 102, 103, 108, 110; but 2 nm 97 FP64 429, 403, 395, 380.
+    const auto lines = [](const void* q, int64_t ld) { return uintptr_t(q) % 128 == 0 && ld * sizeof(T) % 128 == 0; };
+    const int group = lines(X, ldx) && lines(Y, ldy) && (!Z || lines(Z, ldz)) ? 2 : n_chunks;
+    const int64_t nt = (H->grid.n_blocks + 7) / 8 * 8 * n_chunks;
     const T* rg_beta = std::is_same<T, double>::value ? H->rg_beta64.as<T>() : H->rg_beta32.as<T>();
-    hx_tile_kernel<T, PB, SLOTS><<<dim3(unsigned(((nt + 7) / 8) * 8)), dim3(512), 0, s>>>(
-        int(H->grid.n_blocks), n_chunks, H->block_nbr.as<int32_t>(), H->block_mask.as<uint64_t>(), veff_of<T>(H),
+    hx_tile_kernel<T, PB, SLOTS><<<dim3(unsigned(nt)), dim3(512), 0, s>>>(
+        int(H->grid.n_blocks), n_chunks, group, H->block_nbr.as<int32_t>(), H->block_mask.as<uint64_t>(), veff_of<T>(H),
         H->rg_off.as<int32_t>(), H->rg_slot.as<int32_t>(), rg_beta, H->blk_atom_off.as<int32_t>(),
         H->blk_atoms.as<int32_t>(), C, nvec, X, ldx, Y, ldy, Z, ldz, coef);
     LAUNCH_CHECK();

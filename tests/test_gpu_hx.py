@@ -376,3 +376,26 @@ def test_filter_of_one_row_piece(system, dtype, tol, m):
     assert relerr(from_rows(s, Xg, m), ref) < tol
     s["Hg"].filter(Xh, torch.empty_like(Xg[:, :m // 2].contiguous()), 6, a, b, a0)
     assert torch.equal(Xg, Xh)
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-12), (torch.float32, 2e-6)])
+@pytest.mark.parametrize("radius", [2.0, 9.0])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 5])
+def test_tile_order_covers_every_chunk(dtype, tol, radius, chunks):
+    # blocks of whole cache lines take two chunks of all of an XCD's blocks at a
+    # time: one chunk, an odd last one, and fewer blocks than XCDs
+    from paper_2303_00790_amd import binding as B
+    m = chunks * (32 if dtype == torch.float32 else 16)
+    pos, spc = np.array([[0.1, -0.2, 0.3], [1.5, 0.4, -0.8]]), np.zeros(2, np.int32)
+    pp = OH.PseudoParams(h_s=2.0, h_p=0.5)
+    g = G.build_grid(radius, H_SPACING)
+    Ho = OH.build_hamiltonian(g, pos, spc, pp)
+    Hg = B.Hamiltonian(pos, spc, pp, H_SPACING, radius, B.ORDER_HILBERT)
+    rows = torch.from_numpy(g.row_of_rank).cuda()
+    X = random_block(g.n, m, 3200 + m)
+    Xg = torch.zeros((Hg.n_rows, m), dtype=dtype, device="cuda")
+    Xg[rows] = torch.from_numpy(X).to(device="cuda", dtype=dtype)
+    Yg = torch.full_like(Xg, float("nan"))
+    Hg.apply(Xg, Yg)
+    assert relerr(Yg[rows].double().cpu().numpy(), Ho.apply(X)) < tol
+    assert not bool(torch.isnan(Yg).any())
