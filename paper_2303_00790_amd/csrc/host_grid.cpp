@@ -306,4 +306,32 @@ void build_block_atoms(const HostGrid& g, HostProj& P) {
     }
 }
 
+void list_row_groups(const HostProj& P, int64_t n_groups, int rows, int step, int scale, int64_t (*first_row)(int64_t),
+                     std::vector<int32_t>& off, std::vector<int32_t>& len, std::vector<int32_t>& slot) {
+    std::vector<uint64_t> mask(static_cast<size_t>(n_groups));
+    off.assign(size_t(n_groups) + 1, 0);
+    len.resize(size_t(n_groups));
+#pragma omp parallel for schedule(static)
+    for (int64_t g = 0; g < n_groups; ++g) {
+        const int64_t row = first_row(g);
+        uint64_t m = 0;
+        for (int64_t e = P.ent_off[size_t(row)]; e < P.ent_off[size_t(row + rows)]; ++e)
+            m |= uint64_t(1) << P.ent_slot[size_t(e)];
+        mask[size_t(g)] = m;
+        len[size_t(g)] = __builtin_popcountll(m);
+    }
+    int64_t n = 0;
+    for (int64_t g = 0; g < n_groups; ++g) {
+        n += (len[size_t(g)] + step - 1) / step * step;
+        CHF_REQUIRE(n < (int64_t(1) << 31), "ham_build: more than 2^31 row-group entries");
+        off[size_t(g) + 1] = int32_t(n);
+    }
+    slot.assign(size_t(n), 0);
+#pragma omp parallel for schedule(static)
+    for (int64_t g = 0; g < n_groups; ++g) {
+        int32_t* at = slot.data() + off[size_t(g)];
+        for (uint64_t m = mask[size_t(g)]; m; m &= m - 1) *at++ = __builtin_ctzll(m) * scale;
+    }
+}
+
 }  // namespace chf

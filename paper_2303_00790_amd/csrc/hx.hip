@@ -983,19 +983,11 @@ void build_row_groups(chf_ham* H, hipStream_t s) {
     const HostProj& P = H->proj;
     if (H->grid.ordering != CHF_ORDER_HILBERT || P.n_proj == 0 || P.max_block_atoms > kMaxBlockAtoms) return;
     const int64_t n_rg = H->grid.n_blocks * kGroups;
-    std::vector<int32_t> off(size_t(n_rg) + 1, 0), len(size_t(n_rg), 0), slot;
-    for (int64_t rg = 0; rg < n_rg; ++rg) {
-        // (block, x-line pair, plane): the planes of a pair are consecutive
-        const int64_t row = rg / kGroups * kBlockPts + rg % 8 * 64 + rg / 8 % 4 * kRowGroup;
-        uint64_t m = 0;
-        for (int64_t e = P.ent_off[size_t(row)]; e < P.ent_off[size_t(row + kRowGroup)]; ++e)
-            m |= uint64_t(1) << P.ent_slot[size_t(e)];
-        len[size_t(rg)] = __builtin_popcountll(m);
-        for (; m; m &= m - 1) slot.push_back(__builtin_ctzll(m) * kSlotBytes);
-        while (slot.size() % kKbStep) slot.push_back(0);
-        CHF_REQUIRE(slot.size() < (size_t(1) << 31), "ham_build: more than 2^31 row-group entries");
-        off[size_t(rg) + 1] = int32_t(slot.size());
-    }
+    std::vector<int32_t> off, len, slot;
+    // (block, x-line pair, plane): the planes of a pair are consecutive
+    list_row_groups(P, n_rg, kRowGroup, kKbStep, kSlotBytes, [](int64_t rg) {
+        return rg / kGroups * kBlockPts + rg % 8 * 64 + rg / 8 % 4 * kRowGroup;
+    }, off, len, slot);
     DevBuf dlen;
     upload(H->rg_off, off, s);
     upload(H->rg_slot, slot, s);

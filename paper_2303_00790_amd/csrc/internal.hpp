@@ -146,6 +146,11 @@ struct HostProj {
 };
 
 void build_block_atoms(const HostGrid& g, HostProj& P);
+// per group of `rows` consecutive rows from first_row(group) on, the atom slots that
+// touch it times `scale`, ascending: offsets, counts, and the lists padded with 0
+// to a multiple of `step`
+void list_row_groups(const HostProj& P, int64_t n_groups, int rows, int step, int scale, int64_t (*first_row)(int64_t),
+                     std::vector<int32_t>& off, std::vector<int32_t>& len, std::vector<int32_t>& slot);
 
 void build_projectors(const HostGrid& g, const chf_atoms& atoms, const chf_pp& pp, HostProj& out);
 
