@@ -641,16 +641,15 @@ __global__ void __launch_bounds__(64 * kLanes) hx_tiled_kernel(int64_t n_blocks,
 // workgroup within half of the 160 KB of LDS and its threads within 128
 // registers: two workgroups run on a CU, one marching while the other loads.
 //
-// What bounds it: the chain of dependent loads at the start of a tile and the
-// memory latency of a plane, and the traffic behind L2 (15.1 GB per 5 nm FP32
-// launch in 2.49 ms = 6.0 TB/s, three times the two blocks read and the one
-// written, for the halos).  One 1024-thread workgroup per CU, whose KB term was
-// applied entry by entry on the VALU, took 21.9 us per tile at every size,
-// 7.8 of them before the first plane; now 16.3.  us per launch, before -> now:
-// 5 nm, 256 FP32 vectors 3337 -> 2494; 8 nm 10815 -> 8112; 5 nm, 128 FP64
-// 3389 -> 2635; 3 nm, 128 FP64 1011 -> 783; 2.5 nm, 256 FP32 674 -> 509;
-// 1.1 nm, 128 FP64 154 -> 110; 2 nm, 97 FP64 (rows on 8 bytes, PB = 8) 470 -> 380,
-// 474 with every 16 bytes in two pieces of 8.
+// What bounds it: the traffic behind the L2 (14.3 GB per 5 nm FP32 launch in 2.36
+// ms = 6.1 TB/s, twice the two blocks read and the one written, for the halos; the
+// same rate for FP64) and the latency of a plane.  One 1024-thread workgroup per CU,
+// whose KB term was applied entry by entry on the VALU, took 21.9 us per tile at
+// every size, 7.8 of them before the first plane; now 15.4.  us per launch,
+// before -> now: 5 nm, 256 FP32 vectors 3337 -> 2360; 5 nm, 128 FP64 3389 -> 2561;
+// 3 nm, 128 FP64 1011 -> 751; 2.5 nm, 256 FP32 674 -> 476; 1.1 nm, 128 FP64
+// 154 -> 102; 2 nm, 97 FP64 (rows on 8 bytes, PB = 8) 470 -> 380, 474 with every 16
+// bytes in two pieces of 8.
 // ---------------------------------------------------------------------------
 constexpr int kSlotBytes = 512;      // staged coefficients of an atom: 4 channels x 128 bytes
 constexpr int kRowGroup = 16;        // rows of a KB weight matrix
@@ -1253,12 +1252,6 @@ bool hx_dot_ok(const chf_ham* H) {
     return H->grid.ordering == CHF_ORDER_HILBERT && H->proj.max_block_atoms <= kMaxBlockAtoms;
 }
 
-int hx_dot(chf_ham* H, const double* x, double* y, double* part, hipStream_t s) {
-    H->kb_coef.ensure(kb_coef_bytes(H, 1, sizeof(double)));
-    launch_kb_gather<double>(H, x, 1, 1, H->kb_coef.as<double>(), s);
-    return launch_narrow<double>(H, x, 1, y, 1, nullptr, 0, 1, H->kb_coef.as<double>(), 1.0, 0.0, 0.0, part, s);
-}
-
 // ---------------------------------------------------------------------------
 // optional per-kernel timing: HIP events recorded on the launch stream
 // around every H X and KB-gather launch while enabled
@@ -1307,6 +1300,17 @@ static void timed(int which, hipStream_t s, F&& launch) {
     HIP_CHECK(hipEventRecord(b, s));
     std::lock_guard<std::mutex> lk(g_timer_mu);
     g_timer.spans[which].emplace_back(a, b);
+}
+
+void timed_hx(hipStream_t s, const std::function<void()>& launch) { timed(0, s, launch); }
+
+int hx_dot(chf_ham* H, const double* x, double* y, double* part, hipStream_t s) {
+    H->kb_coef.ensure(kb_coef_bytes(H, 1, sizeof(double)));
+    double* C = H->kb_coef.as<double>();
+    if (H->proj.n_proj > 0) timed(1, s, [&] { launch_kb_gather<double>(H, x, 1, 1, C, s); });
+    int n = 0;
+    timed(0, s, [&] { n = launch_narrow<double>(H, x, 1, y, 1, nullptr, 0, 1, C, 1.0, 0.0, 0.0, part, s); });
+    return n;
 }
 
 // ---------------------------------------------------------------------------

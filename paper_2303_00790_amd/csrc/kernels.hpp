@@ -1,5 +1,7 @@
 // Launchers shared between the library's translation units.
 #pragma once
+#include <functional>
+
 #include "internal.hpp"
 
 namespace chf {
@@ -25,6 +27,8 @@ void hx_step(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z,
 // returns their number.  hx_dot_ok: whether the handle has the tables for it.
 bool hx_dot_ok(const chf_ham* H);
 int hx_dot(chf_ham* H, const double* x, double* y, double* part, hipStream_t s);
+// a launch counted as an H X launch by the kernel timer
+void timed_hx(hipStream_t s, const std::function<void()>& launch);
 
 // Degree-m scaled Chebyshev filter in place over X and the work block W
 // (column blocks of min(nvec, ldw) vectors)

@@ -638,8 +638,10 @@ static CgResult cg_hilbert(chf_ham* H, chf_ctx* ctx, double* b, double* x, doubl
     const int32_t* bnb = H->block_nbr.as<int32_t>();
     const uint64_t* bmask = H->block_mask.as<uint64_t>();
     cg_reset_kernel<<<1, 1, 0, s>>>(st);
-    cg_stencil_kernel<true><<<grid, 512, 0, s>>>(nblk, per, bnb, bmask, k, x, nullptr, nullptr, b, r, 0, rtol, nullptr, 0,
-                                                 nullptr, 0, part_rr[0], part_bb, nullptr);
+    timed_hx(s, [&] {
+        cg_stencil_kernel<true><<<grid, 512, 0, s>>>(nblk, per, bnb, bmask, k, x, nullptr, nullptr, b, r, 0, rtol, nullptr,
+                                                     0, nullptr, 0, part_rr[0], part_bb, nullptr);
+    });
     LAUNCH_CHECK();
     // partials of r.r: those of the start for iteration 0, then cg_update's
     int it = 0, batch = 0;
@@ -650,9 +652,11 @@ static CgResult cg_hilbert(chf_ham* H, chf_ctx* ctx, double* b, double* x, doubl
             double* p = it & 1 ? b : p0;
             const double* po = it & 1 ? p0 : b;
             const int n_rr = it == 0 ? int(grid) : n_upd;
-            cg_stencil_kernel<false><<<grid, 512, 0, s>>>(nblk, per, bnb, bmask, k, r, po, p, nullptr, ap, it, rtol,
-                                                          part_rr[it & 1], n_rr, part_bb, int(grid), part_pap, nullptr,
-                                                          st);
+            timed_hx(s, [&] {
+                cg_stencil_kernel<false><<<grid, 512, 0, s>>>(nblk, per, bnb, bmask, k, r, po, p, nullptr, ap, it, rtol,
+                                                              part_rr[it & 1], n_rr, part_bb, int(grid), part_pap,
+                                                              nullptr, st);
+            });
             cg_update_kernel<<<n_upd, 256, 0, s>>>(n, it, p, ap, x, r, part_pap, int(grid), part_rr[(it + 1) & 1], st);
             LAUNCH_CHECK();
         }
