@@ -231,8 +231,8 @@ int lanczos_bound(chf_ham* ham, chf_ctx* ctx, const double* v0_dev, int k, doubl
 /* S = A^T B for row-major blocks A [n_rows][lda] (m columns) and B [n_rows][ldb]
  * (n columns): products of row slices (at most 8192 rows each, whatever the
  * width, so that no sum in the block precision runs over more rows) accumulated
- * on MFMA in the block precision (rocBLAS), the slice partials added in FP64 in
- * slice order.  S_dev is FP64 row-major [m][lds].  With A == B and m == n the
+ * on MFMA in the block precision, the slice partials added in FP64 in a fixed
+ * order.  S_dev is FP64 row-major [m][lds].  With A == B and m == n the
  * upper triangle is summed and mirrored, so S is exactly symmetric. */
 int gram(chf_ctx* ctx, chf_dtype dtype, const void* A_dev, int64_t lda, const void* B_dev,
          int64_t ldb, int64_t n_rows, int m, int n, double* S_dev, int64_t lds, void* stream);
