@@ -211,9 +211,10 @@ __global__ void diag_copy_kernel(int m, const double* __restrict__ S, double* __
 }
 
 // out[0] = min_i R_ii^2 / d_i (the squared sine between column i and the span
-// of the columns before it), out[1] = its index; one workgroup of 256
+// of the columns before it), out[1] = its index, out[2] = info; one workgroup of 256
 __global__ void __launch_bounds__(256) pivot_ratio_kernel(int m, const double* __restrict__ R,
-                                                          const double* __restrict__ d, double* __restrict__ out) {
+                                                          const double* __restrict__ d, const int* __restrict__ info,
+                                                          double* __restrict__ out) {
     __shared__ double v[256];
     __shared__ int at[256];
     double best = 2.0;
@@ -237,6 +238,7 @@ __global__ void __launch_bounds__(256) pivot_ratio_kernel(int m, const double* _
     if (threadIdx.x == 0) {
         out[0] = v[0];
         out[1] = double(at[0]);
+        out[2] = double(*info);
     }
 }
 
@@ -279,14 +281,13 @@ static int cholqr_once(chf_ctx* ctx, T* X, int64_t ldx, int64_t n_rows, int m, d
     LAUNCH_CHECK();
     void* work = diag + (m + 1) / 2 * 2;
     cholesky<T>(S, m, work, dinfo, s);
-    double piv[2] = {1.0, 0.0};
+    double piv[3] = {1.0, 0.0, 0.0};
     double* pr = reinterpret_cast<double*>(ctx->info.p) + 2;
-    pivot_ratio_kernel<<<1, 256, 0, s>>>(m, S, diag, pr);
+    pivot_ratio_kernel<<<1, 256, 0, s>>>(m, S, diag, dinfo, pr);
     LAUNCH_CHECK();
-    HIP_CHECK(hipMemcpyAsync(piv, pr, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    int info = 0;
-    HIP_CHECK(hipMemcpyAsync(&info, dinfo, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_CHECK(hipMemcpyAsync(piv, pr, sizeof(piv), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
+    const int info = int(piv[2]);
     if (info != 0) return info;
     const double thr = (f64 || gram64) ? kPivotRelF64 : kPivotRelF32;
     if (shift_rel == 0 && !(piv[0] >= thr)) return int(piv[1]) + 1;

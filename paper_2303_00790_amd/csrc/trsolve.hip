@@ -90,8 +90,9 @@ __device__ inline double from_lane(double v, int lane) {
 
 // The upper triangular kTriBlock square in M (rows of kTriPitch) by its inverse,
 // by 512 threads: 16 x 16 blocks by back substitution, one column per thread,
-// then doubled with Z12 = -Z11 (R12 Z22) in place.
-__device__ inline void invert_upper(double* M) {
+// then doubled with Z12 = -Z11 (R12 Z22) in place, up to the w columns that are not
+// those of the identity.
+__device__ inline void invert_upper(double* M, int w) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     double z[16];
     double* const D = M + (t >> 4) * 16 * (kTriPitch + 1);
@@ -108,7 +109,7 @@ __device__ inline void invert_upper(double* M) {
     if (t < kTriBlock)
 #pragma unroll
         for (int i = 0; i < 16; ++i) D[i * kTriPitch + (t & 15)] = z[i];
-    for (int s = 16; s < kTriBlock; s *= 2) {
+    for (int s = 16; s < w; s *= 2) {
         const int q = s / 16, tiles = kTriBlock / (2 * s) * q * q;
         // side 0: W = R12 Z22 over R12;  side 1: Z12 = -Z11 W over W
         for (int side = 0; side < 2; ++side) {
@@ -159,6 +160,7 @@ __global__ void __launch_bounds__(512) chol_diag_kernel(int m, int b0, double* _
     __shared__ double M[kTriBlock * kTriPitch];
     __shared__ double dinv[16];
     const int t = threadIdx.x, lane = t & 63, l = lane & 15, wave = t >> 6;
+    const int w = min(kTriBlock, m - b0);
     for (int idx = t; idx < kTriBlock * kTriBlock; idx += 512) {
         const int k = idx % kTriBlock, j = idx / kTriBlock;
         double v = k == j ? 1.0 : 0.0;
@@ -166,7 +168,6 @@ __global__ void __launch_bounds__(512) chol_diag_kernel(int m, int b0, double* _
         M[k * kTriPitch + j] = v;
     }
     __syncthreads();
-    const int w = min(kTriBlock, m - b0);
     for (int c0 = 0; c0 < w; c0 += 16) {
         if (wave == 0) {
             double a[16];
@@ -237,8 +238,10 @@ __global__ void __launch_bounds__(512) chol_diag_kernel(int m, int b0, double* _
         else if (k > j) M[k * kTriPitch + j] = 0.0;
     }
     __syncthreads();
-    invert_upper(M);
-    for (int idx = t; idx < kTriBlock * kTriBlock; idx += 512) {
+    invert_upper(M, w);
+    // (the 16-column tiles that hold a column of R; no other is read)
+    const int n = (w + 15) / 16 * 16 * kTriBlock;
+    for (int idx = t; idx < n; idx += 512) {
         int k, j;
         Packed<T>::where(idx, kTriBlock / Packed<T>::KG, &k, &j);
         Z[idx] = k <= j ? T(M[k * kTriPitch + j]) : T(0);
