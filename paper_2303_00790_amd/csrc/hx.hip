@@ -648,8 +648,9 @@ __global__ void __launch_bounds__(64 * kLanes) hx_tiled_kernel(int64_t n_blocks,
 // every size, 7.8 of them before the first plane; now 15.4.  us per launch,
 // before -> now: 5 nm, 256 FP32 vectors 3337 -> 2360; 5 nm, 128 FP64 3389 -> 2561;
 // 3 nm, 128 FP64 1011 -> 751; 2.5 nm, 256 FP32 674 -> 476; 1.1 nm, 128 FP64
-// 154 -> 102; 2 nm, 97 FP64 (rows on 8 bytes, PB = 8) 470 -> 380, 474 with every 16
-// bytes in two pieces of 8.
+// 154 -> 102; 2 nm, 97 FP64 (rows on 8 bytes) 470 -> 343, 474 with every 16 bytes in
+// two pieces of 8.
+// PB: what a row starts on and is a multiple of, 128 bytes (cache lines), 16 or 8.
 // ---------------------------------------------------------------------------
 constexpr int kSlotBytes = 512;      // staged coefficients of an atom: 4 channels x 128 bytes
 constexpr int kRowGroup = 16;        // rows of a KB weight matrix
@@ -682,9 +683,12 @@ __device__ inline mf4 mfma4(float a, float b, mf4 c) { return __builtin_amdgcn_m
 __device__ inline md4 mfma4(double a, double b, md4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-// 16 bytes from any multiple of 4.  policy 2 = non-temporal: Y_{k-1} is read and Y_{k+1} written once per
-// launch, so they should not displace the X rows that neighbouring tiles read
-// again as halos.
+// 16 bytes from any multiple of 4.  policy 2 = non-temporal: Y_{k-1} is read and
+// Y_{k+1} written once per launch, so they should not displace the X rows that
+// neighbouring tiles read again as halos (5 nm, 256 FP32: 2481 -> 2361 us with the
+// reads so, 2429 without the writes so).  Not where two chunks share a cache line,
+// which would be fetched twice (2 nm, 97 FP64: 377 against 343 us; 1.1 nm, 33 FP64
+// 62 against 41).
 template <class V, int POLICY>
 __device__ inline V bload16(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
     return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, voff, int(soff), POLICY));
@@ -798,7 +802,7 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
         V c;
 #pragma unroll
         for (int e = 0; e < N; ++e) c.e[e] = T(0);
-        if constexpr (PB == 16) {
+        if constexpr (PB >= 16) {
             if (vok) c = *reinterpret_cast<const V*>(src);
         } else {
 #pragma unroll
@@ -890,7 +894,7 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         // loads of this plane's update and of the next plane
-        const V zc = bload16<V, 2>(rZ, off_z, unsigned(z) * plane_z);   // zero without Z (empty buffer)
+        const V zc = bload16<V, PB == 128 ? 2 : 0>(rZ, off_z, unsigned(z) * plane_z);   // zero without Z (empty buffer)
         const T vr = veff[base + col + 64 * z];
         if (z < 7) {
 #pragma unroll
@@ -929,13 +933,13 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
         // that distance only for stores without one.
         const u32x4 yb = __builtin_bit_cast(u32x4, y);
         const unsigned oy = off_y + unsigned(z) * plane_y;
-        if constexpr (PB == 16) {
-            __builtin_amdgcn_raw_buffer_store_b128(yb, rY, oy, 0, 2);
+        if constexpr (PB >= 16) {
+            __builtin_amdgcn_raw_buffer_store_b128(yb, rY, oy, 0, PB == 128 ? 2 : 0);
         } else {
             // a row's last piece may be half inside
             const bool whole = vbase + N / 2 < nvec;
-            __builtin_amdgcn_raw_buffer_store_b128(yb, rY, whole ? oy : kOOB, 0, 2);
-            if (nvec % N) __builtin_amdgcn_raw_buffer_store_b64(u32x2{yb.x, yb.y}, rY, whole ? kOOB : oy, 0, 2);
+            __builtin_amdgcn_raw_buffer_store_b128(yb, rY, whole ? oy : kOOB, 0, 0);
+            if (nvec % N) __builtin_amdgcn_raw_buffer_store_b64(u32x2{yb.x, yb.y}, rY, whole ? kOOB : oy, 0, 0);
         }
         if (z < 7) {
             // (the weights are not fetched above the stencil, whose operands
@@ -1016,9 +1020,8 @@ static void launch_tile(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, 
     // Chunks at a time: 2 where rows are whole cache lines, all where chunks share
     // lines.  us per launch for 1, 2, 4, all: 5 nm 256 FP32 2358, 2360, 2454, 2494;
     // 5 nm 128 FP64 2682, 2561, 2619, 2632; 3 nm 256 FP64 1478, 1478, 1536, 1596;
-    // 1.1 nm 128 FP64 102, 103, 108, 110; but 2 nm 97 FP64 429, 403, 395, 380.
-    const auto lines = [](const void* q, int64_t ld) { return uintptr_t(q) % 128 == 0 && ld * sizeof(T) % 128 == 0; };
-    const int group = lines(X, ldx) && lines(Y, ldy) && (!Z || lines(Z, ldz)) ? 2 : n_chunks;
+    // 1.1 nm 128 FP64 102, 103, 108, 110; but 2 nm 97 FP64 449, 393, 374, 343.
+    const int group = PB == 128 ? 2 : n_chunks;
     const int64_t nt = (H->grid.n_blocks + 7) / 8 * 8 * n_chunks;
     const T* rg_beta = std::is_same<T, double>::value ? H->rg_beta64.as<T>() : H->rg_beta32.as<T>();
     hx_tile_kernel<T, PB, SLOTS><<<dim3(unsigned(nt)), dim3(512), 0, s>>>(
@@ -1034,20 +1037,21 @@ void launch_hx_tiled(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, con
     const bool kb = !lap_only && H->proj.n_proj > 0;
     const StepCoef<T> coef = make_coef<T>(H, alpha, shift, beta);
     if (kb && H->proj.max_block_atoms <= kMaxBlockAtoms) {
-        // rows of 16-byte pieces where widths, leading dimensions and base
-        // addresses allow, else of 8-byte ones
+        // rows of whole cache lines or of 16-byte pieces where widths, leading
+        // dimensions and base addresses allow, else of 8-byte ones
         constexpr int N = Wide<T>::N;
         const bool a16 = nvec % N == 0 && ldx % N == 0 && ldy % N == 0 && (!Z || ldz % N == 0) &&
                          uintptr_t(X) % 16 == 0 && uintptr_t(Y) % 16 == 0 && uintptr_t(Z) % 16 == 0;
-        const bool few = H->proj.max_block_atoms <= kFewSlots;
-        auto go = [&](auto pb, auto slots) {
-            launch_tile<T, decltype(pb)::value, decltype(slots)::value>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, coef, s);
+        const auto lines = [](const void* q, int64_t ld) { return uintptr_t(q) % 128 == 0 && ld * sizeof(T) % 128 == 0; };
+        const bool whole = a16 && lines(X, ldx) && lines(Y, ldy) && (!Z || lines(Z, ldz));
+        auto go = [&](auto slots) {
+            constexpr int SLOTS = decltype(slots)::value;
+            if (whole) launch_tile<T, 128, SLOTS>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, coef, s);
+            else if (a16) launch_tile<T, 16, SLOTS>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, coef, s);
+            else launch_tile<T, 8, SLOTS>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, coef, s);
         };
-        using std::integral_constant;
-        if (few && a16) go(integral_constant<int, 16>{}, integral_constant<int, kFewSlots>{});
-        else if (few) go(integral_constant<int, 8>{}, integral_constant<int, kFewSlots>{});
-        else if (a16) go(integral_constant<int, 16>{}, integral_constant<int, kMaxBlockAtoms>{});
-        else go(integral_constant<int, 8>{}, integral_constant<int, kMaxBlockAtoms>{});
+        if (H->proj.max_block_atoms <= kFewSlots) go(std::integral_constant<int, kFewSlots>{});
+        else go(std::integral_constant<int, kMaxBlockAtoms>{});
         return;
     }
     constexpr int CH = kLanes * Lane<T>::N;
