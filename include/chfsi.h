@@ -289,9 +289,9 @@ int orthonormalize(chf_ctx* ctx, chf_dtype dtype, void* X_dev, int64_t ldx, int6
 /* Rayleigh-Ritz (paper: the CheFSI paragraph): W = H X in column blocks of
  * min(nvec, ldw) vectors through the work block ([n_rows][ldw], ldw >= 1,
  * same dtype as X, disjoint from it), Hs = X^T W symmetrised (FP64),
- * Hs = Q diag(eig) Q^T (FP64), X <- X Q in row panels of n_rows ldw / nvec
- * rows, in place (the work block holds one panel at a time; Q rounded to
- * FP32 for an FP32 block).  eig_host [nvec] ascending.  So the work block
+ * Hs = Q diag(eig) Q^T (FP64), X <- X Q in place: up to 128 vectors directly,
+ * beyond in row panels of n_rows ldw / nvec rows (the work block holds one
+ * panel at a time); Q rounded to FP32 for an FP32 block.  eig_host [nvec] ascending.  So the work block
  * can be much narrower than X: at 7552 FP64 states a 256-wide work block is
  * 1/30 of X.  Errors: CHF_EINVAL (null argument, ldx < nvec, ldw < 1, X and
  * work overlapping, nvec above the grid's point count, a handle without this

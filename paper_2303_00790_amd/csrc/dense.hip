@@ -6,7 +6,7 @@
 // its ChFSI reference).  The Gram products X^T X and X^T (H X) are kernels of
 // gram.hip, the FP64 Cholesky factorisation and the solve X R^{-1} trsolve.hip, the
 // M x M symmetric eigensolve eig.hip (FP64, around rocSOLVER); the N x M x M block
-// update X Q is a plain GEMM (rocBLAS on MFMA).
+// update X Q is rotate() of trsolve.hip up to 128 columns, else a plain GEMM (rocBLAS).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -202,7 +202,10 @@ static double* mm_scratch(chf_ctx* ctx, int m, size_t extra_bytes) {
 static size_t cholqr_extra(int m, size_t elem_bytes) {
     return size_t(m + 1) / 2 * 2 * sizeof(double) + cholesky_work_bytes(m, elem_bytes);
 }
-static size_t rr_extra(int m) { return size_t(m) * sizeof(double) * 2 + eig_work_bytes(m); }
+// (the rotation's operands may take the eigensolver's scratch once that is done)
+static size_t rr_extra(int m) {
+    return size_t(m) * sizeof(double) * 2 + std::max(eig_work_bytes(m), rotate_work_bytes(m, sizeof(double)));
+}
 
 __global__ void diag_copy_kernel(int m, const double* __restrict__ S, double* __restrict__ d, int* __restrict__ info) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -358,7 +361,9 @@ void rayleigh_ritz_t(chf_ham* H, chf_ctx* ctx, T* X, int64_t ldx, int m, double*
     if (info != 0) fail(CHF_ENOTCONV, "rayleigh_ritz: eigensolver did not converge (info %d)", info);
     for (int i = 0; i < m; ++i)
         if (!std::isfinite(eig_host[i])) fail(CHF_ENONFINITE, "rayleigh_ritz: non-finite Ritz value");
-    // Hs now holds Q column-major (column j = eigenvector j).  X <- X Q in row
+    // Hs now holds Q column-major (column j = eigenvector j)
+    if (rotate<T>(X, ldx, n_rows, m, Hs, E + m, s)) return;
+    // wider: X <- X Q in row
     // panels, in place: a panel of P rows of X (row-major, = column-major
     // Xc [m][P]) gives Qᵀ Xc, computed into the work block used as flat
     // storage of P x m values (P = n_rows ldw / m), then copied back.

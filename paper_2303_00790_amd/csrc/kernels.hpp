@@ -92,6 +92,12 @@ void cholesky(double* S, int m, void* work, int* info, hipStream_t s);
 template <class T>
 void solve_upper(T* X, int64_t ldx, int64_t n_rows, int m, const double* R, void* work, hipStream_t s);
 
+// X <- X Q in place, Q m x m column-major FP64, for the widths it takes (else false);
+// work: rotate_work_bytes(m) bytes, 16-byte aligned (trsolve.hip)
+size_t rotate_work_bytes(int m, size_t elem_bytes);
+template <class T>
+bool rotate(T* X, int64_t ldx, int64_t n_rows, int m, const double* Q, void* work, hipStream_t s);
+
 // eigenvalues (ascending) and eigenvectors (columns, over S) of the symmetric
 // m x m S; E: m doubles, work: eig_work_bytes(m) (eig.hip)
 constexpr int kEigMax = 192;

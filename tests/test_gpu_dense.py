@@ -445,3 +445,24 @@ def test_orthonormalize_reports_the_failing_column(system, dtype, col):
     Xg = torch.from_numpy(X).to(device="cuda", dtype=dtype)
     with pytest.raises(B.ChfError, match=rf"minor {col + 1}\b"):
         B.orthonormalize(system["ctx"], Xg)
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-13), (torch.float32, 2e-6)])
+@pytest.mark.parametrize("m", [1, 15, 17, 31, 97, 128, 129])
+def test_rayleigh_ritz_rotation_in_place(system, dtype, tol, m):
+    # the rotation of up to 128 columns in place, and the panels beyond, on
+    # columns off any alignment with NaN beside them, which stay: X Q from the
+    # Q that takes X to the result, sums of m products of unit columns
+    s, B = system, system["B"]
+    X, _ = np.linalg.qr(np.random.default_rng(m).standard_normal((s["g"].n, m)))
+    Xg = torch.full((s["Hg"].n_rows, m + 3), float("nan"), dtype=dtype, device="cuda")
+    Xg[:, 1:1 + m] = to_rows(s, X, dtype)
+    X = from_rows(s, Xg[:, 1:1 + m].contiguous(), m)
+    W = torch.zeros((s["Hg"].n_rows, m), dtype=dtype, device="cuda")
+    B.rayleigh_ritz(s["Hg"], s["ctx"], Xg[:, 1:1 + m], W)
+    got = from_rows(s, Xg[:, 1:1 + m].contiguous(), m)
+    Q = np.linalg.lstsq(X, got, rcond=None)[0]
+    assert np.abs(X @ Q - got).max() < 8 * tol * (np.sqrt(m) + 2) * np.abs(got).max()
+    assert np.abs(Q.T @ Q - np.eye(m)).max() < 8 * tol * (np.sqrt(m) + 2)
+    assert bool(torch.isnan(Xg[:, 0]).all()) and bool(torch.isnan(Xg[:, 1 + m:]).all())
+    assert not bool(torch.isnan(Xg[:, 1:1 + m]).any())
