@@ -2,11 +2,11 @@
 // FP64) and X <- X R^{-1} for the tall row-major block.
 //
 // Panels of 128 columns, left to right: X_j <- (X_j - sum_{k<j} X_k R_kj) R_jj^{-1},
-// with the diagonal blocks inverted beforehand in FP64.  A wave owns 32 rows and
+// with the diagonal blocks inverted beforehand in FP64.  A wave owns 32 or 16 rows and
 // walks all panels, so the solve is one launch without a barrier; its operands
 // come straight from memory, 16 bytes along k per lane and load (a lane's values
 // go to successive products, which permutes k alike on both sides).  R and the
-// inverses are laid out beforehand as such operands, 1 KB per 16 columns and
+// inverses are laid out beforehand as operands, 1 KB per 16 columns and
 // group of k: from their column-major form a load takes half of 16 cache lines,
 // more than the L1 holds until the other halves are wanted.
 //
@@ -57,14 +57,19 @@ __device__ inline Piece16<T> load16(const T* p) {
 
 // values of one operand (64 lanes), and the operand order of an upper triangle
 // of 16-column tiles and `groups` groups of k per tile: element e of lane l of
-// tile t and group g is R[k][j], j = 16 t + l % 16, k = g KG + N (l / 16) + e
+// tile t and group g is R[k][j], j = 16 t + l % 16, and k = g KG + N (l / 16) + e
+// where the other operand comes from memory, whose pieces lie along k.  The
+// inverses take k = g KG + 4 e + l / 16 instead, so that the products add k in
+// ascending order and the largest term, the diagonal's, last: out of order the
+// sums after it round at its size (FP64, 128 columns: 1.11 against 1.05 eps beside
+// the columns' common factors, 1.05 for the library).
 template <class T>
 struct Packed {
     static constexpr int N = Piece16<T>::N, KG = 4 * N, V = 64 * N;
-    __device__ static void where(int64_t idx, int groups, int* k, int* j) {
+    __device__ static void where(int64_t idx, int groups, bool ascending, int* k, int* j) {
         const int e = int(idx % N), l = int(idx / N % 64);
         const int64_t op = idx / V;
-        *k = int(op % groups) * KG + N * (l >> 4) + e;
+        *k = int(op % groups) * KG + (ascending ? 4 * e + (l >> 4) : N * (l >> 4) + e);
         *j = int(op / groups) * 16 + (l & 15);
     }
 };
@@ -78,7 +83,7 @@ __global__ void __launch_bounds__(256) pack_upper_kernel(int m, int groups, int6
     const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (idx >= n) return;
     int k, j;
-    Packed<T>::where(idx, groups, &k, &j);
+    Packed<T>::where(idx, groups, false, &k, &j);
     P[idx] = k <= j && j < m ? -T(R[int64_t(j) * m + k]) : T(0);
 }
 
@@ -243,10 +248,10 @@ __global__ void __launch_bounds__(512) chol_diag_kernel(int m, int b0, double* _
     const int n = (w + 15) / 16 * 16 * kTriBlock;
     for (int idx = t; idx < n; idx += 512) {
         int k, j;
-        Packed<T>::where(idx, kTriBlock / Packed<T>::KG, &k, &j);
+        Packed<T>::where(idx, kTriBlock / Packed<T>::KG, true, &k, &j);
         Z[idx] = k <= j ? T(M[k * kTriPitch + j]) : T(0);
         if (W) {
-            Packed<double>::where(idx, kTriBlock / Packed<double>::KG, &k, &j);
+            Packed<double>::where(idx, kTriBlock / Packed<double>::KG, true, &k, &j);
             W[idx] = k <= j ? M[k * kTriPitch + j] : 0.0;
         }
     }
@@ -262,7 +267,9 @@ __global__ void __launch_bounds__(64) chol_panel_kernel(int m, int b0, double* S
     double* const sc = S + int64_t(min(col, m - 1)) * m + b0;
     Piece16<double> b[NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) b[g] = load16(sc + g * K::KG + K::N * kq);
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int e = 0; e < K::N; ++e) b[g].e[e] = sc[g * K::KG + 4 * e + kq];
 #pragma unroll
     for (int q = 0; q < kTriBlock / 16; ++q) {
         Acc<double> acc = {0, 0, 0, 0};
@@ -326,10 +333,10 @@ __global__ void __launch_bounds__(256) chol_update_kernel(int m, int b0, double*
             }
 }
 
-template <class T>
+template <class T, int RT>
 __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kernel(T* X, int64_t ldx, int64_t n_rows, int m, int groups,
                                                              const T* __restrict__ R, const T* __restrict__ Z) {
-    constexpr int N = Piece16<T>::N, KG = 4 * N, G = 16 / KG, RT = 2, CT = kTriBlock / 16;
+    constexpr int N = Piece16<T>::N, KG = 4 * N, G = 16 / KG, CT = kTriBlock / 16;
     constexpr int LP = 16 + N;                 // pitch of a 16 x 16 tile in LDS, rows 16-byte aligned
     __shared__ __align__(16) T turn[4][16 * RT * LP];
     const int lane = threadIdx.x & 63, l = lane & 15, kq = lane >> 4;
@@ -341,12 +348,13 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
     const T* xr[RT];
 #pragma unroll
     for (int p = 0; p < RT; ++p) xr[p] = X + min(row0 + 16 * p + l, n_rows - 1) * ldx + N * kq;
-    // FP32: the products are summed over kTriBlock of k at a time, from zero, and the
-    // sums taken from the panel one after the other, as the blocked solve of a
-    // library does: one chain over all k rounds m / 4 times at the size of the whole
-    // (error against 64 bits at 600 columns 1.3e-6, in blocks 0.8e-6).  FP64
-    // has no registers for it: there the panel is where the products are added.
-    constexpr bool APART = sizeof(T) == 4;
+    // The products are summed over kTriBlock of k at a time, from zero, and the sums
+    // taken from the panel one after the other, as the blocked solve of a library
+    // does: one chain over all k rounds m times at the size of the whole (error at
+    // 600 columns, FP32, 1.3e-6, in blocks 0.8e-6; columns 384 to 400 of 400, FP64,
+    // 8.6 and 2.0 eps).  With FP64 blocks of one panel there are no products, and
+    // the panel is kept where they would be added.
+    constexpr bool APART = sizeof(T) == 4 || RT == 1;
     Acc<T> acc[RT][CT], own[APART ? RT : 1][APART ? CT : 1];
     // columns past the end repeat the last one
     auto start = [&](int j0) {
@@ -371,8 +379,9 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
         // two groups at a time, whole cache lines of its rows.  FP32: the order is
         // kept and the sums stay in accumulation registers, one wave per SIMD
         // (4.8 ms at 440,000 x 1024; 5.2 as the compiler orders it for two waves).
-        // FP64: two waves, whose products are long enough to cover the loads
-        // (3.3 ms at 440,000 x 600; 3.6 with one).
+        // FP64: two waves, whose products are long enough to cover the loads;
+        // the sums apart leave them registers for 16 rows each (3.5 ms at 440,000 x
+        // 600; 32 rows and one wave 3.8).
         auto keep_order = [] {
             if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
         };
@@ -465,7 +474,8 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
             for (int p = 0; p < RT; ++p)
 #pragma unroll
                 for (int g = 0; g < G; ++g)
-                    v[p][q][g] = *reinterpret_cast<const Piece16<T>*>(tw + (p * 16 + l) * LP + g * KG + N * kq);
+#pragma unroll
+                    for (int e = 0; e < N; ++e) v[p][q][g].e[e] = tw[(p * 16 + l) * LP + g * KG + 4 * e + kq];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
         // times the inverse of R_jj
@@ -522,7 +532,7 @@ __global__ void __launch_bounds__(256) pack_square_kernel(int m, int groups, int
     const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (idx >= n) return;
     int k, j;
-    Packed<T>::where(idx, groups, &k, &j);
+    Packed<T>::where(idx, groups, false, &k, &j);
     P[idx] = k < m && j < m ? T(Q[int64_t(j) * m + k]) : T(0);
 }
 
@@ -626,7 +636,18 @@ void solve_upper(T* X, int64_t ldx, int64_t n_rows, int m, const double* R, void
         pack_upper_kernel<T><<<unsigned((n + 255) / 256), 256, 0, s>>>(m, groups, n, R, P);
         LAUNCH_CHECK();
     }
-    solve_upper_kernel<T><<<unsigned((n_rows + 127) / 128), 256, 0, s>>>(X, ldx, n_rows, m, groups, P, Z);
+    // rows of a wave: 32, or 16 for FP64 blocks of several panels (one panel,
+    // 120,000 x 128: 68 us with 32, 71 with 16)
+    auto go = [&](auto rt) {
+        constexpr int RT = decltype(rt)::value;
+        solve_upper_kernel<T, RT><<<unsigned((n_rows + 64 * RT - 1) / (64 * RT)), 256, 0, s>>>(X, ldx, n_rows, m, groups, P, Z);
+    };
+    if constexpr (sizeof(T) == 8) {
+        if (panels > 1) go(std::integral_constant<int, 1>{});
+        else go(std::integral_constant<int, 2>{});
+    } else {
+        go(std::integral_constant<int, 2>{});
+    }
     LAUNCH_CHECK();
 }
 template void solve_upper<float>(float*, int64_t, int64_t, int, const double*, void*, hipStream_t);

@@ -466,3 +466,34 @@ def test_rayleigh_ritz_rotation_in_place(system, dtype, tol, m):
     assert np.abs(Q.T @ Q - np.eye(m)).max() < 8 * tol * (np.sqrt(m) + 2)
     assert bool(torch.isnan(Xg[:, 0]).all()) and bool(torch.isnan(Xg[:, 1 + m:]).all())
     assert not bool(torch.isnan(Xg[:, 1:1 + m]).any())
+
+
+@pytest.mark.parametrize("m", [97, 260, 400])
+def test_orthonormalize_f64_rounds_like_a_blocked_solve(system, m):
+    # Whole numbers: the Gram matrix is exact, and the columns are nearly orthogonal,
+    # so what is left is the rounding of the factorisation and of the solve.  Against
+    # 80 bits, without each column's common factor (the rounding of its pivot).  The
+    # sums over blocks of 128 columns round a few times at the size of the column:
+    # 1.1 eps in an emulation of their order, half of that again for R; twice their
+    # sum is allowed.  One chain over all columns rounds at every one of them: 4.8
+    # eps in the second panel and growing.
+    n = 4096
+    X = np.random.default_rng(m).integers(-8, 9, (n, m)).astype(np.float64)
+    Xl = X.astype(np.longdouble)
+    S = Xl.T @ Xl
+    R = np.zeros_like(S)
+    for k in range(m):
+        R[k, k:] = S[k, k:] / np.sqrt(S[k, k])
+        S[k + 1:, k + 1:] -= np.outer(R[k, k + 1:], R[k, k + 1:])
+    Q = np.zeros_like(Xl)
+    for j in range(m):
+        Q[:, j] = (Xl[:, j] - Q[:, :j] @ R[:j, j]) / R[j, j]
+    Xg = torch.from_numpy(X).cuda()
+    system["B"].orthonormalize(system["ctx"], Xg)
+    err = (Xg.cpu().numpy() - Q).astype(np.float64)
+    Q = Q.astype(np.float64)
+    err -= Q * ((err * Q).sum(0) / (Q * Q).sum(0))
+    for c in range(0, m, 128):
+        rms = np.sqrt((err[:, c:c + 128] ** 2).mean() / (Q * Q).mean()) / 2.0 ** -53
+        print(f"columns from {c}: {rms:.2f} eps")
+        assert rms < 3.2, c
