@@ -31,6 +31,7 @@ constexpr int64_t kGramMinRows = 256;
 constexpr int64_t kGramTargetGroups = 4096;
 constexpr size_t kGramPartBytes = size_t(1) << 30;   // partials at once, a group of slices
 constexpr int64_t kGramUnroll = 4;                   // 4-row steps per loop turn
+constexpr int64_t kMaxGroups = int64_t(1) << 24;     // of 256 threads: a launch has less than 2^32
 
 static int64_t gram_ldp(int n) { return (int64_t(n) + 3) / 4 * 4; }
 
@@ -204,30 +205,36 @@ __global__ void __launch_bounds__(256) gram_kernel(const TI* __restrict__ A, int
 // S[i][j] (+)= sum over slices of part[s][i][j], in FP64 and in a fixed order
 // (accumulate: add to S, for the slice groups after the first); with a symmetric
 // product only i <= j is summed and mirrored, so S is exactly symmetric.  A
-// workgroup takes 32 columns of a row and 8 runs of slices.
+// workgroup takes 32 columns of a row and 8 runs of slices, and goes on to the next
+// of its pieces: a launch holds fewer than 2^24 workgroups of 256 threads, and more
+// would be dropped without an error (from 23,171 x 23,171 on).
 template <class TA>
 __global__ void __launch_bounds__(256) gram_reduce_kernel(int m, int n, int n_slices, const TA* __restrict__ part,
                                                           int64_t ldp, double* __restrict__ S, int64_t lds, int symmetric,
                                                           int accumulate) {
     __shared__ double sh[8][33];
-    const int chunks = (n + 31) / 32;
-    const int i = int(blockIdx.x) / chunks, jb = int(blockIdx.x) % chunks * 32, j = jb + int(threadIdx.x % 32), q = threadIdx.x / 32;
-    if (symmetric && jb + 31 < i) return;
-    double acc = 0.0;
-    if (j < n && !(symmetric && i > j)) {
-        const TA* const p = part + int64_t(i) * ldp + j;
-        const int64_t stride = int64_t(m) * ldp;
+    const int chunks = (n + 31) / 32, q = threadIdx.x / 32;
+    for (int64_t piece = blockIdx.x; piece < int64_t(m) * chunks; piece += gridDim.x) {
+        const int i = int(piece / chunks), jb = int(piece % chunks) * 32, j = jb + int(threadIdx.x % 32);
+        if (symmetric && jb + 31 < i) continue;
+        const bool in = j < n && !(symmetric && i > j);
+        double acc = 0.0;
+        if (in) {
+            const TA* const p = part + int64_t(i) * ldp + j;
+            const int64_t stride = int64_t(m) * ldp;
 #pragma unroll 8
-        for (int k = q; k < n_slices; k += 8) acc += double(p[k * stride]);
-    }
-    sh[q][threadIdx.x % 32] = acc;
-    __syncthreads();
-    if (q > 0 || j >= n || (symmetric && i > j)) return;
-    double s = accumulate ? S[int64_t(i) * lds + j] : 0.0;
+            for (int k = q; k < n_slices; k += 8) acc += double(p[k * stride]);
+        }
+        __syncthreads();             // the last piece's sums have been read
+        sh[q][threadIdx.x % 32] = acc;
+        __syncthreads();
+        if (q > 0 || !in) continue;
+        double s = accumulate ? S[int64_t(i) * lds + j] : 0.0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += sh[k][threadIdx.x];
-    S[int64_t(i) * lds + j] = s;
-    if (symmetric && i < j) S[int64_t(j) * lds + i] = s;
+        for (int k = 0; k < 8; ++k) s += sh[k][threadIdx.x];
+        S[int64_t(i) * lds + j] = s;
+        if (symmetric && i < j) S[int64_t(j) * lds + i] = s;
+    }
 }
 
 template <class TI, class TA>
@@ -247,7 +254,7 @@ void gram_product(chf_ctx* ctx, const TI* A, int64_t lda, const TI* B, int64_t l
         const int64_t at = s0 * g.rows;
         const int64_t slots = (quad ? cnt : (cnt + 3) / 4);
         const int64_t total = slots * g.tiles, groups = (total + 7) / 8 * 8;
-        CHF_REQUIRE(groups <= INT32_MAX && int64_t(m) * ((n + 31) / 32) <= INT32_MAX, "gram: grid too large");
+        CHF_REQUIRE(groups < kMaxGroups, "gram: grid too large");
         auto go = [&](auto p, auto gg, auto qd) {
             gram_kernel<TI, TA, decltype(p)::value, decltype(gg)::value, decltype(qd)::value>
                 <<<unsigned(groups), 256, 0, s>>>(A + at * lda, lda, B + at * ldb, ldb, n_rows - at, m, n, int(g.rows),
@@ -262,7 +269,7 @@ void gram_product(chf_ctx* ctx, const TI* A, int64_t lda, const TI* B, int64_t l
         else if (W == 32) go(Two{}, One{}, std::false_type{});
         else go(One{}, One{}, std::false_type{});
         LAUNCH_CHECK();
-        gram_reduce_kernel<TA><<<unsigned(int64_t(m) * ((n + 31) / 32)), 256, 0, s>>>(
+        gram_reduce_kernel<TA><<<unsigned(std::min(kMaxGroups / 2, int64_t(m) * ((n + 31) / 32))), 256, 0, s>>>(
             m, n, cnt, part, ldp, S, lds, symmetric ? 1 : 0, s0 > 0 ? 1 : 0);
         LAUNCH_CHECK();
     }

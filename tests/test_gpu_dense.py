@@ -497,3 +497,21 @@ def test_orthonormalize_f64_rounds_like_a_blocked_solve(system, m):
         rms = np.sqrt((err[:, c:c + 128] ** 2).mean() / (Q * Q).mean()) / 2.0 ** -53
         print(f"columns from {c}: {rms:.2f} eps")
         assert rms < 3.2, c
+
+
+@pytest.mark.parametrize("same", [True, False])
+def test_gram_of_very_wide_blocks(system, same):
+    # more pieces of 32 columns than a launch has workgroups: every entry of S is
+    # written.  Sums of 3 products of N(0, 1) pairs in FP32.
+    B = system["B"]
+    m = 23200
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+    At = torch.randn((3, m), generator=gen, dtype=torch.float32, device="cuda")
+    Bt = At if same else torch.randn((3, m), generator=gen, dtype=torch.float32, device="cuda")
+    S = torch.full((m, m), float("nan"), dtype=torch.float64, device="cuda")
+    B.gram(system["ctx"], At, Bt, S)
+    err = [float((S[r:r + 2320] - At[:, r:r + 2320].double().T @ Bt.double()).abs().max()) for r in range(0, m, 2320)]
+    del S
+    torch.cuda.empty_cache()
+    assert all(e < 8e-7 * 8 for e in err), err
