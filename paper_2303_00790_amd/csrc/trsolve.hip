@@ -606,6 +606,14 @@ size_t cholesky_work_bytes(int m, size_t elem_bytes) {
     return size_t((elem_bytes == 4 ? 2 * square : 0) + panels * square + packed_values(m)) * elem_bytes;
 }
 
+// the rows in runs whose launches, of up to 4 threads a row, stay below the 2^32
+// threads at which the count wraps
+template <class F>
+static void by_rows(int64_t n_rows, F&& launch) {
+    constexpr int64_t kRun = int64_t(1) << 29;
+    for (int64_t r0 = 0; r0 < n_rows; r0 += kRun) launch(r0, std::min(kRun, n_rows - r0));
+}
+
 template <class T>
 void cholesky(double* S, int m, void* work, int* info, hipStream_t s) {
     double* const W = sizeof(T) == 4 ? static_cast<double*>(work) : nullptr;
@@ -640,7 +648,10 @@ void solve_upper(T* X, int64_t ldx, int64_t n_rows, int m, const double* R, void
     // 120,000 x 128: 68 us with 32, 71 with 16)
     auto go = [&](auto rt) {
         constexpr int RT = decltype(rt)::value;
-        solve_upper_kernel<T, RT><<<unsigned((n_rows + 64 * RT - 1) / (64 * RT)), 256, 0, s>>>(X, ldx, n_rows, m, groups, P, Z);
+        by_rows(n_rows, [&](int64_t r0, int64_t rows) {
+            solve_upper_kernel<T, RT><<<unsigned((rows + 64 * RT - 1) / (64 * RT)), 256, 0, s>>>(X + r0 * ldx, ldx, rows, m,
+                                                                                                groups, P, Z);
+        });
     };
     if constexpr (sizeof(T) == 8) {
         if (panels > 1) go(std::integral_constant<int, 1>{});
@@ -664,7 +675,9 @@ bool rotate(T* X, int64_t ldx, int64_t n_rows, int m, const double* Q, void* wor
     T* const P = static_cast<T*>(work);
     pack_square_kernel<T><<<unsigned((n + 255) / 256), 256, 0, s>>>(m, (m + 15) / 16 * 16 / Packed<T>::KG, n, Q, P);
     LAUNCH_CHECK();
-    rotate_kernel<T><<<unsigned((n_rows + 127) / 128), 256, 0, s>>>(X, ldx, n_rows, m, P);
+    by_rows(n_rows, [&](int64_t r0, int64_t rows) {
+        rotate_kernel<T><<<unsigned((rows + 127) / 128), 256, 0, s>>>(X + r0 * ldx, ldx, rows, m, P);
+    });
     LAUNCH_CHECK();
     return true;
 }

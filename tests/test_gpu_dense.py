@@ -515,3 +515,17 @@ def test_gram_of_very_wide_blocks(system, same):
     del S
     torch.cuda.empty_cache()
     assert all(e < 8e-7 * 8 for e in err), err
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-12), (torch.float32, 1e-5)])
+def test_orthonormalize_of_the_longest_blocks(system, dtype, tol):
+    # one column of the most rows the call takes, where a launch over all of them
+    # would have 2^32 threads: it is scaled to length one
+    B = system["B"]
+    n = (1 << 31) - 1
+    X = torch.full((n, 1), 3.0, dtype=dtype, device="cuda")
+    assert B.orthonormalize(system["ctx"], X) == 0
+    lo, hi = float(X.min()), float(X.max())
+    del X
+    torch.cuda.empty_cache()
+    assert abs(lo * n ** 0.5 - 1) < tol and abs(hi * n ** 0.5 - 1) < tol
