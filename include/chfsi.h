@@ -241,9 +241,9 @@ int gram(chf_ctx* ctx, chf_dtype dtype, const void* A_dev, int64_t lda, const vo
  * coefficients on the Hamiltonian; M x M matrices, Gram partials, Lanczos
  * vectors and reduction partials on the context) and grows it on first use
  * at a larger size.  For an operation at nvec vectors of dtype on the
- * Hamiltonian's grid, chf_workspace_bytes reports the scratch it grows to on
- * each handle (ldw: the Rayleigh-Ritz work leading dimension, ignored
- * otherwise); chf_reserve grows it now, so later calls of that operation at
+ * Hamiltonian's grid, chf_workspace_bytes reports the most scratch that it and
+ * smaller ones grow to on each handle (ldw: the Rayleigh-Ritz work leading
+ * dimension, ignored otherwise); chf_reserve grows it now, so later calls of that operation at
  * the same or smaller sizes make no device allocation in this library
  * (rocBLAS / rocSOLVER keep their own workspace on the context's handle,
  * grown by them on first use).  Operations: */

@@ -664,8 +664,9 @@ int rayleigh_ritz(chf_ham* H, chf_ctx* ctx, chf_dtype dtype, void* X, int64_t ld
     });
 }
 
-// device scratch of one operation: on the Hamiltonian (KB coefficients) and on
-// the context (M x M matrices, Gram partials, Lanczos vectors, reductions)
+// device scratch of one operation, at this size and any smaller one: on the
+// Hamiltonian (KB coefficients) and on the context (M x M matrices, Gram partials,
+// Lanczos vectors, reductions)
 struct WsNeed {
     size_t kb = 0, scratch = 0, scratch2 = 0, vec = 0, red = 0;
 };
@@ -683,15 +684,16 @@ static WsNeed ws_need(const chf_ham* H, int op, chf_dtype dtype, int nvec, int64
         break;
     case CHF_WS_ORTHONORMALIZE:
         w.scratch = mm_scratch_bytes(nvec, cholqr_extra(nvec, es));
-        w.scratch2 = gram_slices(n_rows, nvec, nvec, es, es, nvec, true).part_bytes;
+        w.scratch2 = gram_part_bound(n_rows, nvec, nvec, es, true);
         break;
     case CHF_WS_RAYLEIGH_RITZ: {
         if (ldw <= 0) fail(CHF_EINVAL, "chf_workspace_bytes: Rayleigh-Ritz needs the work leading dimension");
         const int nb = int(std::min<int64_t>(nvec, ldw));
         w.kb = kb_coef_bytes(H, nb, es);
-        w.scratch = mm_scratch_bytes(nvec, rr_extra(nvec));
-        w.scratch2 = gram_slices(n_rows, nvec, nb, es, es, nvec, false).part_bytes;
-        if (nvec % nb) w.scratch2 = std::max(w.scratch2, gram_slices(n_rows, nvec, nvec % nb, es, es, nvec, false).part_bytes);
+        // (up to kEigMax columns the own eigensolver needs more than the library's)
+        const int own = std::min(nvec, kEigMax);
+        w.scratch = std::max(mm_scratch_bytes(nvec, rr_extra(nvec)), mm_scratch_bytes(own, rr_extra(own)));
+        w.scratch2 = gram_part_bound(n_rows, nvec, nb, es, false);
         break;
     }
     case CHF_WS_LANCZOS:

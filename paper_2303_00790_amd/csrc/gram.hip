@@ -16,6 +16,7 @@
 //   120,000 x 128  FP64   X^T X 231 -> 81;   x 24: 227 -> 18.5
 //   440,000 x 12   FP32   X^T X 125 -> 24
 #include <algorithm>
+#include <vector>
 
 #include "internal.hpp"
 #include "kernels.hpp"
@@ -56,12 +57,38 @@ GramSlices gram_slices(int64_t n_rows, int m, int n, size_t acc_bytes, size_t in
     g.part_stride = int64_t(m) * gram_ldp(n);
     const size_t per = size_t(g.part_stride) * acc_bytes;
     const int64_t total = std::max<int64_t>(1, (n_rows + rows - 1) / rows);
+    g.most = std::max((n_rows + kGramSliceRows - 1) / kGramSliceRows,
+                      std::min(want, (n_rows + kGramMinRows - 1) / kGramMinRows));
     rows = std::max<int64_t>(1, (n_rows + total - 1) / total);             // balanced
     g.group = std::max<int64_t>(1, std::min<int64_t>(total, int64_t(kGramPartBytes / per)));
     g.part_bytes = size_t(g.group) * per;
     const int64_t fit = ((int64_t(1) << 32) - 1) / (ld * int64_t(in_bytes));   // 32-bit sizes of a slice
     g.rows = std::max<int64_t>(1, std::min(rows, fit));
     return g;
+}
+
+// Most bytes of partials over all products of at most n_rows rows, m x n columns:
+// narrower ones have fewer pieces, so more slices, and may hold more in all.  With
+// the number of pieces the slices are given, and the widest of that number holds
+// most.
+size_t gram_part_bound(int64_t n_rows, int m, int n, size_t acc_bytes, bool symmetric) {
+    size_t most = 0;
+    const auto widths = [](int w) {
+        std::vector<int> v;
+        for (int c : {16, 32, 64})
+            if (c < w) v.push_back(c);
+        for (int c = 128; c < w; c += 128) v.push_back(c);
+        v.push_back(w);
+        return v;
+    };
+    for (int a : widths(m))
+        for (int b : widths(n)) {
+            if (symmetric && a != b) continue;
+            const GramSlices g = gram_slices(n_rows, a, b, acc_bytes, acc_bytes, 1, symmetric);
+            const size_t per = size_t(g.part_stride) * acc_bytes;
+            most = std::max(most, std::min(size_t(g.most) * per, std::max(kGramPartBytes, per)));
+        }
+    return most;
 }
 
 namespace {

@@ -74,10 +74,12 @@ struct GramSlices {
     int64_t tiles;        // pieces of S per slice
     int64_t rows;         // rows per slice
     int64_t group;        // slices whose partials are held at once
+    int64_t most;         // slices of any product of these pieces over at most n_rows rows
     int64_t part_stride;  // values of one partial
     size_t part_bytes;    // partials scratch
 };
 GramSlices gram_slices(int64_t n_rows, int m, int n, size_t acc_bytes, size_t in_bytes, int64_t ld, bool symmetric);
+size_t gram_part_bound(int64_t n_rows, int m, int n, size_t acc_bytes, bool symmetric);
 template <class TI, class TA>
 void gram_product(chf_ctx* ctx, const TI* A, int64_t lda, const TI* B, int64_t ldb, int64_t n_rows, int m, int n,
                   double* S, int64_t lds, hipStream_t s);

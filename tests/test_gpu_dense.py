@@ -529,3 +529,29 @@ def test_orthonormalize_of_the_longest_blocks(system, dtype, tol):
     del X
     torch.cuda.empty_cache()
     assert abs(lo * n ** 0.5 - 1) < tol and abs(hi * n ** 0.5 - 1) < tol
+
+
+def test_reserved_workspace_covers_smaller_calls(system):
+    # the scratch of an operation is not largest at its largest size: at 128 columns
+    # a Gram matrix is one piece in 1.1 times the bytes of 129, and up to 192 columns
+    # the eigensolver is the library's own
+    from oracle import hamiltonian as OH
+    B = system["B"]
+    helper, ctx = B.Context(0), B.Context(0)
+    B.reserve(system["Hg"], ctx, B.WS_RAYLEIGH_RITZ, B.CHF_F64, 193, 193)
+    for m, ldw in ((193, 193), (192, 192), (130, 3), (129, 128), (128, 100), (65, 65), (17, 16)):
+        X = to_rows(system, random_block(system["g"].n, m, 2420 + m), torch.float64)
+        W = torch.empty((X.shape[0], ldw), dtype=torch.float64, device="cuda")
+        B.orthonormalize(helper, X)
+        before = B.device_allocations()
+        B.rayleigh_ritz(system["Hg"], ctx, X, W)
+        assert B.device_allocations() == before, (m, ldw)
+    H = B.Hamiltonian(np.zeros((1, 3)), np.zeros(1, np.int32), OH.PseudoParams(h_s=2.0, h_p=0.5), 0.7, 27.0,
+                      B.ORDER_HILBERT)
+    ctx = B.Context(0)
+    B.reserve(H, ctx, B.WS_ORTHONORMALIZE, B.CHF_F64, 129)
+    before = B.device_allocations()
+    for m in (129, 128, 64, 32, 16, 1):
+        X = torch.randn((H.n_rows, m), dtype=torch.float64, device="cuda")
+        B.orthonormalize(ctx, X)
+        assert B.device_allocations() == before, m
