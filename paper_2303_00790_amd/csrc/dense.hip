@@ -684,7 +684,9 @@ static WsNeed ws_need(const chf_ham* H, int op, chf_dtype dtype, int nvec, int64
         break;
     case CHF_WS_ORTHONORMALIZE:
         w.scratch = mm_scratch_bytes(nvec, cholqr_extra(nvec, es));
-        w.scratch2 = gram_part_bound(n_rows, nvec, nvec, es, true);
+        // an FP32 block may take an FP64 Gram, by choice or after a breakdown
+        w.scratch2 = std::max(gram_part_bound(n_rows, nvec, nvec, es, true),
+                              gram_part_bound(n_rows, nvec, nvec, sizeof(double), true));
         break;
     case CHF_WS_RAYLEIGH_RITZ: {
         if (ldw <= 0) fail(CHF_EINVAL, "chf_workspace_bytes: Rayleigh-Ritz needs the work leading dimension");

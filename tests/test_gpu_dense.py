@@ -555,3 +555,20 @@ def test_reserved_workspace_covers_smaller_calls(system):
         X = torch.randn((H.n_rows, m), dtype=torch.float64, device="cuda")
         B.orthonormalize(ctx, X)
         assert B.device_allocations() == before, m
+
+
+@pytest.mark.parametrize("gram_dtype", ["f32", "f64"])
+def test_reserved_workspace_covers_the_fp64_gram_of_an_fp32_block(system, gram_dtype):
+    # its partials are twice as large; with an FP32 Gram a dependent column (see the
+    # retry's test) makes the call redo the product in FP64
+    B = system["B"]
+    X = random_block(system["g"].n, 32, 2411)
+    X = X / np.abs(X).max()
+    X[:, 7] = X[:, 3] + 3e-4 * X[:, 7]
+    Xg = to_rows(system, X, torch.float32)
+    ctx = B.Context(0)
+    B.reserve(system["Hg"], ctx, B.WS_ORTHONORMALIZE, B.CHF_F32, 32)
+    before = B.device_allocations()
+    fb = B.orthonormalize(ctx, Xg, gram_dtype=B.CHF_F32 if gram_dtype == "f32" else B.CHF_F64)
+    assert fb == (1 if gram_dtype == "f32" else 0)
+    assert B.device_allocations() == before
