@@ -90,14 +90,17 @@ static void check_block(const chf_ham* H, int dtype, const void* p, int64_t ld, 
 }
 
 // The two blocks of a call that reads one while it writes the other must not
-// share memory: [n_rows][ld] spans of each may not overlap.
+// share memory
+void check_disjoint(const void* A, size_t bytes_a, const void* B, size_t bytes_b, const char* what) {
+    const char* a = static_cast<const char*>(A);
+    const char* b = static_cast<const char*>(B);
+    CHF_REQUIRE(a + bytes_a <= b || b + bytes_b <= a, "%s overlap", what);
+}
+// the same of the whole [n_rows][ld] spans
 void check_disjoint(const chf_ham* H, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                     const char* what) {
     const size_t es = dsize(dtype);
-    const char* a = static_cast<const char*>(A);
-    const char* b = static_cast<const char*>(B);
-    const size_t span_a = size_t(H->grid.n_rows) * size_t(lda) * es, span_b = size_t(H->grid.n_rows) * size_t(ldb) * es;
-    CHF_REQUIRE(a + span_a <= b || b + span_b <= a, "%s overlap", what);
+    check_disjoint(A, size_t(H->grid.n_rows) * size_t(lda) * es, B, size_t(H->grid.n_rows) * size_t(ldb) * es, what);
 }
 
 }  // namespace chf

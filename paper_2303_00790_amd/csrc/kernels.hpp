@@ -43,6 +43,7 @@ template <class T>
 void filter_run_noalloc(chf_ham* H, T* X, int64_t ldx, T* W, int64_t ldw, int nvec, int m, double a, double b,
                         double a0, hipStream_t s);
 // CHF_EINVAL unless the [n_rows][ld] spans of A and B are disjoint (capi.cpp)
+void check_disjoint(const void* A, size_t bytes_a, const void* B, size_t bytes_b, const char* what);
 void check_disjoint(const chf_ham* H, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                     const char* what);
 

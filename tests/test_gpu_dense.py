@@ -572,3 +572,15 @@ def test_reserved_workspace_covers_the_fp64_gram_of_an_fp32_block(system, gram_d
     fb = B.orthonormalize(ctx, Xg, gram_dtype=B.CHF_F32 if gram_dtype == "f32" else B.CHF_F64)
     assert fb == (1 if gram_dtype == "f32" else 0)
     assert B.device_allocations() == before
+
+
+def test_rayleigh_ritz_rejects_overlapping_work(system):
+    # H X would overwrite columns of X that the projection and the rotation still read
+    s, B = system, system["B"]
+    buf = to_rows(s, random_block(s["g"].n, 24, 2430), torch.float64)
+    kept = buf.clone()
+    for X, W in ((buf[:, :16], buf[:, 8:]), (buf[:, :16], buf[:, :16]), (buf[:, 4:8], buf[:, :1])):
+        with pytest.raises(B.ChfError) as e:
+            B.rayleigh_ritz(s["Hg"], s["ctx"], X, W)
+        assert e.value.code == -1 and "overlap" in str(e.value)
+    assert torch.equal(buf, kept)
