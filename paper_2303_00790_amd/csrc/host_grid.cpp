@@ -306,8 +306,8 @@ void build_block_atoms(const HostGrid& g, HostProj& P) {
     }
 }
 
-void list_row_groups(const HostProj& P, int64_t n_groups, int rows, int step, int scale, int64_t (*first_row)(int64_t),
-                     std::vector<int32_t>& off, std::vector<int32_t>& len, std::vector<int32_t>& slot) {
+void list_row_groups(const HostProj& P, int64_t n_groups, int rows, int step, int ahead, int scale,
+                     int64_t (*first_row)(int64_t), std::vector<int32_t>& off, std::vector<int32_t>& len, std::vector<int32_t>& slot) {
     std::vector<uint64_t> mask(static_cast<size_t>(n_groups));
     off.assign(size_t(n_groups) + 1, 0);
     len.resize(size_t(n_groups));
@@ -326,7 +326,7 @@ void list_row_groups(const HostProj& P, int64_t n_groups, int rows, int step, in
         CHF_REQUIRE(n < (int64_t(1) << 31), "ham_build: more than 2^31 row-group entries");
         off[size_t(g) + 1] = int32_t(n);
     }
-    slot.assign(size_t(n), 0);
+    slot.assign(size_t(n + ahead), 0);
 #pragma omp parallel for schedule(static)
     for (int64_t g = 0; g < n_groups; ++g) {
         int32_t* at = slot.data() + off[size_t(g)];

@@ -656,6 +656,7 @@ constexpr int kSlotBytes = 512;      // staged coefficients of an atom: 4 channe
 constexpr int kRowGroup = 16;        // rows of a KB weight matrix
 constexpr int kGroups = kBlockPts / kRowGroup;
 constexpr int kKbStep = 4;           // a group's atom list is padded to this multiple
+constexpr int kKbAhead = 2 * kKbStep;  // entries of a plane whose weights are fetched ahead
 // slots of the half-LDS variant; blocks touched by more atoms take the one
 // with kMaxBlockAtoms slots, one workgroup per CU
 constexpr int kFewSlots = 40;
@@ -831,15 +832,16 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
     const int a_off = lk * 128 + (f32 ? (wave & 1) * 64 + li * 4 : (4 * (li & 3) + (li >> 2)) * 8);
     auto kb_mine = [&](int z) { return f32 || (wave >> 2) == (z & 1); };
     // this wave's entries, plane after plane (one row group's 8 planes are
-    // consecutive): the weights of the first 2 kKbStep entries of a plane are
-    // fetched ahead (kb_fetch), while the plane before it is worked on
+    // consecutive): the weights of the first kKbAhead entries of a plane are
+    // fetched ahead (kb_fetch), while the plane before it is worked on, also where
+    // its list is shorter; behind the last list lie as many that nothing uses
     int e_off[9];
     const int64_t rg0 = int64_t(blk) * kGroups + grp * 8;
 #pragma unroll
     for (int z = 0; z < 9; ++z) e_off[z] = rg_off[rg0 + z];
     const __amdgpu_buffer_rsrc_t rW =
         make_rsrc(rg_beta + int64_t(e_off[0]) * 64, unsigned(e_off[8] - e_off[0]) * 64u * es);
-    T kb_b[2 * kKbStep];
+    T kb_b[kKbAhead];
     auto weight = [&](int e) {
         const unsigned o = unsigned(e - e_off[0]) * 64u * es;
         if constexpr (f32) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rW, unsigned(lane) * es, int(o), 0));
@@ -864,7 +866,7 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
         const int e0 = e_off[z], e1 = e_off[z + 1];
         if (e0 < e1) acc = kb_step(acc, e0, kb_b);
         if (e0 + kKbStep < e1) acc = kb_step(acc, e0 + kKbStep, kb_b + kKbStep);
-        for (int e = e0 + 2 * kKbStep; e < e1; e += kKbStep) {
+        for (int e = e0 + kKbAhead; e < e1; e += kKbStep) {
             T b[kKbStep];
 #pragma unroll
             for (int u = 0; u < kKbStep; ++u) b[u] = weight(e + u);
@@ -988,7 +990,7 @@ void build_row_groups(chf_ham* H, hipStream_t s) {
     const int64_t n_rg = H->grid.n_blocks * kGroups;
     std::vector<int32_t> off, len, slot;
     // (block, x-line pair, plane): the planes of a pair are consecutive
-    list_row_groups(P, n_rg, kRowGroup, kKbStep, kSlotBytes, [](int64_t rg) {
+    list_row_groups(P, n_rg, kRowGroup, kKbStep, kKbAhead, kSlotBytes, [](int64_t rg) {
         return rg / kGroups * kBlockPts + rg % 8 * 64 + rg / 8 % 4 * kRowGroup;
     }, off, len, slot);
     DevBuf dlen;

@@ -148,8 +148,10 @@ struct HostProj {
 void build_block_atoms(const HostGrid& g, HostProj& P);
 // per group of `rows` consecutive rows from first_row(group) on, the atom slots that
 // touch it times `scale`, ascending: offsets, counts, and the lists padded with 0
-// to a multiple of `step`
-void list_row_groups(const HostProj& P, int64_t n_groups, int rows, int step, int scale, int64_t (*first_row)(int64_t),
+// to a multiple of `step`; `ahead` more zeros follow the last list, for a reader that
+// fetches so many entries from where a list starts
+void list_row_groups(const HostProj& P, int64_t n_groups, int rows, int step, int ahead, int scale,
+                     int64_t (*first_row)(int64_t),
                      std::vector<int32_t>& off, std::vector<int32_t>& len, std::vector<int32_t>& slot);
 
 void build_projectors(const HostGrid& g, const chf_atoms& atoms, const chf_pp& pp, HostProj& out);
@@ -183,8 +185,8 @@ struct chf_ham {
     // row groups (16 rows) of the tiled kernel: the slots that touch each, as
     // LDS byte offsets, and their weights in MFMA operand order
     chf::DevBuf rg_off;         // int32 [32 n_blocks + 1]
-    chf::DevBuf rg_slot;        // int32 [entries]
-    chf::DevBuf rg_beta64, rg_beta32;  // [entries][64]
+    chf::DevBuf rg_slot;        // int32 [entries and 8 more]
+    chf::DevBuf rg_beta64, rg_beta32;  // [the same][64]
     chf::DevBuf blk_atom_off;   // int32 [n_blocks + 1]
     chf::DevBuf blk_atoms;      // int32 [sum of block atom counts]
     chf::DevBuf sup_beta64, ent_beta64;  // double [pairs][4]

@@ -140,6 +140,24 @@ static int run(double h, double radius, int ordering, int n_atoms, uint64_t seed
             }
         }
         EXPECT(P.max_block_atoms == max_na);
+        // the slots that touch each 16 rows of a block, as the tiled kernel lists them:
+        // in groups of 4, and from every list's start 8 entries can be read
+        std::vector<int32_t> off, len, slot;
+        const int64_t n_groups = g.n_blocks * 32;
+        list_row_groups(P, n_groups, 16, 4, 8, 512, [](int64_t q) { return q * 16; }, off, len, slot);
+        EXPECT(int64_t(off.size()) == n_groups + 1 && int64_t(len.size()) == n_groups);
+        for (int64_t q = 0; q < n_groups; ++q) {
+            std::vector<int32_t> seen;
+            for (int64_t e = P.ent_off[size_t(q * 16)]; e < P.ent_off[size_t((q + 1) * 16)]; ++e)
+                seen.push_back(512 * P.ent_slot[size_t(e)]);
+            std::sort(seen.begin(), seen.end());
+            seen.erase(std::unique(seen.begin(), seen.end()), seen.end());
+            EXPECT(int64_t(seen.size()) == len[size_t(q)]);
+            EXPECT(off[size_t(q) + 1] - off[size_t(q)] == (len[size_t(q)] + 3) / 4 * 4);
+            for (int i = 0; i < off[size_t(q) + 1] - off[size_t(q)]; ++i)
+                EXPECT(slot[size_t(off[size_t(q)] + i)] == (i < len[size_t(q)] ? seen[size_t(i)] : 0));
+            for (int i = 0; i < 8; ++i) EXPECT(size_t(off[size_t(q)] + i) < slot.size());
+        }
     }
     std::printf("h %.2f radius %.1f ordering %d: %lld points, %lld rows, %zu support entries\n", h, radius, ordering,
                 (long long)g.n, (long long)g.n_rows, P.sup_row.size());
