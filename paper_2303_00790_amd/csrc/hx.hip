@@ -729,8 +729,10 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
     const int lane = t & 63;
     constexpr unsigned es = sizeof(T);
     constexpr unsigned kOOB = 0x80000000u;
-    // bytes of a block from its first to its last vector: the second piece of a
-    // ragged row's last lane may lie past the row, but never past this
+    // bytes of a block from its first to its last vector.  The last 16 bytes of a
+    // ragged row's last lane may reach past the row (PB 8), of the block's last row
+    // past this; the range that holds for certain is that of the vector offset, so
+    // the last plane's offset is added to it.
     auto blk_bytes = [&](int64_t ld) { return (unsigned(kBlockPts - 1) * unsigned(ld) + unsigned(nvec)) * es; };
     const unsigned plane_x = 64u * unsigned(ldx) * es;
     const unsigned plane_z = 64u * unsigned(ldz) * es;
@@ -781,10 +783,15 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
         rH[u] = res_x(side == 0 ? nbs[0] : side == 1 ? nbs[1] : side == 2 ? nbs[2] : nbs[3]);
         hoff[u] = vok ? unsigned(lx + 8 * ly) * unsigned(ldx) * es + vbytes : kOOB;
     }
+    auto load = [](auto policy, __amdgpu_buffer_rsrc_t r, unsigned off, int z, unsigned plane) -> V {
+        constexpr int P = decltype(policy)::value;
+        const unsigned o = unsigned(z) * plane;
+        return PB == 8 && z == 7 ? bload16<V, P>(r, off + o, 0) : bload16<V, P>(r, off, o);
+    };
+    constexpr std::integral_constant<int, 0> often;
+    constexpr std::integral_constant<int, PB == 128 ? 2 : 0> once;
     auto load_plane = [&](int zz) -> V {
-        if (zz < 0) return bload16<V, 0>(rZm, off_x, unsigned(zz + 8) * plane_x);
-        if (zz >= 8) return bload16<V, 0>(rZp, off_x, unsigned(zz - 8) * plane_x);
-        return bload16<V, 0>(rOwn, off_x, unsigned(zz) * plane_x);
+        return load(often, zz < 0 ? rZm : zz >= 8 ? rZp : rOwn, off_x, zz & 7, plane_x);
     };
 
     // the X window of this column, the halos of plane 0, Y_{k-1} and V_eff
@@ -792,7 +799,7 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
 #pragma unroll
     for (int i = 0; i < 13; ++i) w[i] = load_plane(i - 6);
 #pragma unroll
-    for (int u = 0; u < 3; ++u) hv[u] = bload16<V, 0>(rH[u], hoff[u], 0u);
+    for (int u = 0; u < 3; ++u) hv[u] = load(often, rH[u], hoff[u], 0, plane_x);
 
     // KB coefficients of the block's atoms, alpha applied: 16 slots a round
     const int a0 = blk_atom_off[blk];
@@ -896,11 +903,11 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         // loads of this plane's update and of the next plane
-        const V zc = bload16<V, PB == 128 ? 2 : 0>(rZ, off_z, unsigned(z) * plane_z);   // zero without Z (empty buffer)
+        const V zc = load(once, rZ, off_z, z, plane_z);   // zero without Z (empty buffer)
         const T vr = veff[base + col + 64 * z];
         if (z < 7) {
 #pragma unroll
-            for (int u = 0; u < 3; ++u) hv[u] = bload16<V, 0>(rH[u], hoff[u], unsigned(z + 1) * plane_x);
+            for (int u = 0; u < 3; ++u) hv[u] = load(often, rH[u], hoff[u], z + 1, plane_x);
             w[z + 13] = load_plane(z + 7);
         }
 

@@ -399,3 +399,24 @@ def test_tile_order_covers_every_chunk(dtype, tol, radius, chunks):
     Hg.apply(Xg, Yg)
     assert relerr(Yg[rows].double().cpu().numpy(), Ho.apply(X)) < tol
     assert not bool(torch.isnan(Yg).any())
+
+
+@pytest.mark.parametrize("dtype,m", [(torch.float64, 17), (torch.float64, 31), (torch.float64, 33), (torch.float32, 34),
+                                     (torch.float32, 62), (torch.float32, 66)])
+def test_ragged_rows_that_end_with_their_memory(system, dtype, m):
+    # rows off 16 bytes with nothing between or behind them, where the last 16 bytes
+    # of a block's last row reach past the block: each vector has the bits that it
+    # has in rows of whole cache lines, with and without the third operand
+    s = system
+    X = random_block(s["g"].n, m, 3300 + m)
+    wide = to_rows(s, X, dtype, 128)
+    Y = torch.zeros_like(wide)
+    s["Hg"].apply(wide[:, :m], Y[:, :m])
+    tight = to_rows(s, X, dtype)
+    Z = torch.empty_like(tight)
+    s["Hg"].apply(tight, Z)
+    assert torch.equal(Z, Y[:, :m])
+    a, b, a0 = _bounds(s)
+    s["Hg"].filter(wide[:, :m], Y[:, :m], 4, a, b, a0)
+    s["Hg"].filter(tight, Z, 4, a, b, a0)
+    assert torch.equal(tight, wide[:, :m])
