@@ -974,17 +974,21 @@ __global__ void __launch_bounds__(64) rg_beta_kernel(const int32_t* __restrict__
                                                      const int32_t* __restrict__ rg_len,
                                                      const int32_t* __restrict__ ent_off,
                                                      const int32_t* __restrict__ ent_soff,
-                                                     const T* __restrict__ ent_beta, T* __restrict__ rg_beta) {
-    const int64_t rg = blockIdx.x;
+                                                     const T* __restrict__ ent_beta, T* __restrict__ rg_beta,
+                                                     int64_t n_rg) {
     const int lane = threadIdx.x;
-    const int64_t row = rg / kGroups * kBlockPts + rg % 8 * 64 + rg / 8 % 4 * kRowGroup + (lane & 15);
-    const int e0 = rg_off[rg], e1 = rg_off[rg + 1], n = rg_len[rg];
-    for (int e = e0; e < e1; ++e) {
-        T b = T(0);
-        if (e - e0 < n)
-            for (int en = ent_off[row]; en < ent_off[row + 1]; ++en)
-                if (ent_soff[en] == rg_slot[e]) b = ent_beta[4 * int64_t(en) + (lane >> 4)];
-        rg_beta[int64_t(e) * 64 + lane] = b;
+    // (in turns: a wave for each group of 2^30 rows would be 2^32 threads, which a
+    // launch does not hold)
+    for (int64_t rg = blockIdx.x; rg < n_rg; rg += gridDim.x) {
+        const int64_t row = rg / kGroups * kBlockPts + rg % 8 * 64 + rg / 8 % 4 * kRowGroup + (lane & 15);
+        const int e0 = rg_off[rg], e1 = rg_off[rg + 1], n = rg_len[rg];
+        for (int e = e0; e < e1; ++e) {
+            T b = T(0);
+            if (e - e0 < n)
+                for (int en = ent_off[row]; en < ent_off[row + 1]; ++en)
+                    if (ent_soff[en] == rg_slot[e]) b = ent_beta[4 * int64_t(en) + (lane >> 4)];
+            rg_beta[int64_t(e) * 64 + lane] = b;
+        }
     }
 }
 
@@ -1006,9 +1010,9 @@ void build_row_groups(chf_ham* H, hipStream_t s) {
     upload(dlen, len, s);
     auto fill = [&](auto* beta, const auto* src) {
         using T = std::remove_pointer_t<decltype(beta)>;
-        rg_beta_kernel<T><<<dim3(unsigned(n_rg)), dim3(64), 0, s>>>(H->rg_off.as<int32_t>(), H->rg_slot.as<int32_t>(),
-                                                                   dlen.as<int32_t>(), H->ent_off32.as<int32_t>(),
-                                                                   H->ent_soff.as<int32_t>(), src, beta);
+        rg_beta_kernel<T><<<dim3(unsigned(std::min<int64_t>(n_rg, 1 << 16))), dim3(64), 0, s>>>(
+            H->rg_off.as<int32_t>(), H->rg_slot.as<int32_t>(), dlen.as<int32_t>(), H->ent_off32.as<int32_t>(),
+            H->ent_soff.as<int32_t>(), src, beta, n_rg);
         LAUNCH_CHECK();
     };
     if (H->dtypes & 2) {
