@@ -556,7 +556,8 @@ __global__ void __launch_bounds__(512) cg_stencil_kernel(int n_blocks, int per_g
     }
 }
 
-// n is a multiple of 512 (Hilbert rows)
+// n is a multiple of 512 (Hilbert rows); x is the caller's and may start on any 8
+// bytes, the others are workspace on 16
 __global__ void __launch_bounds__(256) cg_update_kernel(int64_t n, int it, const double* __restrict__ p,
                                                         const double* __restrict__ ap, double* __restrict__ x,
                                                         double* __restrict__ r, const double* __restrict__ part_pap,
@@ -568,7 +569,7 @@ __global__ void __launch_bounds__(256) cg_update_kernel(int64_t n, int it, const
     auto load = [&](int64_t i) {
         pv = *reinterpret_cast<const double2*>(p + i);
         av = *reinterpret_cast<const double2*>(ap + i);
-        xv = *reinterpret_cast<const double2*>(x + i);
+        __builtin_memcpy(&xv, x + i, sizeof(xv));
         rv = *reinterpret_cast<const double2*>(r + i);
     };
     load(i0);                        // i0 < n: the grid has at most n / 512 workgroups
@@ -583,7 +584,7 @@ __global__ void __launch_bounds__(256) cg_update_kernel(int64_t n, int it, const
         xv.y = fma(a, pv.y, xv.y);
         rv.x = fma(-a, av.x, rv.x);
         rv.y = fma(-a, av.y, rv.y);
-        *reinterpret_cast<double2*>(x + i) = xv;
+        __builtin_memcpy(x + i, &xv, sizeof(xv));
         *reinterpret_cast<double2*>(r + i) = rv;
         s += rv.x * rv.x;
         s += rv.y * rv.y;

@@ -282,3 +282,19 @@ def test_run_writes_one_json_record_per_step(tmp_path):
         assert r["seconds"] > 0 and math.isfinite(r["energy"]) and r["sre_ry"] > 0
         assert r["chfsi_iters"] == (4 if r["step"] == 1 else 1)
         assert r["bound_a0"] < r["bound_a"] < r["bound_b"]
+
+
+def test_hartree_of_vectors_on_any_8_bytes(si35):
+    # the potential and the density start in the middle of 16 bytes: the same bits
+    s = si35
+    n = s["Hg"].n_rows
+    rho = s["Hg"].sad_density(s["c"].pos, s["c"].species, s["c"].n_electrons)
+    vh = torch.zeros(n, dtype=torch.float64, device="cuda")
+    it = s["Hg"].hartree(s["ctx"], rho, vh, 1e-12)
+    off = torch.full((2, n + 2), -7.0, dtype=torch.float64, device="cuda")
+    off[0, 1:n + 1] = rho
+    off[1, 1:n + 1] = 0.0
+    assert off[1, 1:].data_ptr() % 16 == 8
+    assert s["Hg"].hartree(s["ctx"], off[0, 1:n + 1], off[1, 1:n + 1], 1e-12) == it
+    assert torch.equal(off[1, 1:n + 1], vh)
+    assert float(off[1, 0]) == -7.0 and float(off[1, n + 1]) == -7.0
