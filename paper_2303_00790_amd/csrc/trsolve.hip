@@ -453,8 +453,10 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
                 }
             }
         }
-        // X_j - sum, turned from the result layout to the operand layout; columns
-        // past the end count as zero
+        // X_j - sum, turned from the result layout to the operand layout of ascending
+        // k (column 4 e + kq of a group lies at N kq + e); columns past the end count as
+        // zero
+        const int place = l / KG * KG + l % 4 * N + l % KG / 4;
         Piece16<T> v[RT][CT][G];
 #pragma unroll
         for (int q = 0; q < CT; ++q) {
@@ -467,15 +469,14 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
                     T x;
                     if constexpr (APART) x = own[p][q][reg];
                     else x = acc[p][q][reg];
-                    tw[(p * 16 + result_row<T>(reg, lane)) * LP + l] = in ? x : T(0);
+                    tw[(p * 16 + result_row<T>(reg, lane)) * LP + place] = in ? x : T(0);
                 }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
             for (int p = 0; p < RT; ++p)
 #pragma unroll
                 for (int g = 0; g < G; ++g)
-#pragma unroll
-                    for (int e = 0; e < N; ++e) v[p][q][g].e[e] = tw[(p * 16 + l) * LP + g * KG + 4 * e + kq];
+                    v[p][q][g] = *reinterpret_cast<const Piece16<T>*>(tw + (p * 16 + l) * LP + g * KG + N * kq);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
         // times the inverse of R_jj
