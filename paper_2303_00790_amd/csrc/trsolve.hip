@@ -495,7 +495,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
         for (int q = 0; q < CT; ++q) {
             if (16 * q >= w) continue;
             if (D == 1) fetch_z(0, q);
-            else if (q + 1 < CT) fetch_z((q + 1) % D, q + 1);
+            else if (q + 1 < CT && 16 * (q + 1) < w) fetch_z((q + 1) % D, q + 1);
             Acc<T> r[RT];
 #pragma unroll
             for (int p = 0; p < RT; ++p) r[p] = Acc<T>{0, 0, 0, 0};
