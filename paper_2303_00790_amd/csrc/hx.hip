@@ -18,9 +18,9 @@
 //                     LDS, the KB term as MFMA products inside the march.
 //  * hx_narrow        the same operator for one row piece of at most 16 bytes
 //                     (1 or 2 FP64, 2 or 4 FP32 vectors), one thread per point.
-//  * hx_tiled         a tile of the same shape without staging, for blocks touched by
-//                     more than kMaxBlockAtoms projector atoms, Laplacian-only
-//                     products and Hamiltonians without projectors.
+//  * hx_tiled         a tile of the same shape without staging, for Hamiltonians
+//                     with a block touched by more than kMaxBlockAtoms projector
+//                     atoms and those without projectors.
 #include <atomic>
 #include <cmath>
 #include <mutex>
@@ -215,20 +215,6 @@ void launch_hx_generic(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, c
 }
 
 // ---------------------------------------------------------------------------
-// Hilbert-blocked tiled H X (hx_tiled_kernel below)
-//
-// One workgroup per tile = one 8^3 block x one 128-byte vector chunk (32 FP32
-// or 16 FP64 vectors): 1024 threads = 64 columns (x, y) x 16 lanes of 8
-// bytes.  Each thread keeps X(x, y, z-6 .. z+13) of its column and lane in
-// registers and marches z = 0..7; the x/y neighbours of plane z (the plane
-// plus its 6-deep halos from the -x/+x/-y/+y neighbour blocks) are staged in
-// LDS as a 20 x 20 square, double-buffered so that one barrier per plane
-// suffices.  The KB term of each row is applied in the march from the
-// block's staged coefficients; the Chebyshev update is fused into the store.
-// Rows outside the sphere are stored as zero; on input they must hold zero
-// (the layout contract), so they enter the stencil as the zero boundary.
-// ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // KB gather: C[a][lm][v] = sum_j (h^3 beta_alm(row_j)) X[row_j][v]
 //
 // One workgroup per (projector atom, chunk of QL pieces of QN vectors).  The
@@ -417,13 +403,17 @@ __device__ inline void bstore(V v, __amdgpu_buffer_rsrc_t r, unsigned off) {
 }
 
 // Unstaged tile kernel: one workgroup per tile (one 8^3 block x one 128-byte
-// vector chunk), 1024 threads = 64 columns x 16 lanes; a lane holds 8 bytes
-// (2 floats or 1 double) of the chunk.  It serves the blocks the staged tile
-// kernel below cannot take (more than kMaxBlockAtoms projector atoms touch
-// the block), the Laplacian-only products of the Poisson solver and
-// Hamiltonians without projectors: the stencil is applied in a z-march, the
-// eight output rows wait in registers, and the KB term is added after the
-// march from the coefficients in global memory.
+// vector chunk), 1024 threads = 64 columns (x, y) x 16 lanes; a lane holds 8
+// bytes (2 floats or 1 double) of the chunk.  It serves the Hamiltonians that the
+// staged tile kernel below does not take: with a block touched by more than
+// kMaxBlockAtoms projector atoms, and without projectors.  Each thread keeps
+// X(x, y, z-6 .. z+13) of its column and lane in registers and marches z = 0..7; the
+// x/y neighbours of plane z (the plane and its 6-deep halos from the -x/+x/-y/+y
+// blocks) are staged in LDS as a 20 x 20 square, double-buffered so that one
+// barrier per plane suffices.  The eight output rows wait in registers, and the KB
+// term is added after the march from the coefficients in global memory.  Rows
+// outside the sphere are stored as zero; on input they must hold zero (the layout
+// contract), so they enter the stencil as the zero boundary.
 constexpr int kMaxBlockAtoms = 64;
 constexpr int kLanes = 16;
 
@@ -549,7 +539,7 @@ __global__ void __launch_bounds__(64 * kLanes) hx_tiled_kernel(int64_t n_blocks,
     const __amdgpu_buffer_rsrc_t rY = make_rsrc(Y + base * ldy, unsigned(kBlockPts) * unsigned(ldy) * es);
     const unsigned off_y = vok ? (unsigned(lrow) * unsigned(ldy) + unsigned(vbase)) * es : kOOB;
     V r[8];
-    const T* vr = veff ? veff + base : nullptr;
+    const T* vr = veff + base;
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         const int b = z & 1;
@@ -576,7 +566,7 @@ __global__ void __launch_bounds__(64 * kLanes) hx_tiled_kernel(int64_t n_blocks,
             acc = lfma(k.c[s], sum, acc);
         }
         const V xc = w[z + 6];
-        if (vr) acc = lfma(vr[lrow + 64 * z], xc, acc);
+        acc = lfma(vr[lrow + 64 * z], xc, acc);
         V y = lscale(k.alpha, lfma(-k.shift, xc, acc));
         if (Z) y = lfma(-k.beta, zcur, y);
         r[z] = y;
@@ -1046,8 +1036,8 @@ static void launch_tile(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, 
 
 template <class T>
 void launch_hx_tiled(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec,
-                     const T* C, double alpha, double shift, double beta, hipStream_t s, bool lap_only) {
-    const bool kb = !lap_only && H->proj.n_proj > 0;
+                     const T* C, double alpha, double shift, double beta, hipStream_t s) {
+    const bool kb = H->proj.n_proj > 0;
     const StepCoef<T> coef = make_coef<T>(H, alpha, shift, beta);
     if (kb && H->proj.max_block_atoms <= kMaxBlockAtoms) {
         // rows of whole cache lines or of 16-byte pieces where widths, leading
@@ -1072,9 +1062,8 @@ void launch_hx_tiled(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, con
     const int64_t nt = H->grid.n_blocks * int64_t(n_chunks);
     const dim3 grid(unsigned(((nt + 7) / 8) * 8)), block(64 * kLanes);
     const int32_t* eo = kb ? H->ent_off32.as<int32_t>() : nullptr;
-    const T* veff = lap_only ? nullptr : veff_of<T>(H);
     hx_tiled_kernel<T><<<grid, block, 0, s>>>(H->grid.n_blocks, n_chunks, H->block_nbr.as<int32_t>(),
-                                             H->block_mask.as<uint64_t>(), veff, eo, H->ent_atom.as<int32_t>(),
+                                             H->block_mask.as<uint64_t>(), veff_of<T>(H), eo, H->ent_atom.as<int32_t>(),
                                              ent_beta_of<T>(H), C, nvec, X, ldx, Y, ldy, Z, ldz, coef);
     LAUNCH_CHECK();
 }
@@ -1365,11 +1354,11 @@ void hx_step(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z,
         else timed(which, s, launch);
     };
     if (H->proj.n_proj > 0 && !lap_only) run(1, [&] { launch_kb_gather<T>(H, X, ldx, nvec, C, s); });
-    const bool tiled = force_kernel != 1 && tiled_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec);
-    if (tiled && narrow && !lap_only && narrow_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec)) {
+    const bool tiled = force_kernel != 1 && !lap_only && tiled_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec);
+    if (tiled && narrow && narrow_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec)) {
         run(0, [&] { launch_narrow<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, nullptr, s); });
     } else if (tiled) {
-        run(0, [&] { launch_hx_tiled<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, s, lap_only); });
+        run(0, [&] { launch_hx_tiled<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, s); });
     } else {
         if (!H->has_nbr) fail(CHF_EUNSUPPORTED, "generic H X needs the neighbour table (keep_nbr) for this layout");
         run(0, [&] { launch_hx_generic<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, s, lap_only); });

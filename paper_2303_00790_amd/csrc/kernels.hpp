@@ -14,7 +14,7 @@ template <class T>
 void launch_kb_gather(chf_ham* H, const T* X, int64_t ldx, int nvec, T* C, hipStream_t s);
 // Y = alpha (H X - shift X) - beta Z ; Z may be null or alias Y.  force_kernel:
 // 0 = best available, 1 = generic neighbour-table kernel.  lap_only: H is
-// replaced by -1/2 L (no V_eff, no projectors).
+// replaced by -1/2 L (no V_eff, no projectors), by the neighbour-table kernel.
 // C_ext: caller-provided KB-coefficient scratch for nvec vectors (no
 // allocation, no kernel timing); NULL uses the handle's scratch.  narrow: a
 // block of one row piece of 8 or 16 bytes may take the one-thread-per-point
@@ -42,7 +42,8 @@ void noalloc_scratch_init(int device);
 template <class T>
 void filter_run_noalloc(chf_ham* H, T* X, int64_t ldx, T* W, int64_t ldw, int nvec, int m, double a, double b,
                         double a0, hipStream_t s);
-// CHF_EINVAL unless the [n_rows][ld] spans of A and B are disjoint (capi.cpp)
+// CHF_EINVAL unless the bytes, or the [n_rows][ld] spans, of A and B are disjoint
+// (capi.cpp)
 void check_disjoint(const void* A, size_t bytes_a, const void* B, size_t bytes_b, const char* what);
 void check_disjoint(const chf_ham* H, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                     const char* what);
