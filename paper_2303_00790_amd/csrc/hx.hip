@@ -1126,7 +1126,13 @@ __global__ void __launch_bounds__(512) hx_narrow_kernel(int n_blocks, int per_gr
     V zero;
 #pragma unroll
     for (int e = 0; e < N; ++e) zero.e[e] = T(0);
-    auto load = [&](int64_t r) { return *reinterpret_cast<const V*>(X + r * ldx); };
+    // (rows may start on any element)
+    auto piece = [](const T* p) {
+        V v;
+        __builtin_memcpy(&v, p, sizeof(V));
+        return v;
+    };
+    auto load = [&](int64_t r) { return piece(X + r * ldx); };
     double dot = 0.0;
     for (int blk = first; blk < last; ++blk) {
         const int64_t base = int64_t(blk) * kBlockPts;
@@ -1140,7 +1146,7 @@ __global__ void __launch_bounds__(512) hx_narrow_kernel(int n_blocks, int per_gr
             const int nb = bnb[6 * int64_t(blk) + item / 6];
             if (nb >= 0) hv[j] = load(int64_t(nb) * kBlockPts + row[j]);
         }
-        const V zv = Z ? *reinterpret_cast<const V*>(Z + (base + t) * ldz) : zero;
+        const V zv = Z ? piece(Z + (base + t) * ldz) : zero;
         const T vr = veff[base + t];
         int e0 = 0, e1 = 0, na = 0, a0 = 0;
         V cv = zero;
@@ -1211,7 +1217,7 @@ __global__ void __launch_bounds__(512) hx_narrow_kernel(int n_blocks, int per_gr
             const T r = fma(-k.beta, zv.e[e], fma(dg, v.e[e], fma(k.alpha, kb.e[e], acc.e[e])));
             out.e[e] = in ? r : T(0);
         }
-        *reinterpret_cast<V*>(Y + (base + t) * ldy) = out;
+        __builtin_memcpy(Y + (base + t) * ldy, &out, sizeof(V));
         dot += double(v.e[0]) * double(out.e[0]);
     }
     if (part) {
@@ -1220,16 +1226,13 @@ __global__ void __launch_bounds__(512) hx_narrow_kernel(int n_blocks, int per_gr
     }
 }
 
-// whether a block of nvec vectors is one row piece that the kernel can load,
-// on a handle with the tables it reads
+// whether a block of nvec vectors is one row piece, on a handle with the tables
+// that the kernel reads.  The rule is the width alone, so that a filter that goes
+// through its columns one by one has the arithmetic of one that takes them at once.
 template <class T>
-static bool narrow_ok(const chf_ham* H, const void* X, int64_t ldx, const void* Y, int64_t ldy, const void* Z, int64_t ldz,
-                      int nvec) {
+static bool narrow_ok(const chf_ham* H, int nvec) {
     const int64_t bytes = int64_t(nvec) * int64_t(sizeof(T));
-    if (H->grid.ordering != CHF_ORDER_HILBERT || H->proj.max_block_atoms > kMaxBlockAtoms) return false;
-    if (bytes != 8 && bytes != 16) return false;
-    return ldx % nvec == 0 && ldy % nvec == 0 && (!Z || ldz % nvec == 0) && uintptr_t(X) % bytes == 0 &&
-           uintptr_t(Y) % bytes == 0 && uintptr_t(Z) % bytes == 0;
+    return H->grid.ordering == CHF_ORDER_HILBERT && H->proj.max_block_atoms <= kMaxBlockAtoms && (bytes == 8 || bytes == 16);
 }
 
 // launches it and returns the number of workgroups (= partials)
@@ -1355,7 +1358,7 @@ void hx_step(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z,
     };
     if (H->proj.n_proj > 0 && !lap_only) run(1, [&] { launch_kb_gather<T>(H, X, ldx, nvec, C, s); });
     const bool tiled = force_kernel != 1 && !lap_only && tiled_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec);
-    if (tiled && narrow && narrow_ok<T>(H, X, ldx, Y, ldy, Z, ldz, nvec)) {
+    if (tiled && narrow && narrow_ok<T>(H, nvec)) {
         run(0, [&] { launch_narrow<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, nullptr, s); });
     } else if (tiled) {
         run(0, [&] { launch_hx_tiled<T>(H, X, ldx, Y, ldy, Z, ldz, nvec, C, alpha, shift, beta, s); });

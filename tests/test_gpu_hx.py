@@ -420,3 +420,23 @@ def test_ragged_rows_that_end_with_their_memory(system, dtype, m):
     s["Hg"].filter(wide[:, :m], Y[:, :m], 4, a, b, a0)
     s["Hg"].filter(tight, Z, 4, a, b, a0)
     assert torch.equal(tight, wide[:, :m])
+
+
+@pytest.mark.parametrize("dtype,m", [(torch.float64, 2), (torch.float32, 4)])
+def test_filter_of_one_row_piece_off_its_alignment(system, dtype, m):
+    # columns of a wider block that start in the middle of 16 bytes: half of them at
+    # a time give the same bits, and those of an aligned block
+    s = system
+    a, b, a0 = _bounds(s)
+    X = random_block(s["g"].n, m, 3120 + m)
+    out = []
+    for ld, c0, w in ((m, 0, m), (3 * m, m // 2, m), (3 * m, m // 2, m // 2)):
+        Xg = torch.zeros((s["Hg"].n_rows, ld), dtype=dtype, device="cuda")
+        Xg[:, c0:c0 + m] = to_rows(s, X, dtype)
+        assert Xg[:, c0:].data_ptr() % 16 == (0 if c0 == 0 else 8)
+        W = torch.empty((s["Hg"].n_rows, w), dtype=dtype, device="cuda")
+        s["Hg"].filter(Xg[:, c0:c0 + m], W, 6, a, b, a0)
+        out.append(Xg[:, c0:c0 + m].clone())
+        Xg[:, c0:c0 + m] = 0
+        assert float(Xg.abs().max()) == 0.0
+    assert torch.equal(out[1], out[0]) and torch.equal(out[2], out[0])
