@@ -22,22 +22,24 @@ namespace chf {
 constexpr double kPi = 3.14159265358979323846;
 
 // ---------------------------------------------------------------------------
-// density: rho[row] = (2 / h^3) sum_{i < n_occ} X[row][i]^2, one wave per row
+// density: rho[row] = (2 / h^3) sum_{i < n_occ} X[row][i]^2, one wave per row, rows
+// in turns (a wave for each of 2^26 rows would be 2^32 threads, more than a launch
+// holds)
 // ---------------------------------------------------------------------------
 template <class T>
 __global__ void __launch_bounds__(256) density_kernel(int64_t n_rows, const T* __restrict__ X, int64_t ldx, int n_occ,
                                                       double scale, double* __restrict__ rho) {
-    const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (row >= n_rows) return;
-    const T* xr = X + row * ldx;
-    double acc = 0.0;
-    for (int i = lane; i < n_occ; i += 64) {
-        const double v = double(xr[i]);
-        acc += v * v;
+    for (int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6); row < n_rows; row += int64_t(gridDim.x) * 4) {
+        const T* xr = X + row * ldx;
+        double acc = 0.0;
+        for (int i = lane; i < n_occ; i += 64) {
+            const double v = double(xr[i]);
+            acc += v * v;
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) rho[row] = scale * acc;
     }
-    acc = wave_sum(acc);
-    if (lane == 0) rho[row] = scale * acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -742,7 +744,7 @@ template <class T>
 void density_t(chf_ham* H, const T* X, int64_t ldx, int n_occ, double* rho, hipStream_t s) {
     const int64_t n = H->grid.n_rows;
     const double h = H->h;
-    density_kernel<T><<<unsigned((n + 3) / 4), 256, 0, s>>>(n, X, ldx, n_occ, 2.0 / (h * h * h), rho);
+    density_kernel<T><<<unsigned(std::min<int64_t>((n + 3) / 4, 1 << 22)), 256, 0, s>>>(n, X, ldx, n_occ, 2.0 / (h * h * h), rho);
     LAUNCH_CHECK();
 }
 

@@ -298,3 +298,15 @@ def test_hartree_of_vectors_on_any_8_bytes(si35):
     assert s["Hg"].hartree(s["ctx"], off[0, 1:n + 1], off[1, 1:n + 1], 1e-12) == it
     assert torch.equal(off[1, 1:n + 1], vh)
     assert float(off[1, 0]) == -7.0 and float(off[1, n + 1]) == -7.0
+
+
+def test_density_of_more_than_2_26_rows():
+    # a sphere of 71,373,824 rows: every row's density is written
+    from paper_2303_00790_amd import binding as B
+    from synth.workloads import MODEL_PP
+    H = B.Hamiltonian(np.zeros((1, 3)), np.array([1], np.int32), MODEL_PP, 0.7, 176.5, B.ORDER_HILBERT, dtypes=1)
+    assert H.n_rows > 1 << 26
+    X = torch.rand((H.n_rows, 1), dtype=torch.float32, device="cuda")
+    rho = torch.full((H.n_rows,), float("nan"), dtype=torch.float64, device="cuda")
+    H.density(X, 1, rho)
+    assert bool(torch.allclose(rho, 2.0 / 0.7 ** 3 * X[:, 0].double() ** 2, rtol=1e-14, atol=0.0))
