@@ -119,7 +119,7 @@ struct StepCoef {
 };
 
 template <class T>
-__global__ void __launch_bounds__(256) hx_generic_kernel(int64_t n_rows, int nvec, int nvc,
+__global__ void __launch_bounds__(256) hx_generic_kernel(int64_t row0, int64_t n_rows, int nvec, int nvc,
                                                          const int32_t* __restrict__ nbr,
                                                          const uint8_t* __restrict__ inside,
                                                          const T* __restrict__ veff,
@@ -129,8 +129,8 @@ __global__ void __launch_bounds__(256) hx_generic_kernel(int64_t n_rows, int nve
                                                          const T* __restrict__ X, int64_t ldx, T* Y, int64_t ldy,
                                                          const T* Z, int64_t ldz, StepCoef<T> k) {
     const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t row = gid / nvc;
-    const int vc = int(gid - row * nvc);
+    const int64_t r = gid / nvc, row = row0 + r;
+    const int vc = int(gid - r * nvc);
     if (row >= n_rows) return;
     constexpr int VPT = 4;
     const int v0 = vc * VPT;
@@ -205,13 +205,17 @@ template <class T>
 void launch_hx_generic(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, int nvec,
                        const T* C, double alpha, double shift, double beta, hipStream_t s, bool lap_only) {
     const int nvc = (nvec + 3) / 4;
-    const int64_t total = H->grid.n_rows * nvc;
-    hx_generic_kernel<T><<<dim3(unsigned((total + 255) / 256)), dim3(256), 0, s>>>(
-        H->grid.n_rows, nvec, nvc, H->nbr_rows.as<int32_t>(), H->row_inside.as<uint8_t>(),
-        lap_only ? nullptr : veff_of<T>(H), lap_only ? nullptr : H->ent_off.as<int64_t>(), H->ent_atom.as<int32_t>(),
-        ent_beta_of<T>(H), C, X, ldx, Y, ldy, Z, ldz,
-        make_coef<T>(H, alpha, shift, beta));
-    LAUNCH_CHECK();
+    // (a launch holds fewer than 2^32 threads: runs of rows of at most half of that)
+    const int64_t n = H->grid.n_rows, run = std::max<int64_t>(1, (int64_t(1) << 31) / nvc);
+    for (int64_t row0 = 0; row0 < n; row0 += run) {
+        const int64_t end = std::min(n, row0 + run), total = (end - row0) * nvc;
+        hx_generic_kernel<T><<<dim3(unsigned((total + 255) / 256)), dim3(256), 0, s>>>(
+            row0, end, nvec, nvc, H->nbr_rows.as<int32_t>(), H->row_inside.as<uint8_t>(),
+            lap_only ? nullptr : veff_of<T>(H), lap_only ? nullptr : H->ent_off.as<int64_t>(),
+            H->ent_atom.as<int32_t>(), ent_beta_of<T>(H), C, X, ldx, Y, ldy, Z, ldz,
+            make_coef<T>(H, alpha, shift, beta));
+        LAUNCH_CHECK();
+    }
 }
 
 // ---------------------------------------------------------------------------

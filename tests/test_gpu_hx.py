@@ -440,3 +440,25 @@ def test_filter_of_one_row_piece_off_its_alignment(system, dtype, m):
         Xg[:, c0:c0 + m] = 0
         assert float(Xg.abs().max()) == 0.0
     assert torch.equal(out[1], out[0]) and torch.equal(out[2], out[0])
+
+
+def test_neighbour_table_kernel_of_more_than_2_32_threads():
+    # 33 rows and so many vectors that a thread for every 4 values of a row would be
+    # more than a launch holds: every value is written, the last vectors with the bits
+    # that they have alone
+    from paper_2303_00790_amd import binding as B
+    H = B.Hamiltonian(np.zeros((1, 3)), np.array([1], np.int32), OH.PseudoParams(), 0.7, 1.5, B.ORDER_LEX, dtypes=1)
+    m = 4 * ((1 << 32) // H.n_rows + 1)
+    X = torch.zeros((H.n_rows, m), dtype=torch.float32, device="cuda")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(13)
+    X[:, -8:] = torch.randn((H.n_rows, 8), generator=gen, dtype=torch.float32, device="cuda")
+    Y = torch.full_like(X, float("nan"))
+    H.apply(X, Y)
+    last = X[:, -8:].contiguous()
+    alone = torch.empty_like(last)
+    H.apply(last, alone)
+    assert torch.equal(Y[:, -8:], alone)
+    assert all(not bool(torch.isnan(y.sum())) for y in Y[:, :-8])
+    del X, Y
+    torch.cuda.empty_cache()
