@@ -188,8 +188,9 @@ static int guard(F&& f) {
     }
 }
 
-// S (row-major M x M, FP64) lives at the start of ctx->scratch; the rest holds
-// the cast factor for FP32 updates and rocSOLVER's info word.
+// S (row-major M x M, FP64) lives at the start of ctx->scratch; behind it lie M x M
+// FP32 values (Q of an FP32 block wider than the rotation in place takes) and the
+// status word of the factorisation or the eigensolver, then the extras below.
 static size_t mm_tail(int m) { return (size_t(m) * m * (sizeof(double) + sizeof(float)) + 256 + 255) / 256 * 256; }
 static size_t mm_scratch_bytes(int m, size_t extra_bytes) { return mm_tail(m) + extra_bytes; }
 static double* mm_scratch(chf_ctx* ctx, int m, size_t extra_bytes) {

@@ -651,8 +651,13 @@ constexpr int kRowGroup = 16;        // rows of a KB weight matrix
 constexpr int kGroups = kBlockPts / kRowGroup;
 constexpr int kKbStep = 4;           // a group's atom list is padded to this multiple
 constexpr int kKbAhead = 2 * kKbStep;  // entries of a plane whose weights are fetched ahead
-// slots of the half-LDS variant; blocks touched by more atoms take the one
-// with kMaxBlockAtoms slots, one workgroup per CU
+// slots of the half-LDS variant (the 1.1 to 5 nm Si clusters have at most 23 atoms to
+// a block); a Hamiltonian with a block touched by more takes the one with
+// kMaxBlockAtoms slots, one workgroup per CU.  An H X with up to 56 atoms to a block
+// (256 Si in a sphere of 18 bohr), one 1024-thread workgroup that adds entry by entry
+// -> this variant: 128 FP64 vectors 287 -> 208 us, 97 323 -> 207, 16 153 -> 43, 256
+// FP32 292 -> 190; with up to 37 atoms (203 Si), two workgroups: 284 -> 156, 321 ->
+// 159, 153 -> 38, 287 -> 146.
 constexpr int kFewSlots = 40;
 // a row's 16-byte pieces lie kKbPitch apart in the KB plane: 16 rows and 32
 // bytes, so that the 8 pieces of two rows fall on different banks
@@ -988,7 +993,10 @@ __global__ void __launch_bounds__(64) rg_beta_kernel(const int32_t* __restrict__
 
 // Row-group lists of the staged tile kernel (Hilbert layout, blocks of at most
 // kMaxBlockAtoms atoms): per group the LDS offsets of the slots whose atoms
-// touch it, and their weights.  Built from the entry tables at ham_build.
+// touch it, and their weights, 256 (FP32) or 512 bytes an entry, kept as long as the
+// handle.  Si clusters have 5.3 entries to a group that has any, 6.9 with the
+// padding: 40 MB (FP32) and 80 MB (FP64) at 3 nm, 176 and 352 MB at 5 nm, 5.9 and
+// 11.7 GB at 16 nm.  Built from the entry tables at ham_build.
 void build_row_groups(chf_ham* H, hipStream_t s) {
     const HostProj& P = H->proj;
     if (H->grid.ordering != CHF_ORDER_HILBERT || P.n_proj == 0 || P.max_block_atoms > kMaxBlockAtoms) return;

@@ -11,9 +11,9 @@
 // more than the L1 holds until the other halves are wanted.
 //
 // Measured against the library's triangular solve (ms): 440,000 x 1024 FP32
-// 6.6 -> 4.8, 440,000 x 600 FP64 5.9 -> 3.3, 120,000 x 128 FP64 0.15 -> 0.066.
+// 5.8 -> 4.7, 440,000 x 600 FP64 6.1 -> 3.5, 120,000 x 128 FP64 0.17 -> 0.068.
 // Bound by the matrix cores: 64 FP32 (32 FP64) products, 2048 cycles, per 10
-// loads of 1 KB.  32 x 128 because the rows' earlier panels, too many to stay in
+// loads of 1 KB.  128 columns because the rows' earlier panels, too many to stay in
 // an L2, are read again for each panel: (M / 128 - 1) / 2 times in all.
 #include <algorithm>
 
@@ -61,8 +61,9 @@ __device__ inline Piece16<T> load16(const T* p) {
 // where the other operand comes from memory, whose pieces lie along k.  The
 // inverses take k = g KG + 4 e + l / 16 instead, so that the products add k in
 // ascending order and the largest term, the diagonal's, last: out of order the
-// sums after it round at its size (FP64, 128 columns: 1.11 against 1.05 eps beside
-// the columns' common factors, 1.05 for the library).
+// sums after it round at its size (FP64, 128 columns, in units of 2^-53 beside the
+// columns' common factors: 1.11 against 1.05, the library 1.05; the whole error of 97
+// FP32 columns with an FP64 Gram, in units of 2^-24: 0.97 against 0.74, library 0.92).
 template <class T>
 struct Packed {
     static constexpr int N = Piece16<T>::N, KG = 4 * N, V = 64 * N;
@@ -155,8 +156,8 @@ __device__ inline void invert_upper(double* M, int w) {
 // multiplied by the inverse (chol_panel_kernel) and what is right of them updated
 // (chol_update_kernel).  Bound by the chain of pivots: 16 x 16 blocks by one wave
 // in registers, their rows by substitution, the rest of the square on the matrix
-// cores: 69 us a block, and 10 + 8 .. 20 for the other two (the library's
-// factorisation: 215 us at M = 128, 1.4 ms at 1024, now 69 us and 0.75 ms, the
+// cores: 72 us a block, and 11 + 8 .. 20 for the other two (the library's
+// factorisation: 240 us at M = 128, 2.6 ms at 1024, now 72 us and 0.85 ms, the
 // inverses of the solve included).  *info: 1 + the first column whose pivot is not positive, if it was 0.
 // Z, W: the inverse in operand order of T and FP64 (W null: Z is that).
 template <class T>
@@ -351,8 +352,8 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
     // The products are summed over kTriBlock of k at a time, from zero, and the sums
     // taken from the panel one after the other, as the blocked solve of a library
     // does: one chain over all k rounds m times at the size of the whole (error at
-    // 600 columns, FP32, 1.3e-6, in blocks 0.8e-6; columns 384 to 400 of 400, FP64,
-    // 8.6 and 2.0 eps).  With FP64 blocks of one panel there are no products, and
+    // 600 columns, FP32, 1.3e-6, in blocks 0.8e-6; columns 384 to 400 of 400, FP64, in
+    // units of 2^-53: 8.6 and 2.0).  With FP64 blocks of one panel there are no products, and
     // the panel is kept where they would be added.
     constexpr bool APART = sizeof(T) == 4 || RT == 1;
     Acc<T> acc[RT][CT], own[APART ? RT : 1][APART ? CT : 1];
@@ -378,7 +379,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 ? 2 : 1) solve_upper_kerne
         // two sets of operands: one is multiplied while the other is loaded; of X
         // two groups at a time, whole cache lines of its rows.  FP32: the order is
         // kept and the sums stay in accumulation registers, one wave per SIMD
-        // (4.8 ms at 440,000 x 1024; 5.2 as the compiler orders it for two waves).
+        // (4.7 ms at 440,000 x 1024; 5.1 as the compiler orders it for two waves).
         // FP64: two waves, whose products are long enough to cover the loads;
         // the sums apart leave them registers for 16 rows each (3.5 ms at 440,000 x
         // 600; 32 rows and one wave 3.8).
