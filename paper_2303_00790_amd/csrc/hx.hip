@@ -629,7 +629,10 @@ __global__ void __launch_bounds__(64 * kLanes) hx_tiled_kernel(int64_t n_blocks,
 // order, the 4 x 16 coefficients are read from LDS, and one 16x16x4 MFMA (FP32
 // or FP64, full precision) adds the atom.  The product is transposed (rows of
 // the result = vectors), so a lane ends up with 4 vectors of one row; it goes
-// through LDS to the lanes that hold that row.
+// through LDS to the lanes that hold that row.  Coefficients that are Inf or NaN
+// would reach rows through zero weights; they are kept out of the products and
+// added entry by entry after the march (5 nm, 256 FP32 vectors of which all are Inf
+// or NaN: 2.4 -> 8.8 ms; others: no change).
 //
 // The plane is single-buffered (two barriers per plane), which keeps a
 // workgroup within half of the 160 KB of LDS and its threads within 128
@@ -694,19 +697,27 @@ __device__ inline V bload16(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned so
     return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, voff, int(soff), POLICY));
 }
 
+// tables that the tile kernel needs only for coefficients that are Inf or NaN
+template <class T>
+struct TileRare {
+    const int32_t *ent_off, *ent_soff, *blk_atom_off, *blk_atoms;
+    const T* ent_beta;
+};
+
 template <class T, int PB, int SLOTS>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SLOTS <= kFewSlots ? 4 : 2)))
 hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict__ bnb, const uint64_t* __restrict__ bmask,
                const T* __restrict__ veff, const int32_t* __restrict__ rg_off, const int32_t* __restrict__ rg_slot,
                const T* __restrict__ rg_beta, const int32_t* __restrict__ blk_atom_off,
                const int32_t* __restrict__ blk_atoms, const T* __restrict__ C, int nvec, const T* __restrict__ X,
-               int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, StepCoef<T> k) {
+               int64_t ldx, T* Y, int64_t ldy, const T* Z, int64_t ldz, const TileRare<T>* rare, StepCoef<T> k) {
     constexpr int N = Wide<T>::N;
     using V = Piece<T, N>;
     using A = typename Wide<T>::A;
     constexpr int CH = 8 * N;                 // vectors of a chunk
     constexpr bool f32 = sizeof(T) == 4;
     __shared__ __align__(16) char lds[SLOTS * kSlotBytes + kPlaneBytes + kKbBytes];
+    __shared__ int odd[8];                    // whether a wave staged a coefficient that is Inf or NaN
     char* const lds_kb = lds + SLOTS * kSlotBytes;
     V (*plane)[8] = reinterpret_cast<V (*)[8]>(lds + SLOTS * kSlotBytes + kKbBytes);
 
@@ -800,9 +811,12 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
 #pragma unroll
     for (int u = 0; u < 3; ++u) hv[u] = load(often, rH[u], hoff[u], 0, plane_x);
 
-    // KB coefficients of the block's atoms, alpha applied: 16 slots a round
+    // KB coefficients of the block's atoms, alpha applied: 16 slots a round.  One that
+    // is Inf or NaN is staged as zero, since the zero weights of the rows outside its
+    // atom's support would make it NaN there; its own rows get it at the end.
     const int a0 = blk_atom_off[blk];
     const int na = min(blk_atom_off[blk + 1] - a0, SLOTS);
+    bool bad = false;
     for (int sl = t >> 5; sl < na; sl += 16) {
         const int lm = (t >> 3) & 3;
         const T* src = C + (int64_t(blk_atoms[a0 + sl]) * 4 + lm) * nvec + vbase;
@@ -817,9 +831,17 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
                 if (vbase + e < nvec) c.e[e] = src[e];
         }
 #pragma unroll
-        for (int e = 0; e < N; ++e) c.e[e] *= k.alpha;
+        for (int e = 0; e < N; ++e) {
+            c.e[e] *= k.alpha;
+            if (!isfinite(c.e[e])) {
+                c.e[e] = T(0);
+                bad = true;
+            }
+        }
         *reinterpret_cast<V*>(lds + sl * kSlotBytes + lm * 128 + p * 16) = c;
     }
+    bad = __any(bad);
+    if (lane == 0) odd[wave] = bad;
     auto stage = [&](int z) {
 #pragma unroll
         for (int u = 0; u < 3; ++u) plane[hrow[u]][p] = hv[u];
@@ -962,6 +984,29 @@ hx_tile_kernel(int n_blocks, int n_chunks, int group, const int32_t* __restrict_
             __syncthreads();
         }
     }
+
+    int any = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) any |= odd[i];
+    if (!__builtin_amdgcn_readfirstlane(any)) return;
+    // (everything is formed anew, so that nothing is kept for this in the march)
+    __threadfence_block();               // a thread reads its rows again
+    const int me = int(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
+    const int my_col = 8 * wave + (me >> 3), v0 = chunk * CH + (me & 7) * N;
+    const int32_t* const atoms = rare->blk_atoms + rare->blk_atom_off[blk];
+    for (int z = 0; z < 8; ++z) {
+        const int64_t row = int64_t(blk) * kBlockPts + my_col + 64 * z;
+        for (int en = rare->ent_off[row]; en < rare->ent_off[row + 1]; ++en)
+            for (int vec = v0; vec < min(v0 + N, nvec); ++vec) {
+                T sum = T(0);
+                for (int lm = 0; lm < 4; ++lm) {
+                    const T v = C[(int64_t(atoms[rare->ent_soff[en] / kSlotBytes]) * 4 + lm) * nvec + vec] * k.alpha;
+                    if (!isfinite(v)) sum += rare->ent_beta[4 * int64_t(en) + lm] * v;
+                }
+                T* const y = Y + row * ldy + vec;
+                if (!(sum == T(0))) *y += sum;
+            }
+    }
 }
 
 // weights of the KB row groups in MFMA operand order: lane 16 k + j of entry e
@@ -1017,13 +1062,19 @@ void build_row_groups(chf_ham* H, hipStream_t s) {
             H->ent_soff.as<int32_t>(), src, beta, n_rg);
         LAUNCH_CHECK();
     };
+    const std::vector<TileRare<double>> rare64{{H->ent_off32.as<int32_t>(), H->ent_soff.as<int32_t>(),
+        H->blk_atom_off.as<int32_t>(), H->blk_atoms.as<int32_t>(), H->ent_beta64.as<double>()}};
+    const std::vector<TileRare<float>> rare32{{H->ent_off32.as<int32_t>(), H->ent_soff.as<int32_t>(),
+        H->blk_atom_off.as<int32_t>(), H->blk_atoms.as<int32_t>(), H->ent_beta32.as<float>()}};
     if (H->dtypes & 2) {
         H->rg_beta64.alloc(slot.size() * 64 * sizeof(double));
         fill(H->rg_beta64.as<double>(), H->ent_beta64.as<double>());
+        upload(H->rare64, rare64, s);
     }
     if (H->dtypes & 1) {
         H->rg_beta32.alloc(slot.size() * 64 * sizeof(float));
         fill(H->rg_beta32.as<float>(), H->ent_beta32.as<float>());
+        upload(H->rare32, rare32, s);
     }
     HIP_CHECK(hipStreamSynchronize(s));   // the host lists and dlen go out of scope
 }
@@ -1042,7 +1093,8 @@ static void launch_tile(chf_ham* H, const T* X, int64_t ldx, T* Y, int64_t ldy, 
     hx_tile_kernel<T, PB, SLOTS><<<dim3(unsigned(nt)), dim3(512), 0, s>>>(
         int(H->grid.n_blocks), n_chunks, group, H->block_nbr.as<int32_t>(), H->block_mask.as<uint64_t>(), veff_of<T>(H),
         H->rg_off.as<int32_t>(), H->rg_slot.as<int32_t>(), rg_beta, H->blk_atom_off.as<int32_t>(),
-        H->blk_atoms.as<int32_t>(), C, nvec, X, ldx, Y, ldy, Z, ldz, coef);
+        H->blk_atoms.as<int32_t>(), C, nvec, X, ldx, Y, ldy, Z, ldz,
+        std::is_same<T, double>::value ? H->rare64.as<TileRare<T>>() : H->rare32.as<TileRare<T>>(), coef);
     LAUNCH_CHECK();
 }
 

@@ -187,6 +187,7 @@ struct chf_ham {
     chf::DevBuf rg_off;         // int32 [32 n_blocks + 1]
     chf::DevBuf rg_slot;        // int32 [entries and 8 more]
     chf::DevBuf rg_beta64, rg_beta32;  // [the same][64]
+    chf::DevBuf rare64, rare32; // addresses of the entry tables for the tiled kernel's rare case
     chf::DevBuf blk_atom_off;   // int32 [n_blocks + 1]
     chf::DevBuf blk_atoms;      // int32 [sum of block atom counts]
     chf::DevBuf sup_beta64, ent_beta64;  // double [pairs][4]

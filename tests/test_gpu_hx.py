@@ -462,3 +462,40 @@ def test_neighbour_table_kernel_of_more_than_2_32_threads():
     assert all(not bool(torch.isnan(y.sum())) for y in Y[:, :-8])
     del X, Y
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype,m", [(torch.float64, 16), (torch.float64, 19), (torch.float32, 32), (torch.float32, 38)])
+@pytest.mark.parametrize("n_atoms", [1, 12, 46])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_infinities_reach_the_rows_of_their_operators_only(dtype, m, n_atoms, value):
+    # one value of one vector is Inf or NaN: the rows that the star and the supports
+    # carry it to are those of the neighbour-table kernel, and the other vectors keep
+    # their bits (the tiled kernel multiplies 16 rows at a time by an atom's
+    # coefficients, with zero weights for those outside its support)
+    from paper_2303_00790_amd import binding as B
+    rng = np.random.default_rng(60 + n_atoms)
+    pos = rng.uniform(-2.5, 2.5, size=(n_atoms, 3))
+    g = G.build_grid(9.0, H_SPACING)
+    Hg = B.Hamiltonian(pos, np.zeros(n_atoms, np.int32), OH.PseudoParams(h_s=2.0, h_p=0.5), H_SPACING, 9.0,
+                       B.ORDER_HILBERT, keep_nbr=True)
+    rows = torch.from_numpy(g.row_of_rank).cuda()
+    X = torch.zeros((Hg.n_rows, m), dtype=dtype, device="cuda")
+    X[rows] = torch.from_numpy(random_block(g.n, m, 3400)).to(device="cuda", dtype=dtype)
+    clean, Y, ref = torch.empty_like(X), torch.empty_like(X), torch.empty_like(X)
+    Hg.apply(X, clean)
+    near = np.argsort((g.xyz ** 2).sum(axis=1))         # points in many supports, in one and in none
+    for col, rank in ((0, near[0]), (m // 2, near[len(near) // 2]), (m - 1, near[-1])):
+        Xb = X.clone()
+        Xb[rows[int(rank)], col] = value
+        Hg.apply(Xb, Y)
+        Hg.apply(Xb, ref, generic=True)
+        assert torch.equal(torch.isfinite(Y), torch.isfinite(ref))
+        others = [c for c in range(m) if c != col]
+        assert torch.equal(Y[:, others], clean[:, others])
+        # three steps of the recurrence, in place on the block two steps before
+        out = []
+        for Xf, generic in ((X, False), (Xb, False), (Xb, True)):
+            out.append(Xf.clone())
+            Hg.filter(out[-1], torch.empty_like(Xf), 3, 2.0, 25.0, -3.0, generic=generic)
+        assert torch.equal(torch.isfinite(out[1]), torch.isfinite(out[2]))
+        assert torch.equal(out[1][:, others], out[0][:, others])
