@@ -96,11 +96,10 @@ void check_disjoint(const void* A, size_t bytes_a, const void* B, size_t bytes_b
     const char* b = static_cast<const char*>(B);
     CHF_REQUIRE(a + bytes_a <= b || b + bytes_b <= a, "%s overlap", what);
 }
-// the same of the whole [n_rows][ld] spans
-void check_disjoint(const chf_ham* H, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
-                    const char* what) {
-    const size_t es = dsize(dtype);
-    check_disjoint(A, size_t(H->grid.n_rows) * size_t(lda) * es, B, size_t(H->grid.n_rows) * size_t(ldb) * es, what);
+// from the first value of a block of m columns to its last (columns of a wider block
+// may end where the other block begins)
+size_t block_bytes(const chf_ham* H, int dtype, int64_t ld, int64_t m) {
+    return (size_t(H->grid.n_rows - 1) * size_t(ld) + size_t(m)) * dsize(dtype);
 }
 
 }  // namespace chf
@@ -117,7 +116,8 @@ static int filter_impl(chf_ham* H, chf_dtype dtype, void* X, int64_t ldx, int nv
         check_device(H);
         check_block(H, dtype, X, ldx, nvec, "chebyshev_filter X");
         check_block(H, dtype, work, ldw, std::min<int64_t>(nvec, ldw), "chebyshev_filter work");
-        check_disjoint(H, dtype, X, ldx, work, ldw, "chebyshev_filter: X and work");
+        check_disjoint(X, block_bytes(H, dtype, ldx, nvec), work,
+                       block_bytes(H, dtype, ldw, std::min<int64_t>(nvec, ldw)), "chebyshev_filter: X and work");
         CHF_REQUIRE(degree >= 1 && degree <= 1000, "chebyshev_filter: degree must be in [1, 1000]");
         CHF_REQUIRE(std::isfinite(a) && std::isfinite(b) && std::isfinite(a0), "chebyshev_filter: non-finite bounds");
         CHF_REQUIRE(a < b && a0 < a, "chebyshev_filter: need a0 < a < b");
@@ -399,7 +399,7 @@ int ham_apply(chf_ham* H, chf_dtype dtype, const void* X, int64_t ldx, void* Y, 
         check_device(H);
         check_block(H, dtype, X, ldx, nvec, "ham_apply X");
         check_block(H, dtype, Y, ldy, nvec, "ham_apply Y");
-        check_disjoint(H, dtype, X, ldx, Y, ldy, "ham_apply: X and Y");
+        check_disjoint(X, block_bytes(H, dtype, ldx, nvec), Y, block_bytes(H, dtype, ldy, nvec), "ham_apply: X and Y");
         hipStream_t s = static_cast<hipStream_t>(stream);
         if (dtype == CHF_F64)
             hx_step<double>(H, static_cast<const double*>(X), ldx, static_cast<double*>(Y), ldy, nullptr, 0, nvec, 1.0, 0.0,

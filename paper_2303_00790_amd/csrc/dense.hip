@@ -652,10 +652,8 @@ int rayleigh_ritz(chf_ham* H, chf_ctx* ctx, chf_dtype dtype, void* X, int64_t ld
         check_ctx_block(ctx, dtype, X, ldx, nvec, "rayleigh_ritz X");
         check_ctx_block(ctx, dtype, work, ldw, std::min(nvec, int(ldw)), "rayleigh_ritz work");
         if (!(H->dtypes & (dtype == CHF_F64 ? 2 : 1))) fail(CHF_EINVAL, "rayleigh_ritz: handle not built for dtype");
-        // (X to its last column, so that columns of a wider block may end beside the
-        // work block; the rotation's panels take the work block's rows as one run)
-        const size_t es = dtype == CHF_F64 ? 8 : 4, rows = size_t(H->grid.n_rows);
-        check_disjoint(X, ((rows - 1) * size_t(ldx) + size_t(nvec)) * es, work, rows * size_t(ldw) * es,
+        // (the rotation's panels take the work block's rows as one run)
+        check_disjoint(X, block_bytes(H, dtype, ldx, nvec), work, block_bytes(H, dtype, ldw, ldw),
                        "rayleigh_ritz: X and work");
         // an orthonormal block has at most as many columns as grid points
         // (this also keeps each row panel of the in-place rotation, m values

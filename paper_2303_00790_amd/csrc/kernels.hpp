@@ -42,11 +42,10 @@ void noalloc_scratch_init(int device);
 template <class T>
 void filter_run_noalloc(chf_ham* H, T* X, int64_t ldx, T* W, int64_t ldw, int nvec, int m, double a, double b,
                         double a0, hipStream_t s);
-// CHF_EINVAL unless the bytes, or the [n_rows][ld] spans, of A and B are disjoint
-// (capi.cpp)
+// CHF_EINVAL unless the bytes of A and B are disjoint; the bytes that a block of m
+// columns spans (capi.cpp)
 void check_disjoint(const void* A, size_t bytes_a, const void* B, size_t bytes_b, const char* what);
-void check_disjoint(const chf_ham* H, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
-                    const char* what);
+size_t block_bytes(const chf_ham* H, int dtype, int64_t ld, int64_t m);
 
 // bytes of the KB coefficient scratch an H X launch on nvec vectors needs
 size_t kb_coef_bytes(const chf_ham* H, int nvec, size_t elem_bytes);

@@ -1206,7 +1206,8 @@ int scf_step(chf_scf* S, void* X, int64_t ldx, void* W, int64_t ldw, chf_scf_rep
     return scf_guard([&] {
         if (!S || !X || !W || !rep) fail(CHF_EINVAL, "scf_step: null argument");
         if (ldx < S->prm.nvec || ldw < 1) fail(CHF_EINVAL, "scf_step: need ldx >= nvec and ldw >= 1");
-        check_disjoint(S->H, S->prm.filter_dtype, X, ldx, W, ldw, "scf_step: X and work");
+        check_disjoint(X, block_bytes(S->H, S->prm.filter_dtype, ldx, S->prm.nvec), W,
+                       block_bytes(S->H, S->prm.filter_dtype, ldw, ldw), "scf_step: X and work");
         if (S->prm.filter_dtype == CHF_F64)
             scf_step_t<double>(S, static_cast<double*>(X), ldx, static_cast<double*>(W), ldw, rep, eig_host);
         else

@@ -499,3 +499,27 @@ def test_infinities_reach_the_rows_of_their_operators_only(dtype, m, n_atoms, va
             Hg.filter(out[-1], torch.empty_like(Xf), 3, 2.0, 25.0, -3.0, generic=generic)
         assert torch.equal(torch.isfinite(out[1]), torch.isfinite(out[2]))
         assert torch.equal(out[1][:, others], out[0][:, others])
+
+
+def test_columns_that_end_beside_the_other_block(system):
+    # columns of a wider block whose last row ends where the other block begins share
+    # no memory with it; with one value in common the calls are refused
+    s, B = system, system["B"]
+    a, b, a0 = _bounds(s)
+    n, m = s["Hg"].n_rows, 6
+    buf = torch.zeros(n * (m + 2) + n * m, dtype=torch.float64, device="cuda")
+    wide = buf[:n * (m + 2)].view(n, m + 2)
+    X = wide[:, 2:]
+    X.copy_(to_rows(s, random_block(s["g"].n, m, 3500), torch.float64))
+    ref, Y = torch.empty((n, m), dtype=torch.float64, device="cuda"), buf[n * (m + 2):].view(n, m)
+    s["Hg"].apply(X, ref)
+    s["Hg"].apply(X, Y)
+    assert torch.equal(Y, ref)
+    ref = X.clone()
+    s["Hg"].filter(ref, torch.empty_like(ref), 3, a, b, a0)
+    over = buf[n * (m + 2) - 1:n * (m + 2) - 1 + n * m].view(n, m)
+    for call in (lambda: s["Hg"].apply(X, over), lambda: s["Hg"].filter(X, over, 3, a, b, a0)):
+        with pytest.raises(B.ChfError, match="overlap"):
+            call()
+    s["Hg"].filter(X, Y, 3, a, b, a0)
+    assert torch.equal(X, ref)
