@@ -158,7 +158,8 @@ __device__ inline void invert_upper(double* M, int w) {
 // in registers, their rows by substitution, the rest of the square on the matrix
 // cores: 72 us a block, and 11 + 8 .. 20 for the other two (the library's
 // factorisation: 240 us at M = 128, 2.6 ms at 1024, now 72 us and 0.85 ms, the
-// inverses of the solve included).  *info: 1 + the first column whose pivot is not positive, if it was 0.
+// inverses of the solve included).  *info: 1 + the first column whose pivot is not
+// positive and finite, if it was 0.
 // Z, W: the inverse in operand order of T and FP64 (W null: Z is that).
 template <class T>
 __global__ void __launch_bounds__(512) chol_diag_kernel(int m, int b0, double* __restrict__ S, T* __restrict__ Z,
@@ -183,7 +184,7 @@ __global__ void __launch_bounds__(512) chol_diag_kernel(int m, int b0, double* _
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 double d = from_lane(a[i], i);
-                if (!(d > 0.0)) {
+                if (!__builtin_amdgcn_class(d, 0x180)) {   // normal or subnormal, above zero
                     bad = min(bad, i);
                     d = 1.0;
                 }

@@ -447,6 +447,19 @@ def test_orthonormalize_reports_the_failing_column(system, dtype, col):
         B.orthonormalize(system["ctx"], Xg)
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("m", [1, 16, 129])
+def test_orthonormalize_stops_at_an_infinite_pivot(system, dtype, m):
+    """an infinite value makes its column's norm infinite, and with the shift of
+    the last attempt every pivot: the first one is named, also of a single column
+    (behind whose square there is no second one)"""
+    B = system["B"]
+    X = torch.from_numpy(np.random.default_rng(m).standard_normal((400, m))).to("cuda", dtype)
+    X[7, m - 1] = float("inf")
+    with pytest.raises(B.ChfError, match=r"CHF_ENOTPD: .*minor 1\)"):
+        B.orthonormalize(system["ctx"], X)
+
+
 @pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-13), (torch.float32, 2e-6)])
 @pytest.mark.parametrize("m", [1, 15, 17, 31, 97, 128, 129])
 def test_rayleigh_ritz_rotation_in_place(system, dtype, tol, m):
